@@ -47,7 +47,7 @@ struct oc_mlp {
 namespace {
 
 struct MlpLayout {
-  uint64_t master, m1, m2, grad, w1b, w2b, w2bt, w3b, xb, z1, h1, z2, h2, y, dy, dyb, dz2, dz2b, dz1,
+  uint64_t master, m1, m2, grad, w1b, w2b, w2bt, w3b, w1f, w2f, w3f, xb, z1, h1, z2, h2, y, dy, dyb, dz2, dz2b, dz1,
       dz1b, partial, part, total;
 };
 
@@ -65,6 +65,9 @@ MlpLayout mlp_layout(int B) {
   L.w2b = take((uint64_t)MLP_NH * MLP_NH * 2);
   L.w2bt = take((uint64_t)MLP_NH * MLP_NH * 2);
   L.w3b = take((uint64_t)MLP_NOUTP * MLP_NH * 2);
+  L.w1f = take((uint64_t)MLP_NH * MLP_KIN * 2);
+  L.w2f = take((uint64_t)MLP_NH * MLP_NH * 2);
+  L.w3f = take((uint64_t)16 * MLP_NH * 2);
   L.xb = take((uint64_t)B * MLP_KIN * 2);
   L.z1 = take((uint64_t)B * MLP_NH * 4);
   L.h1 = take((uint64_t)B * MLP_NH * 2);
@@ -176,12 +179,10 @@ int read_loss(oc_mlp* m, int B, double* loss, hipStream_t s) {
 
 namespace oc {
 
-__bf16* mlp_input(oc_mlp* net) { return net->xb; }
 const float* mlp_output(oc_mlp* net) { return net->y; }
 float* mlp_output_rw(oc_mlp* net) { return net->y; }
 const MlpParams& mlp_params(const oc_mlp* net) { return net->p; }
 int mlp_max_batch(const oc_mlp* net) { return net->max_batch; }
-int mlp_run_forward(oc_mlp* net, int batch, hipStream_t s) { return forward_from_xb(net, batch, s); }
 
 int mlp_params_finite(oc_mlp* net, hipStream_t s) {
   std::vector<float> p(MLP_NPARAM);
@@ -232,6 +233,9 @@ int oc_mlp_create(int32_t max_batch, void* workspace, uint64_t bytes, oc_mlp** o
   m->p.W2b = (__bf16*)(w + L.w2b);
   m->p.W2bT = (__bf16*)(w + L.w2bt);
   m->p.W3b = (__bf16*)(w + L.w3b);
+  m->p.W1f = (__bf16*)(w + L.w1f);
+  m->p.W2f = (__bf16*)(w + L.w2f);
+  m->p.W3f = (__bf16*)(w + L.w3f);
   m->m1 = (float*)(w + L.m1);
   m->m2 = (float*)(w + L.m2);
   m->grad = (float*)(w + L.grad);
@@ -292,11 +296,7 @@ int oc_mlp_forward(oc_mlp* m, const float* x, int32_t batch, float* y, void* str
   int rc = check_batch(m, batch);
   if (rc) return rc;
   if (!x || !y) { set_error("NULL argument"); return OC_ERR_ARG; }
-  hipStream_t s = (hipStream_t)stream;
-  OC_CHECK_HIP(launch_features_to_bf16(x, batch, m->xb, s));
-  rc = forward_from_xb(m, batch, s);
-  if (rc) return rc;
-  OC_CHECK_HIP(hipMemcpyAsync(y, m->y, (size_t)batch * MLP_NOUT * 4, hipMemcpyDeviceToDevice, s));
+  OC_CHECK_HIP(launch_mlp_forward(m->p, x, batch, y, (hipStream_t)stream));
   return OC_OK;
 }
 

@@ -14,17 +14,30 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
+// Fragment-major weight copies: the 16 output rows x 32 inputs that one MFMA
+// takes as an operand are one contiguous kilobyte in lane order (lane l
+// holds 8 consecutive k of row l % 16, k block l / 16), the k blocks of a
+// row block following each other.  A wave's operand load is then one
+// coalesced 16-byte load per lane.
+__host__ __device__ inline int frag_at(int n, int k, int kblocks) {
+  return ((n >> 4) * kblocks + (k >> 5)) * 512 + (((k >> 3) & 3) * 16 + (n & 15)) * 8 + (k & 7);
+}
+
 __device__ void mlp_write_bf16(const MlpParams& p, int t, float w) {
   // master layout: W1 (256 x 500) | b1 | W2 (256 x 256) | b2 | W3 (4 x 256) | b3
   if (t < MLP_OFF_B1) {
     const int r = t / 500, c = t % 500;
     p.W1b[r * 512 + c] = (__bf16)w;
+    p.W1f[frag_at(r, c, MLP_KIN / 32)] = (__bf16)w;
   } else if (t >= MLP_OFF_W2 && t < MLP_OFF_B2) {
     const int r = (t - MLP_OFF_W2) / MLP_NH, c = (t - MLP_OFF_W2) % MLP_NH;
     p.W2b[r * MLP_NH + c] = (__bf16)w;
     p.W2bT[c * MLP_NH + r] = (__bf16)w;   // transposed copy for the backward pass
+    p.W2f[frag_at(r, c, MLP_NH / 32)] = (__bf16)w;
   } else if (t >= MLP_OFF_W3 && t < MLP_OFF_B3) {
+    const int r = (t - MLP_OFF_W3) / MLP_NH, c = (t - MLP_OFF_W3) % MLP_NH;
     p.W3b[t - MLP_OFF_W3] = (__bf16)w;
+    p.W3f[frag_at(r, c, MLP_NH / 32)] = (__bf16)w;
   }
 }
 
@@ -458,100 +471,299 @@ __global__ void __launch_bounds__(256) closure_features_kernel(Dims d, const T* 
   xb[t] = (f < 500) ? (__bf16)feature_value(d, u, v, w, tt, ss, st, cell, f) : (__bf16)0.0f;
 }
 
-// The closure network on every cell of a model, fused.  A workgroup (4
-// waves) takes 64 consecutive cells, gathers their standardised 5x5x5
-// (u, v, w, b) neighbourhoods 64 features at a time (im2col: the walk over
-// (variable, offset) is uniform per wave and runs on the scalar unit) and
-// multiplies them by W1 with MFMA.  The 64 x 256 activations stay in LDS as
-// the A operand of the second layer; the third layer is one MFMA column
-// block (outputs padded to 16).  The next k chunk's features and weights are
-// loaded into registers while the current one is multiplied.  Only y (4 per
-// cell) goes to memory.  Operand rounding matches the unfused path: BF16
-// inputs, weights and activations, FP32 accumulation.
-constexpr int FZ_BM = 64, FZ_BK = 64, FZ_LDP = FZ_BK + 8, FZ_HP = MLP_NH + 8;
+// ---------------------------------------------------------------------------
+// The network on 16 MI rows (cells), from staged features to the four
+// outputs, by a workgroup of four waves.  Wave wv computes outputs
+// [64 wv, 64 wv + 64) of the two wide layers for every row, transposed
+// (C^T = W H^T: weights as the first MFMA operand, rows as the second), so
+// that a lane's four results are four consecutive outputs of one row and go
+// to LDS in one 8-byte store.  The weights come from L2 straight into
+// registers in operand order (one contiguous kilobyte per MFMA operand; with
+// row-major weights the same loads touched sixteen 64-byte pieces each and
+// the in-model kernel took 240 us at 64^3 instead of 157), NET_D chunks ahead
+// of their use and across the layers.  Activations stay in LDS as the operand
+// of the next layer; operands are rounded to BF16, sums are FP32 in ascending
+// k.  Bound by issue: the two GELU epilogues (about 20 vector slots per
+// activation, 65 us at 262144 rows) and the MFMAs (41 us) share the SIMDs
+// with the staging.  64 rows, weights two chunks ahead and two workgroups'
+// registers measured best at 262144 rows: 187 us, against 214 (128 rows),
+// 226 (32 rows), 197 (weights one chunk ahead), 209 (a register cap for
+// three waves per SIMD, spills) and 188-190 (features two or three blocks
+// ahead).
+//
+// stage(b) writes features 64 b .. 64 b + 63 of every row to columns
+// 64 (b % 2) .. of `sx` (pitch NET_SP); out(i, c) takes the outputs of row
+// block i (lanes 0..15: row 16 i + lane, the four outputs in c).  `sx` and the
+// stager's own tables may share LDS with `hs`: they are dead before the
+// first activation is stored.
+// ---------------------------------------------------------------------------
+constexpr int NET_HP = MLP_NH + 8, NET_SP = 2 * 64 + 8, NET_D = 2;
+constexpr int NET_S1 = MLP_KIN / 32, NET_S2 = MLP_NH / 32;   // k chunks per layer
 
-template <class T>
-__global__ void __launch_bounds__(256) closure_mlp_fused_kernel(Dims d, const T* u, const T* v,
-                                                               const T* w, const T* tt,
-                                                               const T* ss, ClosureStats st,
-                                                               MlpParams p, float* y) {
-  __shared__ __bf16 Ws[MLP_NH][FZ_LDP];      // weight chunk, rows = outputs
-  __shared__ __bf16 Hs[FZ_BM][FZ_HP];        // layer activations; layer 1 uses its
-                                             // first FZ_LDP columns for the features
-  const long ncell = (long)d.nx * d.ny * d.nz;
-  const long c0 = (long)blockIdx.x * FZ_BM;
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wv = tid >> 6;   // wave wv: output columns [64 wv, +64)
-  const float* b1 = p.master + MLP_OFF_B1;
-  const float* b2 = p.master + MLP_OFF_B2;
-  const float* b3 = p.master + MLP_OFF_B3;
+__device__ inline bf16x8 ldfrag(const __bf16* f, int block) {
+  return *(const __attribute__((address_space(1))) bf16x8*)(f + (long)block * 512 +
+                                                            (threadIdx.x & 63) * 8);
+}
 
-  f32x4 acc[4][4];
+template <int MI, class Stage, class Out>
+__device__ inline void net_rows(const MlpParams& p, __bf16* hs, const __bf16* sx, Stage& stage,
+                                const Out& out) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int lr = lane & 15, lg = lane >> 4;
+  auto load_b = [&](int s, bf16x8* b) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      b[j] = s < NET_S1 ? ldfrag(p.W1f, (wv * 4 + j) * NET_S1 + s)
+                        : ldfrag(p.W2f, (wv * 4 + j) * NET_S2 + s - NET_S1);
+  };
+  f32x4 acc[MI][4];
   auto zero = [&]() {
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < MI; ++i)
 #pragma unroll
       for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   };
-  // acc += A[64 rows][ka .. ka + 64) * Ws^T (A = Hs, pitch FZ_HP)
-  auto mma = [&](int ka) {
+  auto mma = [&](const __bf16* rows, int pitch, int k0, const bf16x8* b) {
 #pragma unroll
-    for (int ks = 0; ks < FZ_BK; ks += 32) {
-      bf16x8 a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        a[i] = *(const bf16x8*)&Hs[i * 16 + (lane & 15)][ka + ks + 8 * (lane >> 4)];
+    for (int i = 0; i < MI; ++i) {
+      const bf16x8 a = *(const bf16x8*)&rows[(i * 16 + lr) * pitch + k0 + 8 * lg];
 #pragma unroll
       for (int j = 0; j < 4; ++j)
-        b[j] = *(const bf16x8*)&Ws[wv * 64 + j * 16 + (lane & 15)][ks + 8 * (lane >> 4)];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[j], a, acc[i][j], 0, 0, 0);
     }
   };
-  // weight chunk in registers: rows (tid >> 3) + 32 c, k offset 8 (tid & 7)
-  bf16x8 wreg[8];
-  auto load_w = [&](const __bf16* W, int ldw, int k0) {
-#pragma unroll
-    for (int c = 0; c < 8; ++c)
-      wreg[c] = *(const bf16x8*)(W + (long)((tid >> 3) + 32 * c) * ldw + k0 + (tid & 7) * 8);
-  };
-  auto stash_w = [&]() {
-#pragma unroll
-    for (int c = 0; c < 8; ++c) *(bf16x8*)&Ws[(tid >> 3) + 32 * c][(tid & 7) * 8] = wreg[c];
-  };
+  // acc[i][j][e]: row 16 i + lane % 16, output wv 64 + 16 j + 4 (lane / 16) + e
   auto store_h = [&](const float* bias) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int j = 0; j < 4; ++j) {
+      const int n = wv * 64 + j * 16 + 4 * lg;
+      const f32x4 bn = *(const __attribute__((address_space(1))) f32x4*)(bias + n);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int n = wv * 64 + j * 16 + (lane & 15);
-        const float bn = bias[n];
+      for (int i = 0; i < MI; ++i) {
+        bf16x4 h;
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-          Hs[i * 16 + 4 * (lane >> 4) + e][n] = (__bf16)gelu(acc[i][j][e] + bn);
+        for (int e = 0; e < 4; ++e) h[e] = (__bf16)gelu(acc[i][j][e] + bn[e]);
+        *(bf16x4*)&hs[(i * 16 + lr) * NET_HP + n] = h;
       }
+    }
   };
+  bf16x8 wb[NET_D][4];
+#pragma unroll
+  for (int s = 0; s < NET_D; ++s) load_b(s, wb[s]);
 
-  // ---- gather: cell gc (lane), features gf .. gf + 15 (gf uniform per wave)
-  const int gc = lane;
-  const int gf = __builtin_amdgcn_readfirstlane(wv * 16);
-  const long cell = c0 + gc;
-  const bool live = cell < ncell;
-  int corner = 0;   // padded offset of the neighbourhood corner (i-2, j-2, k-2)
-  if (live) {
-    const int ci = (int)(cell % d.nx);
-    const int cj = (int)((cell / d.nx) % d.ny);
-    const int ck = (int)(cell / ((long)d.nx * d.ny));
-    corner = (int)pidx(d, ci - 2, cj - 2, ck - 2);
+  // layer 1: two 32-deep chunks per barrier.  Block b uses half b % 2 of sx;
+  // a wave writes a half only after the barrier of the block in between,
+  // which every wave reaches after its products of the block that last read
+  // the half.
+  zero();
+#pragma unroll
+  for (int b = 0; b < NET_S1 / 2; ++b) {
+    stage(b);
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int s = 2 * b + q;
+      mma(sx, NET_SP, (b & 1) * 64 + q * 32, wb[s % NET_D]);
+      load_b(s + NET_D, wb[s % NET_D]);
+    }
   }
-  const int sy = (int)d.sy, sz = (int)d.sz;
+  __syncthreads();                  // every wave's last feature reads are done
+  store_h(p.master + MLP_OFF_B1);
+  __syncthreads();
+
+  // layer 2: no barriers
+  zero();
+#pragma unroll
+  for (int s = NET_S1; s < NET_S1 + NET_S2; ++s) {
+    mma(hs, NET_HP, (s - NET_S1) * 32, wb[s % NET_D]);
+    if (s + NET_D < NET_S1 + NET_S2) load_b(s + NET_D, wb[s % NET_D]);
+  }
+  __syncthreads();                  // every wave's reads of the layer-1 activations are done
+  store_h(p.master + MLP_OFF_B2);
+  __syncthreads();
+
+  // layer 3 (outputs padded to 16): wave wv takes row blocks wv, wv + 4, ...
+  const float* b3 = p.master + MLP_OFF_B3;
+#pragma unroll
+  for (int i0 = 0; i0 < MI; i0 += 4) {
+    const int i = i0 + wv;
+    if (i >= MI) break;             // uniform per wave
+    f32x4 c3 = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < NET_S2; ++s)
+      c3 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+          ldfrag(p.W3f, s), *(const bf16x8*)&hs[(i * 16 + lr) * NET_HP + s * 32 + 8 * lg], c3, 0,
+          0, 0);
+#pragma unroll
+    for (int e = 0; e < MLP_NOUT; ++e) c3[e] += b3[e];
+    if (lg == 0) out(i, c3);
+  }
+}
+
+// Features from rows of 500 FP32 (oc_mlp_forward): a block of 64 features is
+// loaded 256 bytes per row (16 bytes per lane) one block ahead, rounded and
+// stored to LDS.  Rows past the batch repeat its last row.
+template <int MI>
+struct RowStage {
+  const float* x;
+  __bf16* sx;
+  int row0, last;
+  f32x4 r[MI];
+  __device__ inline void load(int b) {
+    const int f = b * 64 + (threadIdx.x & 15) * 4, t = threadIdx.x >> 4;
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+      r[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (f < MLP_NIN) r[i] = ld4(x, (long)min(row0 + 16 * i + t, last) * MLP_NIN + f);
+    }
+  }
+  __device__ inline void operator()(int b) {
+    const int c = (b & 1) * 64 + (threadIdx.x & 15) * 4, t = threadIdx.x >> 4;
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+      bf16x4 h;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) h[e] = (__bf16)r[i][e];
+      *(bf16x4*)&sx[(16 * i + t) * NET_SP + c] = h;
+    }
+    if (b + 1 < NET_S1 / 2) load(b + 1);
+  }
+};
+
+// Inference from FP32 rows in one pass: each feature is read once (524 MB at
+// 262144 rows) and only the outputs are written; 787 us (a conversion pass
+// and three products through memory) -> 187 us, 2.8 TB/s.
+template <int MI>
+__global__ void __launch_bounds__(256, 2) mlp_forward_kernel(MlpParams p, const float* x, int B,
+                                                             float* y) {
+  __shared__ __attribute__((aligned(16))) __bf16 hs[MI * 16 * NET_HP];
+  RowStage<MI> st;
+  st.x = x;
+  st.sx = hs;      // features first, activations once the first layer is done
+  st.row0 = (int)blockIdx.x * MI * 16;
+  st.last = B - 1;
+  st.load(0);
+  net_rows<MI>(p, hs, hs, st, [&](int i, f32x4 c) {
+    const int row = st.row0 + 16 * i + (int)(threadIdx.x & 15);
+    if (row < B)
+      *(__attribute__((address_space(1))) v4u<float>*)(y + (long)row * MLP_NOUT) = c;
+  });
+}
+
+// The closure network on every cell of a model: 16 MI consecutive cells per
+// workgroup, whose features are the standardised (u, v, w, b) in the 5 x 5 x
+// 5 neighbourhoods.
+//
+// Rows of GW consecutive cells share an x row, so the standardised BF16
+// values over their whole 5 x 5 x (GW + 4) neighbourhood regions are loaded
+// once (coalesced along x) into LDS, and each block of features is copied
+// out of the region (im2col in LDS).
+constexpr int RG_ROWS = 4 * 25 + 1;                         // + a row of zeros
+constexpr int rg_pitch(int gw) { return gw + 8; }
+
+// Element offset in the region buffer of input feature f: variable f / 125
+// (u, v, w, b), row 25 var + 5 dk + dj and column di, where (dk, dj, di) are
+// the base-5 digits of f % 125; the padding features past the 500 inputs
+// read the row of zeros.
+struct RgOffsets {
+  unsigned short v[MLP_KIN];
+};
+constexpr RgOffsets make_rg_offsets(int pitch) {
+  RgOffsets t{};
+  for (int f = 0; f < MLP_KIN; ++f) {
+    if (f >= MLP_NIN) {
+      t.v[f] = (unsigned short)((RG_ROWS - 1) * pitch);
+      continue;
+    }
+    const int var = f / 125, o = f % 125;
+    t.v[f] = (unsigned short)((var * 25 + o / 5) * pitch + o % 5);
+  }
+  return t;
+}
+__constant__ RgOffsets kRgOff64 = make_rg_offsets(rg_pitch(64));
+__constant__ RgOffsets kRgOff32 = make_rg_offsets(rg_pitch(32));
+
+template <int MI, int GW>
+struct RegionStage {
+  const __bf16* rg;
+  __bf16* sx;
+  // cell `lane` + 64 m of the workgroup; wave wv copies features 64 b + 16 wv .. + 15
+  __device__ inline void operator()(int b) const {
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int f0 = __builtin_amdgcn_readfirstlane(b * 64 + 16 * wv);
+    const unsigned short* off = GW == 64 ? kRgOff64.v : kRgOff32.v;
+#pragma unroll
+    for (int m = 0; m < MI / 4; ++m) {
+      const int c = lane + 64 * m;
+      const __bf16* r = rg + (c / GW) * (RG_ROWS * rg_pitch(GW)) + c % GW;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        bf16x8 xv;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) xv[q] = r[off[f0 + 8 * h + q]];
+        *(bf16x8*)&sx[c * NET_SP + (b & 1) * 64 + 16 * wv + 8 * h] = xv;
+      }
+    }
+  }
+};
+
+template <class T, int MI, int GW>
+__global__ void __launch_bounds__(256, 2) closure_mlp_region_kernel(Dims d, const T* u, const T* v,
+                                                                const T* w, const T* tt,
+                                                                const T* ss, ClosureStats st,
+                                                                MlpParams p, float* y) {
+  constexpr int MR = MI * 16, NG = MR / GW, RX = GW + 4, RP = rg_pitch(GW);
+  constexpr int SX = MR * NET_SP, LDS = SX + NG * RG_ROWS * RP;
+  constexpr int HS = MR * NET_HP;
+  __shared__ __attribute__((aligned(16))) __bf16 lds[LDS > HS ? LDS : HS];
+  __bf16* sx = lds;
+  __bf16* rg = lds + SX;
+  const int c0 = (int)blockIdx.x * MR;
+  // the neighbourhood regions, standardised, in BF16 (compile-time trip
+  // count: every load of a region is in flight before the first is used)
+#pragma unroll
+  for (int g = 0; g < NG; ++g) {
+    const int cg = c0 + g * GW;
+    const int i0 = cg % d.nx, jk = cg / d.nx;
+    const int j0 = jk % d.ny, k0 = jk / d.ny;
+    __bf16* R = rg + g * RG_ROWS * RP;
+#pragma unroll
+    for (int q = 0; q < (25 * RX + 255) / 256; ++q) {
+      const int e = (int)threadIdx.x + q * 256;
+      if (e >= 25 * RX) break;
+      const int row = e / RX, x = e - row * RX;
+      const int dk = row / 5, dj = row - dk * 5;
+      const long pp = pidx(d, i0 - 2 + x, j0 - 2 + dj, k0 - 2 + dk);
+      R[row * RP + x] = (__bf16)(((float)u[pp] - st.in_mean[0]) * st.in_rstd[0]);
+      R[(25 + row) * RP + x] = (__bf16)(((float)v[pp] - st.in_mean[1]) * st.in_rstd[1]);
+      R[(50 + row) * RP + x] = (__bf16)(((float)w[pp] - st.in_mean[2]) * st.in_rstd[2]);
+      const float b =
+          st.g_alpha * ((float)tt[pp] - st.t_ref) - st.g_beta * ((float)ss[pp] - st.s_ref);
+      R[(75 + row) * RP + x] = (__bf16)((b - st.in_mean[3]) * st.in_rstd[3]);
+    }
+    if ((int)threadIdx.x < RP) R[(RG_ROWS - 1) * RP + threadIdx.x] = (__bf16)0.0f;
+  }
+  __syncthreads();
+  RegionStage<MI, GW> stage{rg, sx};
+  net_rows<MI>(p, lds, sx, stage, [&](int i, f32x4 c) {
+    *(__attribute__((address_space(1))) f32x4*)(
+        y + (long)(c0 + 16 * i + (int)(threadIdx.x & 15)) * MLP_NOUT) = c;
+  });
+}
+
+// Any x length (rows of 8 or 16 cells): the features gathered from memory
+// 64 at a time, one block ahead of their use; the walk over (variable,
+// offset) is uniform per wave and runs on the scalar unit.
+template <class T>
+struct GatherStage {
+  const T *u, *v, *w, *tt, *ss;
+  const ClosureStats& st;
+  __bf16* sx;
+  int corner, sy, sz;   // padded offset of the neighbourhood corner (i-2, j-2, k-2)
+  bool live;
   float graw[16], sraw[16];
-  bf16x8 xreg[2];
-  auto gather_load = [&](int k0) {
-    int f = k0 + gf;   // uniform: the walk below is scalar
+  __device__ inline void load(int b) {
+    int f = __builtin_amdgcn_readfirstlane(b * 64 + (int)(threadIdx.x >> 6) * 16);
     int var = f / 125, o = f - var * 125;
     int dk = o / 25, dj = (o - dk * 25) / 5, di = o - dk * 25 - dj * 5;
 #pragma unroll
@@ -567,268 +779,49 @@ __global__ void __launch_bounds__(256) closure_mlp_fused_kernel(Dims d, const T*
       }
       if (++di == 5) { di = 0; if (++dj == 5) { dj = 0; if (++dk == 5) { dk = 0; ++var; } } }
     }
-  };
-  auto gather_convert = [&](int k0) {
-    int f = k0 + gf;
+  }
+  __device__ inline void operator()(int b) {
+    int f = __builtin_amdgcn_readfirstlane(b * 64 + (int)(threadIdx.x >> 6) * 16);
     int var = f / 125;
     int o = f - var * 125;
+    bf16x8 xv[2];
 #pragma unroll
     for (int q = 0; q < 16; ++q, ++f) {
       const int vq = var < 4 ? var : 3;
       const float raw = vq == 3 ? st.g_alpha * (graw[q] - st.t_ref) - st.g_beta * (sraw[q] - st.s_ref)
                                 : graw[q];
       const float x = (live && f < MLP_NIN) ? (raw - st.in_mean[vq]) * st.in_rstd[vq] : 0.f;
-      xreg[q >> 3][q & 7] = (__bf16)x;
+      xv[q >> 3][q & 7] = (__bf16)x;
       if (++o == 125) { o = 0; ++var; }
     }
-  };
-
-  // ---- layer 1: 8 chunks of 64 features (500 real, zero padding to 512),
-  // staged in the first FZ_BK columns of Hs
-  zero();
-  gather_load(0);
-  gather_convert(0);
-  load_w(p.W1b, MLP_KIN, 0);
-  for (int k0 = 0; k0 < MLP_KIN; k0 += FZ_BK) {
-    *(bf16x8*)&Hs[gc][gf] = xreg[0];
-    *(bf16x8*)&Hs[gc][gf + 8] = xreg[1];
-    stash_w();
-    __syncthreads();
-    const bool more = k0 + FZ_BK < MLP_KIN;
-    if (more) {                   // next chunk's loads in flight during the multiply
-      gather_load(k0 + FZ_BK);
-      load_w(p.W1b, MLP_KIN, k0 + FZ_BK);
-    }
-    mma(0);
-    if (more) gather_convert(k0 + FZ_BK);
-    __syncthreads();
+    __bf16* at = &sx[(threadIdx.x & 63) * NET_SP + (b & 1) * 64 + (threadIdx.x >> 6) * 16];
+    *(bf16x8*)at = xv[0];
+    *(bf16x8*)(at + 8) = xv[1];
+    if (b + 1 < NET_S1 / 2) load(b + 1);
   }
-  store_h(b1);
-
-  // ---- layer 2: A = the layer-1 activations in Hs, 4 chunks of W2
-  zero();
-  load_w(p.W2b, MLP_NH, 0);
-  for (int k0 = 0; k0 < MLP_NH; k0 += FZ_BK) {
-    stash_w();
-    __syncthreads();    // (first chunk: also orders the Hs writes above)
-    if (k0 + FZ_BK < MLP_NH) load_w(p.W2b, MLP_NH, k0 + FZ_BK);
-    mma(k0);
-    __syncthreads();
-  }
-  store_h(b2);          // every wave has finished reading Hs (barrier above)
-  __syncthreads();
-
-  // ---- layer 3: wave wv takes rows [16 wv, +16) against W3 rows 0..15
-  // (rows >= 4 are zero): 8 MFMAs over k
-  {
-    f32x4 c3 = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int ks = 0; ks < MLP_NH; ks += 32) {
-      const bf16x8 a = *(const bf16x8*)&Hs[wv * 16 + (lane & 15)][ks + 8 * (lane >> 4)];
-      const bf16x8 b = *(const bf16x8*)(p.W3b + (long)(lane & 15) * MLP_NH + ks + 8 * (lane >> 4));
-      c3 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c3, 0, 0, 0);
-    }
-    const int o = lane & 15;
-    if (o < MLP_NOUT)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const long c = c0 + wv * 16 + 4 * (lane >> 4) + e;
-        if (c < ncell) y[c * MLP_NOUT + o] = c3[e] + b3[o];
-      }
-  }
-}
-
-// The same network for grids whose x rows hold a multiple of 64 cells: the
-// 64 cells of a workgroup share one x row, so the standardised BF16 values
-// of (u, v, w, b) over their whole 5 x 5 x 68 neighbourhood region are
-// loaded once (coalesced along x) into LDS, and every 32-deep k chunk of
-// features is copied out of that region (im2col in LDS, double-buffered
-// column blocks, one barrier per chunk).  Each wave's B operands (its 64
-// output rows of the weights, k contiguous) go from global memory (L2)
-// straight into registers in the MFMA operand layout, RG_D chunks ahead of
-// their use: no weight staging in LDS, and the second layer runs without
-// barriers.  The weight prefetch crosses from the first layer into the
-// second.
-constexpr int RG_X = FZ_BM + 4, RG_P = RG_X + 4, RG_D = 2;
-constexpr int RG_S1 = MLP_KIN / 32, RG_S2 = MLP_NH / 32;   // k chunks per layer
-constexpr int RG_ROWS = 4 * 25 + 1;                         // + a row of zeros
-// k chunks of features staged per barrier (two blocks alternate in the
-// first 4 RG_BLK 32 columns of the activation buffer): 16 -> 8 barriers
-// per layer, 0.259 -> 0.252 ms per substage at 64^3; four chunks per
-// barrier measured 0.256 ms
-constexpr int RG_BLK = 2;
-static_assert(2 * RG_BLK * 32 <= MLP_NH && RG_S1 % RG_BLK == 0, "staging blocks");
-
-// Element offset in the region buffer of input feature f: variable f / 125
-// (u, v, w, b), row 25 var + 5 dk + dj and column di, where (dk, dj, di) are
-// the base-5 digits of f % 125; the padding features past the 500 inputs
-// read the row of zeros.
-struct RgOffsets {
-  unsigned short v[MLP_KIN];
 };
-constexpr RgOffsets make_rg_offsets() {
-  RgOffsets t{};
-  for (int f = 0; f < MLP_KIN; ++f) {
-    if (f >= MLP_NIN) {
-      t.v[f] = (unsigned short)((RG_ROWS - 1) * RG_P);
-      continue;
-    }
-    const int var = f / 125, o = f % 125;
-    t.v[f] = (unsigned short)((var * 25 + o / 5) * RG_P + o % 5);
-  }
-  return t;
-}
-__constant__ RgOffsets kRgOff = make_rg_offsets();
 
 template <class T>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
-closure_mlp_region_kernel(Dims d, const T* u, const T* v,
+__global__ void __launch_bounds__(256) closure_mlp_gather_kernel(Dims d, const T* u, const T* v,
                                                                 const T* w, const T* tt,
                                                                 const T* ss, ClosureStats st,
                                                                 MlpParams p, float* y) {
-  __shared__ __bf16 Rg[RG_ROWS][RG_P];       // (25 var + 5 dk + dj, x - (i0 - 2)); zero row
-  __shared__ __bf16 Hs[FZ_BM][FZ_HP];        // activations; layer 1 stages features here
-  const long c0 = (long)blockIdx.x * FZ_BM;
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wv = tid >> 6;
-  const int i0 = (int)(c0 % d.nx);
-  const int j0 = (int)((c0 / d.nx) % d.ny);
-  const int k0c = (int)(c0 / ((long)d.nx * d.ny));
-  const float* b1 = p.master + MLP_OFF_B1;
-  const float* b2 = p.master + MLP_OFF_B2;
-  const float* b3 = p.master + MLP_OFF_B3;
-
-  // this wave's B operands of k chunk s (s < RG_S1: W1; then W2): lane
-  // holds 8 consecutive k of output row wv 64 + 16 j + lane % 16
-  auto load_b = [&](int s, bf16x8* b) {
-    const bool l1 = s < RG_S1;
-    const __bf16* W = l1 ? p.W1b : p.W2b;
-    const int ldw = l1 ? MLP_KIN : MLP_NH;
-    const int kk = (l1 ? s : s - RG_S1) * 32;
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-      b[j] = *(const __attribute__((address_space(1))) bf16x8*)(
-          W + (long)(wv * 64 + j * 16 + (lane & 15)) * ldw + kk + 8 * (lane >> 4));
-  };
-  bf16x8 wb[RG_D][4];
-#pragma unroll
-  for (int s = 0; s < RG_D; ++s) load_b(s, wb[s]);
-
-  // ---- the neighbourhood region, standardised, in BF16 (compile-time trip
-  // count: every load of the region is in flight before the first is used)
-#pragma unroll
-  for (int q = 0; q < (25 * RG_X + 255) / 256; ++q) {
-    const int e = tid + q * 256;
-    if (e >= 25 * RG_X) break;
-    const int row = e / RG_X, x = e - row * RG_X;
-    const int dk = row / 5, dj = row - dk * 5;
-    const long pp = pidx(d, i0 - 2 + x, j0 - 2 + dj, k0c - 2 + dk);
-    Rg[row][x] = (__bf16)(((float)u[pp] - st.in_mean[0]) * st.in_rstd[0]);
-    Rg[25 + row][x] = (__bf16)(((float)v[pp] - st.in_mean[1]) * st.in_rstd[1]);
-    Rg[50 + row][x] = (__bf16)(((float)w[pp] - st.in_mean[2]) * st.in_rstd[2]);
-    const float b = st.g_alpha * ((float)tt[pp] - st.t_ref) - st.g_beta * ((float)ss[pp] - st.s_ref);
-    Rg[75 + row][x] = (__bf16)((b - st.in_mean[3]) * st.in_rstd[3]);
+  __shared__ __attribute__((aligned(16))) __bf16 hs[64 * NET_HP];
+  const int ncell = d.nx * d.ny * d.nz;
+  const int c0 = (int)blockIdx.x * 64, cell = c0 + (int)(threadIdx.x & 63);
+  const bool live = cell < ncell;
+  int corner = 0;
+  if (live) {
+    const int jk = cell / d.nx;
+    corner = (int)pidx(d, cell % d.nx - 2, jk % d.ny - 2, jk / d.ny - 2);
   }
-  if (tid < RG_P) Rg[RG_ROWS - 1][tid] = (__bf16)0.0f;
-
-  f32x4 acc[4][4];
-  auto zero = [&]() {
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  };
-  // one 32-deep k chunk, computed transposed: C^T = W H^T, weights (from
-  // registers) as the first operand and the cells' features or
-  // activations (Hs columns [ka, ka + 32)) as the second, so that a lane's
-  // four results are four consecutive outputs of one cell
-  auto mma = [&](int ka, const bf16x8* b) {
-    bf16x8 a[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      a[i] = *(const bf16x8*)&Hs[i * 16 + (lane & 15)][ka + 8 * (lane >> 4)];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[j], a[i], acc[i][j], 0, 0, 0);
-  };
-  // acc[i][j][e]: cell 16 i + lane % 16, output wv 64 + 16 j + 4 (lane / 16) + e
-  auto store_h = [&](const float* bias) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int n = wv * 64 + j * 16 + 4 * (lane >> 4);
-      const f32x4 bn = *(const __attribute__((address_space(1))) f32x4*)(bias + n);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        bf16x4 h;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) h[e] = (__bf16)gelu(acc[i][j][e] + bn[e]);
-        *(bf16x4*)&Hs[i * 16 + (lane & 15)][n] = h;
-      }
-    }
-  };
-  // features [kk, kk + 32) of cell `lane`: wave wv writes features kk + 8 wv .. + 7
-  auto stage_x = [&](int kk) {
-    const int f0 = __builtin_amdgcn_readfirstlane(kk + 8 * wv);
-    const __bf16* rg = &Rg[0][0] + lane;
-    bf16x8 xv;
-#pragma unroll
-    for (int q = 0; q < 8; ++q) xv[q] = rg[kRgOff.v[f0 + q]];
-    *(bf16x8*)&Hs[lane][kk % (2 * RG_BLK * 32) + 8 * wv] = xv;
-  };
-
-  // ---- layer 1: 16 chunks of 32 features in blocks of RG_BLK chunks, one
-  // barrier per block.  Block b is staged in half b % 2 of the first
-  // 2 RG_BLK 32 columns of Hs.  A wave writes a half only after the barrier
-  // of the block in between, which every wave reaches after its products
-  // of the block that last read the half.
-  zero();
-  __syncthreads();                  // the region is complete
-#pragma unroll
-  for (int s0 = 0; s0 < RG_S1; s0 += RG_BLK) {
-#pragma unroll
-    for (int q = 0; q < RG_BLK; ++q) stage_x((s0 + q) * 32);
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < RG_BLK; ++q) {
-      const int s = s0 + q;
-      mma((s * 32) % (2 * RG_BLK * 32), wb[s % RG_D]);
-      if (s + RG_D < RG_S1 + RG_S2) load_b(s + RG_D, wb[s % RG_D]);
-    }
-  }
-  __syncthreads();                  // every wave's last feature reads are done
-  store_h(b1);
-  __syncthreads();
-
-  // ---- layer 2: A = the activations in Hs, no barriers
-  zero();
-#pragma unroll
-  for (int s = RG_S1; s < RG_S1 + RG_S2; ++s) {
-    mma((s - RG_S1) * 32, wb[s % RG_D]);
-    if (s + RG_D < RG_S1 + RG_S2) load_b(s + RG_D, wb[s % RG_D]);
-  }
-  __syncthreads();                  // every wave's reads of the layer-1 activations are done
-  store_h(b2);
-  __syncthreads();
-
-  // ---- layer 3 (outputs padded to 16 columns)
-  {
-    f32x4 c3 = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int ks = 0; ks < MLP_NH; ks += 32) {
-      const bf16x8 a = *(const bf16x8*)&Hs[wv * 16 + (lane & 15)][ks + 8 * (lane >> 4)];
-      const bf16x8 b = *(const bf16x8*)(p.W3b + (long)(lane & 15) * MLP_NH + ks + 8 * (lane >> 4));
-      c3 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c3, 0, 0, 0);
-    }
-    const int o = lane & 15;
-    if (o < MLP_NOUT)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const long c = c0 + wv * 16 + 4 * (lane >> 4) + e;
-        y[c * MLP_NOUT + o] = c3[e] + b3[o];
-      }
-  }
+  GatherStage<T> stage{u, v, w, tt, ss, st, hs, corner, (int)d.sy, (int)d.sz, live, {}, {}};
+  stage.load(0);
+  net_rows<4>(p, hs, hs, stage, [&](int i, f32x4 c) {
+    const int row = c0 + 16 * i + (int)(threadIdx.x & 15);
+    if (row < ncell)
+      *(__attribute__((address_space(1))) f32x4*)(y + (long)row * MLP_NOUT) = c;
+  });
 }
 
 // FP32 rows of 500: the network input of oc_mlp_* (training data).
@@ -890,17 +883,32 @@ hipError_t launch_closure_features(const Dims& d, const T* u, const T* v, const 
   return hipGetLastError();
 }
 
+// 64-row workgroups once they fill the 256 CUs twice (65536 rows: 48 us
+// against 53 with 32 rows); below that 32-row ones, twice as many and half as
+// long (4096 rows: 11 us).
+hipError_t launch_mlp_forward(const MlpParams& p, const float* x, int B, float* y, hipStream_t s) {
+  if (B >= 2 * 256 * 64)
+    hipLaunchKernelGGL(mlp_forward_kernel<4>, dim3((B + 63) / 64), dim3(256), 0, s, p, x, B, y);
+  else
+    hipLaunchKernelGGL(mlp_forward_kernel<2>, dim3((B + 31) / 32), dim3(256), 0, s, p, x, B, y);
+  return hipGetLastError();
+}
+
 template <class T>
 hipError_t launch_closure_mlp_fused(const Dims& d, const T* u, const T* v, const T* w, const T* t,
                                     const T* s, ClosureStats st, const MlpParams& p, float* y,
                                     hipStream_t stream) {
-  const long n = (long)d.nx * d.ny * d.nz;
-  if (d.nx % FZ_BM == 0)
-    hipLaunchKernelGGL(closure_mlp_region_kernel<T>, dim3((unsigned)(n / FZ_BM)), dim3(256), 0,
-                       stream, d, u, v, w, t, s, st, p, y);
+  const int n = d.nx * d.ny * d.nz;   // a multiple of 512 (grid lengths are multiples of 8)
+  const dim3 nt(256);
+  if (d.nx % 64 == 0)
+    hipLaunchKernelGGL((closure_mlp_region_kernel<T, 4, 64>), dim3(n / 64), nt, 0, stream, d, u, v,
+                       w, t, s, st, p, y);
+  else if (d.nx % 32 == 0)
+    hipLaunchKernelGGL((closure_mlp_region_kernel<T, 4, 32>), dim3(n / 64), nt, 0, stream, d, u, v,
+                       w, t, s, st, p, y);
   else
-    hipLaunchKernelGGL(closure_mlp_fused_kernel<T>, dim3((unsigned)((n + FZ_BM - 1) / FZ_BM)),
-                       dim3(256), 0, stream, d, u, v, w, t, s, st, p, y);
+    hipLaunchKernelGGL(closure_mlp_gather_kernel<T>, dim3((n + 63) / 64), nt, 0, stream, d, u, v,
+                       w, t, s, st, p, y);
   return hipGetLastError();
 }
 template hipError_t launch_closure_mlp_fused<float>(const Dims&, const float*, const float*,

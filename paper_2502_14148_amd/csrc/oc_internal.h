@@ -332,6 +332,10 @@ struct MlpParams {
   __bf16* W2b;              // 256 x 256
   __bf16* W2bT;             // its transpose (backward pass)
   __bf16* W3b;              // 32 x 256 (rows >= 4 zero)
+  // the same in MFMA operand order (16-row x 32-k blocks of one kilobyte)
+  __bf16* W1f;              // 16 row blocks x 16 k blocks
+  __bf16* W2f;              // 16 x 8
+  __bf16* W3f;              // 1 x 8 (rows >= 4 zero)
 };
 
 __device__ void mlp_write_bf16(const MlpParams& p, int t, float w);
@@ -340,6 +344,8 @@ hipError_t launch_loss_grad(const float* Y, int ldy, const float* T, int B, floa
                             int ldd, double* partial, int nblocks, hipStream_t s);
 hipError_t launch_colsum(const float* a, int rows, int cols, int lda, float* out, float* part,
                          hipStream_t s);
+// y (B x 4) = network(x), x: B x 500 FP32 (element-aligned), B a multiple of 32
+hipError_t launch_mlp_forward(const MlpParams& p, const float* x, int B, float* y, hipStream_t s);
 hipError_t launch_features_to_bf16(const float* x, int B, __bf16* xb, hipStream_t s);
 hipError_t launch_adam(const MlpParams& p, const float* grad, float* m1, float* m2, int n, float lr,
                        int step, hipStream_t s);
@@ -383,12 +389,10 @@ template <class T>
 hipError_t launch_coarse_grain(const CoarseArgs<T>& a, hipStream_t s);
 
 // Access to a network from the model's step (implemented in closure_api.hip).
-__bf16* mlp_input(oc_mlp* net);
 const float* mlp_output(oc_mlp* net);
 float* mlp_output_rw(oc_mlp* net);
 const MlpParams& mlp_params(const oc_mlp* net);
 int mlp_max_batch(const oc_mlp* net);
-int mlp_run_forward(oc_mlp* net, int batch, hipStream_t s);
 int mlp_params_finite(oc_mlp* net, hipStream_t s);  // 1, 0, or a negative error
 
 // Host-side error reporting (per thread).

@@ -161,3 +161,28 @@ def test_closure_refuses_diverged_network(gpu_lib):
     m.rk3_step(0.5, 2)
     d = m.diagnostics()
     assert np.isfinite(d["max_w"])
+
+
+@pytest.mark.parametrize("B", [64, 32736, 32768, 32800])
+def test_forward_tile_edges(gpu_lib, B):
+    """The last batch of the 32-row tiles, the first of the 64-row ones and
+    one that leaves half a tile; every row, to the bars of
+    test_forward_parity, and rows do not depend on the batch they are in."""
+    p, X, _ = _data(8, B)
+    net = gpu_lib.Mlp(B)
+    net.set_params(p)
+    x = _dev(X)
+    y = net.forward(x)
+    yo, _ = cl.forward(p, X, use_bf16=True)
+    got = y.cpu().numpy().astype(np.float64)
+    assert rel_l2(got, yo) < 2e-3
+    assert np.max(np.abs(got - yo)) < 2e-2 * np.max(np.abs(yo))
+    assert np.array_equal(net.forward(x[-32:]).cpu().numpy(), y[-32:].cpu().numpy())
+
+
+@pytest.mark.parametrize("n,precision", [((96, 8, 8), "fp32"), ((16, 16, 8), "fp32"),
+                                         ((8, 8, 16), "fp64")])
+def test_closure_row_lengths(gpu_lib, n, precision):
+    """x rows of 32k cells (three groups to a row) and the short rows that
+    take the direct gather."""
+    test_closure_tendency_parity(gpu_lib, n, precision)
