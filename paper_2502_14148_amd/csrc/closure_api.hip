@@ -1,6 +1,6 @@
 // C ABI of the MLP subgrid closure (declared in include/oc.h): workspace
 // carving, parameter upload, and the forward / backward / Adam sequences
-// built from the BF16 MFMA GEMM kernel of mlp.hip.
+// built from the kernels of mlp.hip.
 #include <cmath>
 #include <cstring>
 #include <new>
@@ -19,36 +19,22 @@ using namespace oc;
     }                                                             \
   } while (0)
 
-static const int LOSS_BLOCKS = 256;
-
 struct oc_mlp {
   int max_batch;
   MlpParams p;
   float* m1;
   float* m2;
   float* grad;
-  __bf16* xb;       // B x 512
-  float* z1;        // B x 256 pre-activations
-  __bf16* h1;       // B x 256
-  float* z2;
-  __bf16* h2;
-  float* y;         // B x 4
-  float* dy;        // B x 32
-  __bf16* dyb;
-  float* dz2;       // B x 256
-  __bf16* dz2b;
-  float* dz1;
-  __bf16* dz1b;
-  double* partial;  // LOSS_BLOCKS
-  float* part;      // split-K and column-sum partials (MLP_PART_FLOATS)
+  float* y;         // max_batch x 4: outputs inside a model's step
+  MlpTrain t;
   int step;
 };
 
 namespace {
 
 struct MlpLayout {
-  uint64_t master, m1, m2, grad, w1b, w2b, w2bt, w3b, w1f, w2f, w3f, xb, z1, h1, z2, h2, y, dy, dyb, dz2, dz2b, dz1,
-      dz1b, partial, part, total;
+  uint64_t master, m1, m2, grad, w1f, w2f, w2tf, w3f, w3tf, y, xf, h1f, h2f, dyf, dz2f, dz1f, biasp,
+      lossp, loss, part, total;
 };
 
 uint64_t a256(uint64_t x) { return (x + 255) & ~uint64_t(255); }
@@ -57,58 +43,29 @@ MlpLayout mlp_layout(int B) {
   MlpLayout L;
   uint64_t o = 0;
   auto take = [&](uint64_t bytes) { uint64_t r = o; o += a256(bytes); return r; };
+  const uint64_t kb = (uint64_t)B / 32, block = 1024;   // 32-row blocks; bytes of an operand block
   L.master = take((uint64_t)MLP_NPARAM * 4);
   L.m1 = take((uint64_t)MLP_NPARAM * 4);
   L.m2 = take((uint64_t)MLP_NPARAM * 4);
   L.grad = take((uint64_t)MLP_NPARAM * 4);
-  L.w1b = take((uint64_t)MLP_NH * MLP_KIN * 2);
-  L.w2b = take((uint64_t)MLP_NH * MLP_NH * 2);
-  L.w2bt = take((uint64_t)MLP_NH * MLP_NH * 2);
-  L.w3b = take((uint64_t)MLP_NOUTP * MLP_NH * 2);
   L.w1f = take((uint64_t)MLP_NH * MLP_KIN * 2);
   L.w2f = take((uint64_t)MLP_NH * MLP_NH * 2);
+  L.w2tf = take((uint64_t)MLP_NH * MLP_NH * 2);
   L.w3f = take((uint64_t)16 * MLP_NH * 2);
-  L.xb = take((uint64_t)B * MLP_KIN * 2);
-  L.z1 = take((uint64_t)B * MLP_NH * 4);
-  L.h1 = take((uint64_t)B * MLP_NH * 2);
-  L.z2 = take((uint64_t)B * MLP_NH * 4);
-  L.h2 = take((uint64_t)B * MLP_NH * 2);
+  L.w3tf = take((uint64_t)MLP_NH * 32 * 2);
   L.y = take((uint64_t)B * MLP_NOUT * 4);
-  L.dy = take((uint64_t)B * MLP_NOUTP * 4);
-  L.dyb = take((uint64_t)B * MLP_NOUTP * 2);
-  L.dz2 = take((uint64_t)B * MLP_NH * 4);
-  L.dz2b = take((uint64_t)B * MLP_NH * 2);
-  L.dz1 = take((uint64_t)B * MLP_NH * 4);
-  L.dz1b = take((uint64_t)B * MLP_NH * 2);
-  L.partial = take((uint64_t)LOSS_BLOCKS * 8);
-  L.part = take((uint64_t)MLP_PART_FLOATS * 4);
+  L.xf = take(kb * 32 * block);
+  L.h1f = take(kb * 16 * block);
+  L.h2f = take(kb * 16 * block);
+  L.dyf = take(kb * block);
+  L.dz2f = take(kb * 16 * block);
+  L.dz1f = take(kb * 16 * block);
+  L.biasp = take((uint64_t)TR_MAXWG * TR_NB * 4);
+  L.lossp = take((uint64_t)TR_MAXWG * 8);
+  L.loss = take(8);
+  L.part = take((uint64_t)TR_MAXSPLIT * MLP_NPARAM * 4);
   L.total = o;
   return L;
-}
-
-GemmArgs gemm(const __bf16* A, int lda, int ta, const __bf16* B, int ldb, int tb, int M, int N,
-              int K, int epi, float* C, int ldc, const float* bias = nullptr,
-              const float* Z = nullptr, __bf16* Hh = nullptr, int ldh = 0) {
-  GemmArgs g;
-  g.A = A; g.lda = lda; g.transA = ta;
-  g.B = B; g.ldb = ldb; g.transB = tb;
-  g.M = M; g.N = N; g.K = K;
-  g.epi = epi; g.C = C; g.ldc = ldc; g.bias = bias; g.Z = Z; g.H = Hh; g.ldh = ldh;
-  g.ksplit = 1; g.part = nullptr;
-  return g;
-}
-
-// A weight-gradient GEMM (K = batch) split over K until the grid has about
-// 1024 workgroups, each split covering at least two 32-deep k blocks.
-GemmArgs split_k(GemmArgs g, float* part) {
-  const int tiles = ((g.M + 63) / 64) * ((g.N + 63) / 64);
-  int ks = 1;
-  while (tiles * ks < 1024 && ks < MLP_MAX_KSPLIT && g.K % (64 * ks * 2) == 0 &&
-         (long)2 * ks * g.M * g.N <= MLP_PART_FLOATS)
-    ks *= 2;
-  g.ksplit = ks;
-  g.part = part;
-  return g;
 }
 
 int check_batch(const oc_mlp* m, int B) {
@@ -120,58 +77,12 @@ int check_batch(const oc_mlp* m, int B) {
   return OC_OK;
 }
 
-// forward pass on the BF16 features already in m->xb
-int forward_from_xb(oc_mlp* m, int B, hipStream_t s) {
-  const float* mp = m->p.master;
-  OC_CHECK_HIP(launch_gemm_bf16(gemm(m->xb, MLP_KIN, 0, m->p.W1b, MLP_KIN, 1, B, MLP_NH, MLP_KIN,
-                                     EPI_BIAS_GELU, m->z1, MLP_NH, mp + MLP_OFF_B1, nullptr, m->h1,
-                                     MLP_NH), s));
-  OC_CHECK_HIP(launch_gemm_bf16(gemm(m->h1, MLP_NH, 0, m->p.W2b, MLP_NH, 1, B, MLP_NH, MLP_NH,
-                                     EPI_BIAS_GELU, m->z2, MLP_NH, mp + MLP_OFF_B2, nullptr, m->h2,
-                                     MLP_NH), s));
-  OC_CHECK_HIP(launch_gemm_bf16(gemm(m->h2, MLP_NH, 0, m->p.W3b, MLP_NH, 1, B, MLP_NOUT, MLP_NH,
-                                     EPI_BIAS, m->y, MLP_NOUT, mp + MLP_OFF_B3), s));
-  return OC_OK;
-}
-
-// gradients of the mean squared error into m->grad (packed like the
-// parameters); the per-block squared-error partials into m->partial
-int backward(oc_mlp* m, const float* target, int B, hipStream_t s) {
-  float* g = m->grad;
-  OC_CHECK_HIP(launch_loss_grad(m->y, MLP_NOUT, target, B, m->dy, m->dyb, MLP_NOUTP, m->partial,
-                                LOSS_BLOCKS, s));
-  // layer 3: dW3 = dY^T H2, db3 = colsum dY, dZ2 = (dY W3) * gelu'(Z2)
-  OC_CHECK_HIP(launch_gemm_bf16(split_k(gemm(m->dyb, MLP_NOUTP, 1, m->h2, MLP_NH, 0, MLP_NOUT,
-                                             MLP_NH, B, EPI_STORE, g + MLP_OFF_W3, MLP_NH),
-                                        m->part), s));
-  OC_CHECK_HIP(launch_colsum(m->dy, B, MLP_NOUT, MLP_NOUTP, g + MLP_OFF_B3, m->part, s));
-  OC_CHECK_HIP(launch_gemm_bf16(gemm(m->dyb, MLP_NOUTP, 0, m->p.W3b, MLP_NH, 0, B, MLP_NH,
-                                     MLP_NOUTP, EPI_GELU_BWD, m->dz2, MLP_NH, nullptr, m->z2,
-                                     m->dz2b, MLP_NH), s));
-  // layer 2
-  OC_CHECK_HIP(launch_gemm_bf16(split_k(gemm(m->dz2b, MLP_NH, 1, m->h1, MLP_NH, 0, MLP_NH,
-                                             MLP_NH, B, EPI_STORE, g + MLP_OFF_W2, MLP_NH),
-                                        m->part), s));
-  OC_CHECK_HIP(launch_colsum(m->dz2, B, MLP_NH, MLP_NH, g + MLP_OFF_B2, m->part, s));
-  OC_CHECK_HIP(launch_gemm_bf16(gemm(m->dz2b, MLP_NH, 0, m->p.W2bT, MLP_NH, 1, B, MLP_NH, MLP_NH,
-                                     EPI_GELU_BWD, m->dz1, MLP_NH, nullptr, m->z1, m->dz1b,
-                                     MLP_NH), s));
-  // layer 1
-  OC_CHECK_HIP(launch_gemm_bf16(split_k(gemm(m->dz1b, MLP_NH, 1, m->xb, MLP_KIN, 0, MLP_NH,
-                                             MLP_NIN, B, EPI_STORE, g + MLP_OFF_W1, MLP_NIN),
-                                        m->part), s));
-  OC_CHECK_HIP(launch_colsum(m->dz1, B, MLP_NH, MLP_NH, g + MLP_OFF_B1, m->part, s));
-  return OC_OK;
-}
-
 int read_loss(oc_mlp* m, int B, double* loss, hipStream_t s) {
   if (!loss) return OC_OK;
-  double part[LOSS_BLOCKS];
-  OC_CHECK_HIP(hipMemcpyAsync(part, m->partial, sizeof(part), hipMemcpyDeviceToHost, s));
+  double sum = 0.0;
+  OC_CHECK_HIP(hipMemcpyAsync(&sum, m->t.loss, sizeof(sum), hipMemcpyDeviceToHost, s));
   OC_CHECK_HIP(hipStreamSynchronize(s));
-  double acc = 0.0;
-  for (int b = 0; b < LOSS_BLOCKS; ++b) acc += part[b];
-  *loss = acc / ((double)B * MLP_NOUT);
+  *loss = sum / ((double)B * MLP_NOUT);
   return OC_OK;
 }
 
@@ -229,30 +140,25 @@ int oc_mlp_create(int32_t max_batch, void* workspace, uint64_t bytes, oc_mlp** o
   char* w = (char*)workspace;
   m->max_batch = max_batch;
   m->p.master = (float*)(w + L.master);
-  m->p.W1b = (__bf16*)(w + L.w1b);
-  m->p.W2b = (__bf16*)(w + L.w2b);
-  m->p.W2bT = (__bf16*)(w + L.w2bt);
-  m->p.W3b = (__bf16*)(w + L.w3b);
-  m->p.W1f = (__bf16*)(w + L.w1f);
-  m->p.W2f = (__bf16*)(w + L.w2f);
-  m->p.W3f = (__bf16*)(w + L.w3f);
   m->m1 = (float*)(w + L.m1);
   m->m2 = (float*)(w + L.m2);
   m->grad = (float*)(w + L.grad);
-  m->xb = (__bf16*)(w + L.xb);
-  m->z1 = (float*)(w + L.z1);
-  m->h1 = (__bf16*)(w + L.h1);
-  m->z2 = (float*)(w + L.z2);
-  m->h2 = (__bf16*)(w + L.h2);
+  m->p.W1f = (__bf16*)(w + L.w1f);
+  m->p.W2f = (__bf16*)(w + L.w2f);
+  m->p.W2Tf = (__bf16*)(w + L.w2tf);
+  m->p.W3f = (__bf16*)(w + L.w3f);
+  m->p.W3Tf = (__bf16*)(w + L.w3tf);
   m->y = (float*)(w + L.y);
-  m->dy = (float*)(w + L.dy);
-  m->dyb = (__bf16*)(w + L.dyb);
-  m->dz2 = (float*)(w + L.dz2);
-  m->dz2b = (__bf16*)(w + L.dz2b);
-  m->dz1 = (float*)(w + L.dz1);
-  m->dz1b = (__bf16*)(w + L.dz1b);
-  m->partial = (double*)(w + L.partial);
-  m->part = (float*)(w + L.part);
+  m->t.xf = (__bf16*)(w + L.xf);
+  m->t.h1f = (__bf16*)(w + L.h1f);
+  m->t.h2f = (__bf16*)(w + L.h2f);
+  m->t.dyf = (__bf16*)(w + L.dyf);
+  m->t.dz2f = (__bf16*)(w + L.dz2f);
+  m->t.dz1f = (__bf16*)(w + L.dz1f);
+  m->t.biasp = (float*)(w + L.biasp);
+  m->t.lossp = (double*)(w + L.lossp);
+  m->t.loss = (double*)(w + L.loss);
+  m->t.part = (float*)(w + L.part);
   m->step = 0;
   // zero everything: padded weight rows/columns stay zero for good
   if (hipMemset(workspace, 0, L.total) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
@@ -306,12 +212,7 @@ int oc_mlp_gradients(oc_mlp* m, const float* x, const float* target, int32_t bat
   if (rc) return rc;
   if (!x || !target || !grad) { set_error("NULL argument"); return OC_ERR_ARG; }
   hipStream_t s = (hipStream_t)stream;
-  OC_CHECK_HIP(launch_features_to_bf16(x, batch, m->xb, s));
-  rc = forward_from_xb(m, batch, s);
-  if (rc) return rc;
-  rc = backward(m, target, batch, s);
-  if (rc) return rc;
-  OC_CHECK_HIP(hipMemcpyAsync(grad, m->grad, (size_t)MLP_NPARAM * 4, hipMemcpyDeviceToDevice, s));
+  OC_CHECK_HIP(launch_mlp_gradients(m->p, m->t, x, target, batch, grad, nullptr, nullptr, 0.f, 0, s));
   return read_loss(m, batch, loss, s);
 }
 
@@ -321,13 +222,9 @@ int oc_mlp_train_step(oc_mlp* m, const float* x, const float* target, int32_t ba
   if (rc) return rc;
   if (!x || !target || !(lr > 0)) { set_error("need inputs, targets and lr > 0"); return OC_ERR_ARG; }
   hipStream_t s = (hipStream_t)stream;
-  OC_CHECK_HIP(launch_features_to_bf16(x, batch, m->xb, s));
-  rc = forward_from_xb(m, batch, s);
-  if (rc) return rc;
-  rc = backward(m, target, batch, s);
-  if (rc) return rc;
   m->step += 1;
-  OC_CHECK_HIP(launch_adam(m->p, m->grad, m->m1, m->m2, MLP_NPARAM, lr, m->step, s));
+  OC_CHECK_HIP(launch_mlp_gradients(m->p, m->t, x, target, batch, m->grad, m->m1, m->m2, lr, m->step,
+                                    s));
   return read_loss(m, batch, loss, s);
 }
 

@@ -1,12 +1,17 @@
-// MLP subgrid closure on gfx950: BF16 MFMA GEMMs with FP32 accumulation
-// for the forward and backward passes, fused bias/GELU epilogues, loss and
-// bias-gradient reductions, Adam on FP32 master weights, and the gather of
-// the standardised 5x5x5 (u, v, w, b) neighbourhood of every coarse cell.
+// MLP subgrid closure on gfx950: BF16 MFMA products with FP32 accumulation.
+// Inference and the in-model closure run the whole network in one kernel
+// (the in-model one gathers the standardised 5x5x5 (u, v, w, b)
+// neighbourhood of every cell itself); training takes three launches, with
+// Adam on FP32 master weights in the last.
 //
 // Network: 500 -> 256 -> 256 -> 4 with exact-erf GELU.  On the device the
-// input width is padded to 512 and the output width to 32 with zero weights
-// so every GEMM dimension is a multiple of the 32-deep MFMA k step.
+// input width is padded to 512 with zero weights, a multiple of the 32-deep
+// MFMA k step, and the output width to 16 rows (32 as a reduction).
 #include "oc_internal.h"
+
+#include <algorithm>
+#include <cmath>
+#include <type_traits>
 
 namespace oc {
 
@@ -14,7 +19,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// Fragment-major weight copies: the 16 output rows x 32 inputs that one MFMA
+// The weight copies: the 16 output rows x 32 inputs that one MFMA
 // takes as an operand are one contiguous kilobyte in lane order (lane l
 // holds 8 consecutive k of row l % 16, k block l / 16), the k blocks of a
 // row block following each other.  A wave's operand load is then one
@@ -27,24 +32,20 @@ __device__ void mlp_write_bf16(const MlpParams& p, int t, float w) {
   // master layout: W1 (256 x 500) | b1 | W2 (256 x 256) | b2 | W3 (4 x 256) | b3
   if (t < MLP_OFF_B1) {
     const int r = t / 500, c = t % 500;
-    p.W1b[r * 512 + c] = (__bf16)w;
     p.W1f[frag_at(r, c, MLP_KIN / 32)] = (__bf16)w;
   } else if (t >= MLP_OFF_W2 && t < MLP_OFF_B2) {
     const int r = (t - MLP_OFF_W2) / MLP_NH, c = (t - MLP_OFF_W2) % MLP_NH;
-    p.W2b[r * MLP_NH + c] = (__bf16)w;
-    p.W2bT[c * MLP_NH + r] = (__bf16)w;   // transposed copy for the backward pass
     p.W2f[frag_at(r, c, MLP_NH / 32)] = (__bf16)w;
+    p.W2Tf[frag_at(c, r, MLP_NH / 32)] = (__bf16)w;   // transposed, for the backward pass
   } else if (t >= MLP_OFF_W3 && t < MLP_OFF_B3) {
     const int r = (t - MLP_OFF_W3) / MLP_NH, c = (t - MLP_OFF_W3) % MLP_NH;
-    p.W3b[t - MLP_OFF_W3] = (__bf16)w;
     p.W3f[frag_at(r, c, MLP_NH / 32)] = (__bf16)w;
+    p.W3Tf[frag_at(c, r, 1)] = (__bf16)w;
   }
 }
 
 
 namespace {
-
-constexpr int BM = 64, BN = 64, BK = 32, LDP = BK + 8;  // LDS rows padded by 8 bf16
 
 // erf(z / sqrt 2) and exp(-z^2 / 2) by Abramowitz & Stegun, formula 7.1.26
 // (absolute error of erf at most 1.5e-7, far below the BF16 rounding the
@@ -92,339 +93,12 @@ __device__ inline float gelu_prime(float z) {
   return fmaf(0.5f, r.erf, 0.5f) + z * r.g * 0.39894228040143268f;
 }
 
-// Epilogue of one output element (m, n) of a GEMM.
-__device__ inline void epilogue(const GemmArgs& g, int m, int n, float v) {
-  const long o = (long)m * g.ldc + n;
-  switch (g.epi) {
-    case EPI_STORE:
-      g.C[o] = v;
-      break;
-    case EPI_BIAS:
-      g.C[o] = v + g.bias[n];
-      break;
-    case EPI_BIAS_GELU: {
-      const float z = v + g.bias[n];
-      g.C[o] = z;                                   // pre-activation (for backward)
-      g.H[(long)m * g.ldh + n] = (__bf16)gelu(z);    // activation (next layer)
-      break;
-    }
-    case EPI_GELU_BWD: {
-      const float dz = v * gelu_prime(g.Z[o]);
-      g.C[o] = dz;
-      g.H[(long)m * g.ldh + n] = (__bf16)dz;
-      break;
-    }
-  }
-}
-
-// C[m][n] = sum_k A[m][k] B[k][n].  transA = 0: A[m][k] at A[m*lda + k];
-// 1: at A[k*lda + m].  transB = 0: B[k][n] at B[k*ldb + n]; 1: at B[n*ldb + k].
-// Tiles are staged in LDS with k contiguous, the order the MFMA operands
-// need: lane l holds 8 consecutive k of row (or column) l % 16, k block l / 16.
-__global__ void __launch_bounds__(256) gemm_bf16_kernel(GemmArgs g) {
-  __shared__ __bf16 As[BM][LDP];
-  __shared__ __bf16 Bs[BN][LDP];
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wv = tid >> 6;
-  const int wm = wv >> 1, wn = wv & 1;
-  const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
-  // split K: this workgroup's range of the reduction
-  const int kspan = g.K / g.ksplit;
-  const int kbeg = blockIdx.z * kspan, kend = kbeg + kspan;
-  f32x4 acc[2][2];
-  for (int i = 0; i < 2; ++i)
-    for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  for (int k0 = kbeg; k0 < kend; k0 += BK) {
-    // ---- stage A (BM x BK) and B (BN x BK)
-    if (!g.transA) {
-      const int r = tid >> 2, ks = (tid & 3) * 8;
-      const int m = m0 + r;
-      bf16x8 v;
-      if (m < g.M) v = *(const bf16x8*)(g.A + (long)m * g.lda + k0 + ks);
-      else for (int e = 0; e < 8; ++e) v[e] = (__bf16)0.0f;
-      *(bf16x8*)&As[r][ks] = v;
-    } else {
-      const int kk = tid >> 3, ms = (tid & 7) * 8;
-      const __bf16* src = g.A + (long)(k0 + kk) * g.lda + m0 + ms;
-      for (int e = 0; e < 8; ++e) As[ms + e][kk] = (m0 + ms + e < g.M) ? src[e] : (__bf16)0.0f;
-    }
-    if (g.transB) {
-      const int r = tid >> 2, ks = (tid & 3) * 8;
-      const int n = n0 + r;
-      bf16x8 v;
-      if (n < g.N) v = *(const bf16x8*)(g.B + (long)n * g.ldb + k0 + ks);
-      else for (int e = 0; e < 8; ++e) v[e] = (__bf16)0.0f;
-      *(bf16x8*)&Bs[r][ks] = v;
-    } else {
-      const int kk = tid >> 3, ns = (tid & 7) * 8;
-      const __bf16* src = g.B + (long)(k0 + kk) * g.ldb + n0 + ns;
-      for (int e = 0; e < 8; ++e) Bs[ns + e][kk] = (n0 + ns + e < g.N) ? src[e] : (__bf16)0.0f;
-    }
-    __syncthreads();
-    // ---- 2 x 2 MFMA tiles of 16 x 16 per wave
-    bf16x8 a[2], b[2];
-    for (int i = 0; i < 2; ++i)
-      a[i] = *(const bf16x8*)&As[wm * 32 + i * 16 + (lane & 15)][8 * (lane >> 4)];
-    for (int j = 0; j < 2; ++j)
-      b[j] = *(const bf16x8*)&Bs[wn * 32 + j * 16 + (lane & 15)][8 * (lane >> 4)];
-    for (int i = 0; i < 2; ++i)
-      for (int j = 0; j < 2; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
-    __syncthreads();
-  }
-
-  // ---- epilogue: lane holds rows 4*(lane/16) + e of column lane % 16
-  for (int i = 0; i < 2; ++i)
-    for (int j = 0; j < 2; ++j) {
-      const int n = n0 + wn * 32 + j * 16 + (lane & 15);
-      if (n >= g.N) continue;
-      for (int e = 0; e < 4; ++e) {
-        const int m = m0 + wm * 32 + i * 16 + 4 * (lane >> 4) + e;
-        if (m >= g.M) continue;
-        const float v = acc[i][j][e];
-        if (g.ksplit > 1) {
-          g.part[((long)blockIdx.z * g.M + m) * g.N + n] = v;
-          continue;
-        }
-        epilogue(g, m, n, v);
-      }
-    }
-}
-
-// dY = 2 (Y - T) / (B * 4) on the 4 real outputs (FP32 and BF16, padded
-// columns zero); per-block partial sums of the squared error.
-// C = A B with both operands k-contiguous (A[m][k] at A[m*lda + k], B[k][n]
-// at B[n*ldb + k]), M any multiple of 32, N a multiple of 128, K a multiple
-// of 64.  Workgroup tile 128 x 128, k step 64, four waves of 64 x 64 (4 x 4
-// MFMA 16x16x32 tiles); 16-byte global loads into registers for the next
-// k step while the current one is multiplied out of double-buffered LDS.
-constexpr int NT_BM = 128, NT_BN = 128, NT_BK = 64, NT_LDP = NT_BK + 8;
-
-__global__ void __launch_bounds__(256) gemm_bf16_nt_kernel(GemmArgs g) {
-  __shared__ __bf16 As[2][NT_BM][NT_LDP];
-  __shared__ __bf16 Bs[2][NT_BN][NT_LDP];
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wv = tid >> 6;
-  const int wm = wv >> 1, wn = wv & 1;
-  const int m0 = blockIdx.y * NT_BM, n0 = blockIdx.x * NT_BN;
-  // each thread moves 4 chunks of 8 bf16 per operand and k step: rows
-  // (tid >> 3) + 32 c, k offset 8 (tid & 7)
-  const int lr = tid >> 3, lk = (tid & 7) * 8;
-  bf16x8 ra[4], rb[4];
-  auto load = [&](int k0) {
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int m = m0 + lr + 32 * c;
-      if (m < g.M) ra[c] = *(const bf16x8*)(g.A + (long)m * g.lda + k0 + lk);
-      else for (int e = 0; e < 8; ++e) ra[c][e] = (__bf16)0.0f;
-      const int n = n0 + lr + 32 * c;
-      rb[c] = *(const bf16x8*)(g.B + (long)n * g.ldb + k0 + lk);
-    }
-  };
-  auto stash = [&](int buf) {
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      *(bf16x8*)&As[buf][lr + 32 * c][lk] = ra[c];
-      *(bf16x8*)&Bs[buf][lr + 32 * c][lk] = rb[c];
-    }
-  };
-  f32x4 acc[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const int nk = g.K / NT_BK;
-  load(0);
-  stash(0);
-  __syncthreads();
-  for (int kt = 0; kt < nk; ++kt) {
-    const int buf = kt & 1;
-    if (kt + 1 < nk) load((kt + 1) * NT_BK);
-#pragma unroll
-    for (int ks = 0; ks < NT_BK; ks += 32) {
-      bf16x8 a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        a[i] = *(const bf16x8*)&As[buf][wm * 64 + i * 16 + (lane & 15)][ks + 8 * (lane >> 4)];
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        b[j] = *(const bf16x8*)&Bs[buf][wn * 64 + j * 16 + (lane & 15)][ks + 8 * (lane >> 4)];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
-    }
-    if (kt + 1 < nk) stash(buf ^ 1);
-    __syncthreads();
-  }
-  // lane holds rows 4 (lane / 16) + e of column lane % 16 of each 16 x 16 tile
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int n = n0 + wn * 64 + j * 16 + (lane & 15);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int m = m0 + wm * 64 + i * 16 + 4 * (lane >> 4) + e;
-        if (m < g.M) epilogue(g, m, n, acc[i][j][e]);
-      }
-    }
-}
-
-__global__ void __launch_bounds__(256) loss_grad_kernel(const float* Y, int ldy, const float* T,
-                                                        int B, float* dY, __bf16* dYb, int ldd,
-                                                        double* partial) {
-  __shared__ double red[256];
-  double acc = 0.0;
-  const float scale = 2.0f / (float)(B * 4);
-  for (long t = (long)blockIdx.x * blockDim.x + threadIdx.x; t < (long)B * ldd;
-       t += (long)gridDim.x * blockDim.x) {
-    const int r = (int)(t / ldd), c = (int)(t % ldd);
-    float d = 0.f;
-    if (c < 4) {
-      const float e = Y[(long)r * ldy + c] - T[(long)r * 4 + c];
-      acc += (double)e * e;
-      d = scale * e;
-    }
-    dY[t] = d;
-    dYb[t] = (__bf16)d;
-  }
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
-}
-
-// column sums of a (rows x cols) FP32 matrix into out (bias gradients)
-// Sum of the split-K partials in z order: C[m][n] = sum_z part[z][m][n].
-__global__ void splitk_reduce_kernel(const float* part, int ksplit, int M, int N, float* C,
-                                     int ldc) {
-  const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= (long)M * N) return;
-  const long mn = (long)M * N;
-  float s = 0.f;
-  for (int z = 0; z < ksplit; ++z) s += part[z * mn + t];
-  C[(t / N) * ldc + t % N] = s;
-}
-
-// Column sums in two levels: chunk q of the rows gives part[q][c] (a block
-// of 64 columns x 4 row lanes, combined in LDS), then the chunks are added
-// in order.
-__global__ void __launch_bounds__(256) colsum_partial_kernel(const float* a, int rows, int cols,
-                                                             int lda, int chunk, float* part) {
-  __shared__ float red[4][64];
-  const int cl = threadIdx.x & 63, rl = threadIdx.x >> 6;
-  const int c = blockIdx.x * 64 + cl;
-  const int r0 = blockIdx.y * chunk, r1 = min(r0 + chunk, rows);
-  float s = 0.f;
-  if (c < cols)
-    for (int r = r0 + rl; r < r1; r += 4) s += a[(long)r * lda + c];
-  red[rl][cl] = s;
-  __syncthreads();
-  if (rl == 0 && c < cols)
-    part[(long)blockIdx.y * cols + c] = ((red[0][cl] + red[1][cl]) + red[2][cl]) + red[3][cl];
-}
-
-__global__ void colsum_final_kernel(const float* part, int nchunk, int cols, float* out) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= cols) return;
-  float s = 0.f;
-  for (int q = 0; q < nchunk; ++q) s += part[(long)q * cols + c];
-  out[c] = s;
-}
-
-// FP32 features (B x 500) -> BF16 (B x 512), zero padding
-__global__ void features_to_bf16_kernel(const float* x, int B, __bf16* xb) {
-  const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= (long)B * 512) return;
-  const int r = (int)(t / 512), c = (int)(t % 512);
-  xb[t] = (c < 500) ? (__bf16)x[(long)r * 500 + c] : (__bf16)0.0f;
-}
-
-// Adam (Kingma & Ba) on the FP32 master parameters; refreshes the padded
-// BF16 copies used by the GEMMs.
-__global__ void adam_kernel(MlpParams p, const float* grad, float* m1, float* m2, int n,
-                            float lr, float b1, float b2, float eps, float c1, float c2) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n) return;
-  const float g = grad[t];
-  const float mm = b1 * m1[t] + (1.f - b1) * g;
-  const float vv = b2 * m2[t] + (1.f - b2) * g * g;
-  m1[t] = mm;
-  m2[t] = vv;
-  const float w = p.master[t] - lr * (mm / c1) / (sqrtf(vv / c2) + eps);
-  p.master[t] = w;
-  mlp_write_bf16(p, t, w);
-}
-
 __global__ void refresh_bf16_kernel(MlpParams p, int n) {
   const int t = blockIdx.x * blockDim.x + threadIdx.x;
   if (t < n) mlp_write_bf16(p, t, p.master[t]);
 }
 
 }  // namespace
-
-hipError_t launch_gemm_bf16(const GemmArgs& g, hipStream_t s) {
-  const int ks = g.ksplit > 1 ? g.ksplit : 1;
-  if (ks > 1 && (g.epi != EPI_STORE || g.K % (ks * BK) || !g.part ||
-                 (long)ks * g.M * g.N > MLP_PART_FLOATS))
-    return hipErrorInvalidValue;
-  GemmArgs a = g;
-  a.ksplit = ks;
-  if (ks == 1 && !g.transA && g.transB && g.N % NT_BN == 0 && g.K % NT_BK == 0) {
-    dim3 grid(g.N / NT_BN, (g.M + NT_BM - 1) / NT_BM);
-    hipLaunchKernelGGL(gemm_bf16_nt_kernel, grid, dim3(256), 0, s, a);
-    return hipGetLastError();
-  }
-  dim3 grid((g.N + BN - 1) / BN, (g.M + BM - 1) / BM, ks);
-  hipLaunchKernelGGL(gemm_bf16_kernel, grid, dim3(256), 0, s, a);
-  if (ks > 1) {
-    const long n = (long)g.M * g.N;
-    hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
-                       g.part, ks, g.M, g.N, g.C, g.ldc);
-  }
-  return hipGetLastError();
-}
-
-hipError_t launch_loss_grad(const float* Y, int ldy, const float* T, int B, float* dY, __bf16* dYb,
-                            int ldd, double* partial, int nblocks, hipStream_t s) {
-  hipLaunchKernelGGL(loss_grad_kernel, dim3(nblocks), dim3(256), 0, s, Y, ldy, T, B, dY, dYb, ldd,
-                     partial);
-  return hipGetLastError();
-}
-
-hipError_t launch_colsum(const float* a, int rows, int cols, int lda, float* out, float* part,
-                         hipStream_t s) {
-  int chunk = 128;
-  while ((rows + chunk - 1) / chunk > COLSUM_MAX_CHUNKS) chunk *= 2;
-  const int nchunk = (rows + chunk - 1) / chunk;
-  hipLaunchKernelGGL(colsum_partial_kernel, dim3((cols + 63) / 64, nchunk), dim3(256), 0, s, a,
-                     rows, cols, lda, chunk, part);
-  hipLaunchKernelGGL(colsum_final_kernel, dim3((cols + 127) / 128), dim3(128), 0, s, part, nchunk,
-                     cols, out);
-  return hipGetLastError();
-}
-
-hipError_t launch_features_to_bf16(const float* x, int B, __bf16* xb, hipStream_t s) {
-  const long n = (long)B * 512;
-  hipLaunchKernelGGL(features_to_bf16_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
-                     x, B, xb);
-  return hipGetLastError();
-}
-
-hipError_t launch_adam(const MlpParams& p, const float* grad, float* m1, float* m2, int n, float lr,
-                       int step, hipStream_t s) {
-  const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
-  const float c1 = 1.f - powf(b1, (float)step), c2 = 1.f - powf(b2, (float)step);
-  hipLaunchKernelGGL(adam_kernel, dim3((n + 255) / 256), dim3(256), 0, s, p, grad, m1, m2, n, lr,
-                     b1, b2, eps, c1, c2);
-  return hipGetLastError();
-}
 
 hipError_t launch_refresh_bf16(const MlpParams& p, int n, hipStream_t s) {
   hipLaunchKernelGGL(refresh_bf16_kernel, dim3((n + 255) / 256), dim3(256), 0, s, p, n);
@@ -436,7 +110,6 @@ hipError_t launch_refresh_bf16(const MlpParams& p, int n, hipStream_t s) {
 // conservative flux divergence of the predicted vertical fluxes.
 // ---------------------------------------------------------------------------
 
-// xb[cell][f], f = var * 125 + (dk+2)*25 + (dj+2)*5 + (di+2), var = u, v, w, b
 // Standardised input f (0..499) of the cell `cell`: variable f / 125 of
 // (u, v, w, b) at offset (dk, dj, di) = digits of f % 125 in base 5, minus 2.
 template <class T>
@@ -455,20 +128,6 @@ __device__ inline float feature_value(const Dims& d, const T* u, const T* v, con
   else if (var == 2) x = (float)w[p];
   else x = st.g_alpha * ((float)tt[p] - st.t_ref) - st.g_beta * ((float)ss[p] - st.s_ref);
   return (x - st.in_mean[var]) / st.in_std[var];
-}
-
-// BF16 rows of 512 (the GEMM's padded K) for the model's own closure.
-template <class T>
-__global__ void __launch_bounds__(256) closure_features_kernel(Dims d, const T* u, const T* v,
-                                                               const T* w, const T* tt,
-                                                               const T* ss, ClosureStats st,
-                                                               __bf16* xb) {
-  const long ncell = (long)d.nx * d.ny * d.nz;
-  const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= ncell * 512) return;
-  const long cell = t >> 9;
-  const int f = (int)(t & 511);
-  xb[t] = (f < 500) ? (__bf16)feature_value(d, u, v, w, tt, ss, st, cell, f) : (__bf16)0.0f;
 }
 
 // ---------------------------------------------------------------------------
@@ -500,15 +159,16 @@ __global__ void __launch_bounds__(256) closure_features_kernel(Dims d, const T* 
 constexpr int NET_HP = MLP_NH + 8, NET_SP = 2 * 64 + 8, NET_D = 2;
 constexpr int NET_S1 = MLP_KIN / 32, NET_S2 = MLP_NH / 32;   // k chunks per layer
 
+// operand block `block` (uniform) of f: 16 bytes per lane
 __device__ inline bf16x8 ldfrag(const __bf16* f, int block) {
-  return *(const __attribute__((address_space(1))) bf16x8*)(f + (long)block * 512 +
-                                                            (threadIdx.x & 63) * 8);
+  const __bf16* b = f + (long)block * 512;
+  return ((const __attribute__((address_space(1))) bf16x8*)b)[threadIdx.x & 63];
 }
 
 template <int MI, class Stage, class Out>
-__device__ inline void net_rows(const MlpParams& p, __bf16* hs, const __bf16* sx, Stage& stage,
-                                const Out& out) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+__device__ inline void net_rows(const MlpParams& p, int wv, __bf16* hs, const __bf16* sx,
+                                Stage& stage, const Out& out) {
+  const int lane = threadIdx.x & 63;
   const int lr = lane & 15, lg = lane >> 4;
   auto load_b = [&](int s, bf16x8* b) {
 #pragma unroll
@@ -643,11 +303,405 @@ __global__ void __launch_bounds__(256, 2) mlp_forward_kernel(MlpParams p, const 
   st.row0 = (int)blockIdx.x * MI * 16;
   st.last = B - 1;
   st.load(0);
-  net_rows<MI>(p, hs, hs, st, [&](int i, f32x4 c) {
+  net_rows<MI>(p, threadIdx.x >> 6, hs, hs, st, [&](int i, f32x4 c) {
     const int row = st.row0 + 16 * i + (int)(threadIdx.x & 15);
     if (row < B)
       *(__attribute__((address_space(1))) v4u<float>*)(y + (long)row * MLP_NOUT) = c;
   });
+}
+
+// ---------------------------------------------------------------------------
+// Training: gradients of the mean squared error in three launches.
+//
+//   1. mlp_fwdbwd_kernel: everything that is local to a row.  A workgroup
+//      takes 32 rows from the FP32 features through the three layers, the
+//      loss and back to both layers' errors, with the pre-activations in
+//      registers; it leaves the BF16 operands of the weight gradients and
+//      the FP32 bias gradients and squared error of its rows.
+//   2. mlp_wgrad_kernel: dW = dZ^T H over the batch for the three layers in
+//      one launch, 64 x 64 tiles, the batch split over workgroups and waves.
+//   3. mlp_grad_final_kernel: the splits added in order; for a training step
+//      Adam as well.
+//
+// The operands go between 1 and 2 in MFMA order: one kilobyte holds 32 rows
+// (the k of the weight gradients) x 16 columns, lane l with column l % 16 and
+// rows 4 g + 0..3, 16 + 4 g + 0..3, g = l / 16: the rows whose results a lane
+// of two 16-row products already has, so they are packed in registers and
+// neither side transposes.  (The sum over k takes the rows in any order, the
+// same for both operands.)
+//
+// 4096 rows take 64 us with the loss read back (25 + 10 + 5 us of kernels).
+// They took 21 launches and 279 us when the pre-activations and errors went
+// through memory and the weight gradients transposed both operands two
+// bytes at a time.
+// ---------------------------------------------------------------------------
+constexpr int TR_XP = MLP_KIN + 8;           // LDS pitch of the BF16 features
+constexpr int TR_DP = 40;                    // and of the BF16 output errors
+
+__device__ inline void stfrag(__bf16* f, int block, bf16x8 v) {
+  __bf16* b = f + (long)block * 512;
+  ((__attribute__((address_space(1))) bf16x8*)b)[threadIdx.x & 63] = v;
+}
+// the 8 rows of a lane in a 32-row block
+__device__ inline bf16x8 pack_rows(f32x4 lo, f32x4 hi) {
+  bf16x8 v;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    v[e] = (__bf16)lo[e];
+    v[4 + e] = (__bf16)hi[e];
+  }
+  return v;
+}
+// sum over the 32 rows of a block, in every lane of the column
+__device__ inline float sum_rows(f32x4 lo, f32x4 hi) {
+  float s = ((lo[0] + lo[1]) + (lo[2] + lo[3])) + ((hi[0] + hi[1]) + (hi[2] + hi[3]));
+  s += __shfl_xor(s, 16);
+  return s + __shfl_xor(s, 32);
+}
+
+// Wave wv computes outputs [64 wv, 64 wv + 64) of every layer (rows as the
+// first MFMA operand: lane l holds rows 4 (l / 16) + e of column l % 16).
+// Blocks of 32 rows are dealt to at most TR_MAXWG workgroups, which keep the
+// bias sums of theirs; LOOP: more blocks than workgroups (a kernel of its
+// own, because the loop costs registers: 251 against 134).  Bound by latency
+// at the usual batch sizes: 33 k chunks in a row, each waiting for 16 KB of
+// weights from L2, two chunks in flight (four or eight: the same time, half
+// the waves); 25 us at 4096 rows.
+template <bool LOOP>
+__global__ void __launch_bounds__(256, 2) mlp_fwdbwd_kernel(MlpParams p, MlpTrain t, const float* x,
+                                                            const float* target, int B) {
+  __shared__ __attribute__((aligned(16))) __bf16 xs[32 * TR_XP];   // features, then h2
+  __shared__ __attribute__((aligned(16))) __bf16 hs[32 * NET_HP];  // h1, then dz2
+  __shared__ __attribute__((aligned(16))) __bf16 ds[32 * TR_DP];   // dy (columns 4.. zero)
+  // (the wave number made scalar: operand loads take a scalar base)
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lr = lane & 15, lg = lane >> 4;
+  for (int e = threadIdx.x; e < 32 * TR_DP; e += 256) ds[e] = (__bf16)0.f;
+  const float scale = 2.0f / (float)(B * 4);
+  float db1[4] = {0.f, 0.f, 0.f, 0.f}, db2[4] = {0.f, 0.f, 0.f, 0.f}, db3 = 0.f;
+  double loss = 0.0;
+  int opaque = 0;
+
+  f32x4 acc[2][4], z1[2][4], z2[2][4];
+  // acc = rows (LDS, 32 x 32 S) * weights (operand blocks wv 4 + j, S k blocks)
+  auto product = [&](const __bf16* rows, int pitch, const __bf16* wf, auto nk) {
+    constexpr int S = decltype(nk)::value, D = S < 2 ? S : 2;
+    static_assert(S % D == 0, "whole turns");
+    bf16x8 wb[D][4];
+    auto load_b = [&](int s, bf16x8* b) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) b[j] = ldfrag(wf + opaque, (wv * 4 + j) * S + s);
+    };
+#pragma unroll
+    for (int s = 0; s < D; ++s) load_b(s, wb[s]);
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // not unrolled across turns: the compiler would hoist every weight load
+#pragma unroll 1
+    for (int s0 = 0; s0 < S; s0 += D)
+#pragma unroll
+      for (int q = 0; q < D; ++q) {
+        const int s = s0 + q;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const bf16x8 a = *(const bf16x8*)&rows[(i * 16 + lr) * pitch + s * 32 + 8 * lg];
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, wb[q][j], acc[i][j], 0, 0, 0);
+        }
+        if (s + D < S) load_b(s + D, wb[q]);
+      }
+  };
+  // a layer's 32 x 64 results: to LDS as the next product's rows, to memory
+  // as an operand of the weight gradients
+  auto emit = [&](const f32x4 (&h)[2], int j, __bf16* rows, int pitch, __bf16* out, int kb) {
+    const int n = wv * 64 + j * 16 + lr;
+    if (rows) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) rows[(i * 16 + 4 * lg + e) * pitch + n] = (__bf16)h[i][e];
+    }
+    stfrag(out, kb * 16 + wv * 4 + j, pack_rows(h[0], h[1]));
+  };
+  auto bias_gelu = [&](const float* bias, f32x4 (&z)[2][4], __bf16* rows, int pitch, __bf16* out,
+                       int kb) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float bn = bias[wv * 64 + j * 16 + lr];
+      f32x4 h[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          z[i][j][e] = acc[i][j][e] + bn;
+          h[i][e] = gelu(z[i][j][e]);
+        }
+      emit(h, j, rows, pitch, out, kb);
+    }
+  };
+  auto gelu_bwd = [&](const f32x4 (&z)[2][4], float* db, __bf16* rows, int pitch, __bf16* out,
+                      int kb) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      f32x4 dz[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) dz[i][e] = acc[i][j][e] * gelu_prime(z[i][j][e]);
+      db[j] += sum_rows(dz[0], dz[1]);
+      emit(dz, j, rows, pitch, out, kb);
+    }
+  };
+  using K1 = std::integral_constant<int, NET_S1>;
+  using K2 = std::integral_constant<int, NET_S2>;
+
+  int kb = blockIdx.x;
+  do {
+    const long row0 = (long)kb * 32;
+    // an offset of zero that the compiler cannot see through: it would hoist
+    // the weight loads out of this loop and spill them
+    if (LOOP) {
+      asm volatile("" : "+s"(opaque));
+      __syncthreads();   // the previous block's h2 is read
+    }
+    // ---- features: 8 rows x 512 bytes per pass
+    {
+      f32x4 r[16];
+      const int c = (threadIdx.x & 31) * 4, rr = threadIdx.x >> 5;
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        const int f = (q & 3) * 128 + c;
+        r[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (f < MLP_NIN) r[q] = ld4(x, (row0 + (q >> 2) * 8 + rr) * MLP_NIN + f);
+      }
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        bf16x4 h;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) h[e] = (__bf16)r[q][e];
+        *(bf16x4*)&xs[((q >> 2) * 8 + rr) * TR_XP + (q & 3) * 128 + c] = h;
+      }
+    }
+    __syncthreads();
+    product(xs, TR_XP, p.W1f, K1{});
+    // the features as an operand (8 of the 32 column blocks per wave)
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int fb = wv * 8 + q;
+      bf16x8 v;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        v[e] = xs[(4 * lg + e) * TR_XP + fb * 16 + lr];
+        v[4 + e] = xs[(16 + 4 * lg + e) * TR_XP + fb * 16 + lr];
+      }
+      stfrag(t.xf, kb * 32 + fb, v);
+    }
+    bias_gelu(p.master + MLP_OFF_B1, z1, hs, NET_HP, t.h1f, kb);
+    __syncthreads();
+    product(hs, NET_HP, p.W2f, K2{});
+    bias_gelu(p.master + MLP_OFF_B2, z2, xs, NET_HP, t.h2f, kb);   // h2 over the features
+    __syncthreads();
+    // ---- outputs, loss and their error: the first wave
+    if (wv == 0) {
+      f32x4 y[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+      for (int s = 0; s < NET_S2; ++s) {
+        const bf16x8 b = ldfrag(p.W3f + opaque, s);
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+          y[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+              *(const bf16x8*)&xs[(i * 16 + lr) * NET_HP + s * 32 + 8 * lg], b, y[i], 0, 0, 0);
+      }
+      f32x4 dy[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+      if (lr < MLP_NOUT) {
+        const float b3 = p.master[MLP_OFF_B3 + lr];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int r = i * 16 + 4 * lg + e;
+            const float d = (y[i][e] + b3) - target[(row0 + r) * MLP_NOUT + lr];
+            loss += (double)d * d;
+            dy[i][e] = scale * d;
+            ds[r * TR_DP + lr] = (__bf16)dy[i][e];
+          }
+      }
+      db3 += sum_rows(dy[0], dy[1]);
+      stfrag(t.dyf, kb, pack_rows(dy[0], dy[1]));
+    }
+    __syncthreads();
+    product(ds, TR_DP, p.W3Tf, std::integral_constant<int, 1>{});
+    gelu_bwd(z2, db2, hs, NET_HP, t.dz2f, kb);   // dz2 over h1
+    __syncthreads();
+    product(hs, NET_HP, p.W2Tf, K2{});
+    gelu_bwd(z1, db1, nullptr, 0, t.dz1f, kb);
+    kb += gridDim.x;
+  } while (LOOP && kb < B / 32);
+
+  // this workgroup's bias sums (any lane of a column) and squared error
+  float* pb = t.biasp + (long)blockIdx.x * TR_NB;
+  if (lg == 0)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      pb[wv * 64 + j * 16 + lr] = db1[j];
+      pb[MLP_NH + wv * 64 + j * 16 + lr] = db2[j];
+    }
+  if (wv == 0) {
+    if (lane < MLP_NOUT) pb[2 * MLP_NH + lane] = db3;
+#pragma unroll
+    for (int h = 32; h > 0; h >>= 1) loss += __shfl_xor(loss, h);
+    if (lane == 0) t.lossp[blockIdx.x] = loss;
+  }
+}
+
+// Tiles of the weight gradients: 4 x 8 of dW1 (the last column tile half
+// padding), 4 x 4 of dW2, 1 x 4 of dW3 (16 rows, 4 real).  A tile's batch
+// range is dealt to the four waves, whose sums are added in LDS.
+constexpr int WG_T1 = 32, WG_T2 = WG_T1 + 16, WG_TILES = WG_T2 + 4;
+
+__global__ void __launch_bounds__(256) mlp_wgrad_kernel(MlpTrain t, int nkb, int nsplit,
+                                                        float* out) {
+  __shared__ __attribute__((aligned(16))) float red[4][64 * 64];
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int tile = blockIdx.x, sp = blockIdx.y;
+  const __bf16 *A, *Bm;
+  int na, nb, a0, b0, ld, cols, off;   // operand blocks per 32 rows; this tile's first ones
+  if (tile < WG_T1) {
+    A = t.dz1f; na = 16; a0 = (tile >> 3) * 4;
+    Bm = t.xf; nb = 32; b0 = (tile & 7) * 4;
+    ld = MLP_NIN; cols = MLP_NIN; off = MLP_OFF_W1;
+  } else if (tile < WG_T2) {
+    A = t.dz2f; na = 16; a0 = ((tile - WG_T1) >> 2) * 4;
+    Bm = t.h1f; nb = 16; b0 = ((tile - WG_T1) & 3) * 4;
+    ld = MLP_NH; cols = MLP_NH; off = MLP_OFF_W2;
+  } else {
+    A = t.dyf; na = 1; a0 = 0;
+    Bm = t.h2f; nb = 16; b0 = (tile - WG_T2) * 4;
+    ld = MLP_NH; cols = MLP_NH; off = MLP_OFF_W3;
+  }
+  const int ni = na == 1 ? 1 : 4;   // uniform
+  const int k0 = (int)((long)sp * nkb / nsplit), k1 = (int)((long)(sp + 1) * nkb / nsplit);
+  f32x4 acc[4][4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  bf16x8 a[2][4], b[2][4];
+  auto load = [&](int kb, bf16x8* va, bf16x8* vb) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (i < ni) va[i] = ldfrag(A, kb * na + a0 + i);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) vb[j] = ldfrag(Bm, kb * nb + b0 + j);
+  };
+  auto mma = [&](const bf16x8* va, const bf16x8* vb) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (i < ni)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[i], vb[j], acc[i][j], 0, 0, 0);
+  };
+  int kb = k0 + wv;
+  if (kb < k1) load(kb, a[0], b[0]);
+  for (; kb < k1; kb += 8) {   // two blocks per turn, each loaded one ahead
+    if (kb + 4 < k1) load(kb + 4, a[1], b[1]);
+    mma(a[0], b[0]);
+    if (kb + 4 < k1) {
+      if (kb + 8 < k1) load(kb + 8, a[0], b[0]);
+      mma(a[1], b[1]);
+    }
+  }
+  // lane: rows 16 i + 4 (lane / 16) + e, column 16 j + lane % 16
+  const int lr = lane & 15, lg = lane >> 4;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    if (i < ni)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          red[wv][(16 * i + 4 * lg + e) * 64 + 16 * j + lr] = acc[i][j][e];
+  __syncthreads();
+  float* o = out + (long)sp * MLP_NPARAM + off;
+  const int rows = na == 1 ? MLP_NOUT : 64;
+  for (int q = threadIdx.x; q < rows * 64; q += 256) {
+    const int r = a0 * 16 + (q >> 6), c = b0 * 16 + (q & 63);
+    if (c < cols) o[r * ld + c] = ((red[0][q] + red[1][q]) + red[2][q]) + red[3][q];
+  }
+}
+
+// Sums of the splits, in order; biases from the workgroups' sums.  The first
+// blocks take the weights (a thread per parameter), then 33 blocks of 16
+// biases (16 lanes each over the workgroups, added in a fixed tree); one
+// more adds the loss.  adam.lr > 0: Adam (Kingma & Ba) on the FP32
+// master parameters, refreshing the BF16 copies.
+struct AdamArgs {
+  float *m1, *m2;
+  float lr, c1, c2;   // c = 1 - beta^t
+};
+constexpr int GF_BIAS = (2 * MLP_NH + MLP_NOUT + 15) / 16;
+
+__global__ void __launch_bounds__(256) mlp_grad_final_kernel(MlpParams p, MlpTrain t,
+                                                             const float* part, int nsplit,
+                                                             int nwg, float* grad, AdamArgs ad) {
+  auto finish = [&](int q, float g) {
+    grad[q] = g;
+    if (ad.lr > 0.f) {
+      const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
+      const float mm = b1 * ad.m1[q] + (1.f - b1) * g;
+      const float vv = b2 * ad.m2[q] + (1.f - b2) * g * g;
+      ad.m1[q] = mm;
+      ad.m2[q] = vv;
+      const float w = p.master[q] - ad.lr * (mm / ad.c1) / (sqrtf(vv / ad.c2) + eps);
+      p.master[q] = w;
+      mlp_write_bf16(p, q, w);
+    }
+  };
+  const int nw = (MLP_NPARAM + 255) / 256;
+  if ((int)blockIdx.x < nw) {
+    const int q = blockIdx.x * 256 + threadIdx.x;
+    const bool bias = (q >= MLP_OFF_B1 && q < MLP_OFF_W2) || (q >= MLP_OFF_B2 && q < MLP_OFF_W3) ||
+                      q >= MLP_OFF_B3;
+    if (q >= MLP_NPARAM || bias) return;
+    float s = 0.f;
+    for (int z = 0; z < nsplit; ++z) s += part[(long)z * MLP_NPARAM + q];
+    finish(q, s);
+    return;
+  }
+  const int bb = (int)blockIdx.x - nw;
+  if (bb < GF_BIAS) {
+    __shared__ float red[16][17];
+    const int c = threadIdx.x & 15, rl = threadIdx.x >> 4, n = bb * 16 + c;
+    float s = 0.f;
+    if (n < 2 * MLP_NH + MLP_NOUT)
+#pragma unroll 8
+      for (int w = rl; w < nwg; w += 16) s += t.biasp[(long)w * TR_NB + n];
+    red[rl][c] = s;
+    __syncthreads();
+    if (rl == 0 && n < 2 * MLP_NH + MLP_NOUT) {
+      float a = 0.f;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) a += red[r][c];
+      finish(n < MLP_NH ? MLP_OFF_B1 + n
+                        : (n < 2 * MLP_NH ? MLP_OFF_B2 + n - MLP_NH : MLP_OFF_B3 + n - 2 * MLP_NH),
+             a);
+    }
+    return;
+  }
+  __shared__ double sd[256];
+  double s = 0.0;
+  for (int w = threadIdx.x; w < nwg; w += 256) s += t.lossp[w];
+  sd[threadIdx.x] = s;
+  __syncthreads();
+  for (int h = 128; h > 0; h >>= 1) {
+    if ((int)threadIdx.x < h) sd[threadIdx.x] += sd[threadIdx.x + h];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) t.loss[0] = sd[0];
 }
 
 // The closure network on every cell of a model: 16 MI consecutive cells per
@@ -745,7 +799,7 @@ __global__ void __launch_bounds__(256, 2) closure_mlp_region_kernel(Dims d, cons
   }
   __syncthreads();
   RegionStage<MI, GW> stage{rg, sx};
-  net_rows<MI>(p, lds, sx, stage, [&](int i, f32x4 c) {
+  net_rows<MI>(p, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lds, sx, stage, [&](int i, f32x4 c) {
     *(__attribute__((address_space(1))) f32x4*)(
         y + (long)(c0 + 16 * i + (int)(threadIdx.x & 15)) * MLP_NOUT) = c;
   });
@@ -817,7 +871,7 @@ __global__ void __launch_bounds__(256) closure_mlp_gather_kernel(Dims d, const T
   }
   GatherStage<T> stage{u, v, w, tt, ss, st, hs, corner, (int)d.sy, (int)d.sz, live, {}, {}};
   stage.load(0);
-  net_rows<4>(p, hs, hs, stage, [&](int i, f32x4 c) {
+  net_rows<4>(p, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), hs, hs, stage, [&](int i, f32x4 c) {
     const int row = c0 + 16 * i + (int)(threadIdx.x & 15);
     if (row < ncell)
       *(__attribute__((address_space(1))) f32x4*)(y + (long)row * MLP_NOUT) = c;
@@ -874,12 +928,25 @@ __global__ void __launch_bounds__(256) closure_apply_kernel(Dims d, const float*
   gw[p] = (k == 0) ? (T)0 : (T)(-(F(2, i, j, k) - F(2, i, j, k - 1)) * rz);
 }
 
-template <class T>
-hipError_t launch_closure_features(const Dims& d, const T* u, const T* v, const T* w, const T* t,
-                                   const T* s, ClosureStats st, __bf16* xb, hipStream_t stream) {
-  const long n = (long)d.nx * d.ny * d.nz * 512;
-  hipLaunchKernelGGL(closure_features_kernel<T>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0,
-                     stream, d, u, v, w, t, s, st, xb);
+// Splits of the batch in the weight gradients: enough that the 52 tiles
+// occupy the 256 CUs, each wave with at least four 32-row blocks.
+static int wgrad_splits(int nkb) { return std::max(1, std::min(nkb / 16, TR_MAXSPLIT)); }
+
+hipError_t launch_mlp_gradients(const MlpParams& p, const MlpTrain& t, const float* x,
+                                const float* target, int B, float* grad, float* m1, float* m2,
+                                float lr, int step, hipStream_t s) {
+  const int nkb = B / 32, nwg = std::min(nkb, TR_MAXWG), nsplit = wgrad_splits(nkb);
+  const auto rows = nwg == nkb ? mlp_fwdbwd_kernel<false> : mlp_fwdbwd_kernel<true>;
+  hipLaunchKernelGGL(rows, dim3(nwg), dim3(256), 0, s, p, t, x, target, B);
+  hipLaunchKernelGGL(mlp_wgrad_kernel, dim3(WG_TILES, nsplit), dim3(256), 0, s, t, nkb, nsplit,
+                     t.part);
+  AdamArgs ad{m1, m2, lr, 1.f, 1.f};
+  if (lr > 0.f) {
+    ad.c1 = 1.f - powf(0.9f, (float)step);
+    ad.c2 = 1.f - powf(0.999f, (float)step);
+  }
+  hipLaunchKernelGGL(mlp_grad_final_kernel, dim3((MLP_NPARAM + 255) / 256 + GF_BIAS + 1), dim3(256),
+                     0, s, p, t, (const float*)t.part, nsplit, nwg, grad, ad);
   return hipGetLastError();
 }
 
@@ -946,12 +1013,6 @@ hipError_t launch_closure_apply(const Dims& d, const float* y, ClosureStats st, 
   return hipGetLastError();
 }
 
-template hipError_t launch_closure_features<float>(const Dims&, const float*, const float*,
-                                                   const float*, const float*, const float*,
-                                                   ClosureStats, __bf16*, hipStream_t);
-template hipError_t launch_closure_features<double>(const Dims&, const double*, const double*,
-                                                    const double*, const double*, const double*,
-                                                    ClosureStats, __bf16*, hipStream_t);
 template hipError_t launch_closure_apply<float>(const Dims&, const float*, ClosureStats, double,
                                                 float*, float*, float*, float*, hipStream_t);
 template hipError_t launch_closure_apply<double>(const Dims&, const float*, ClosureStats, double,

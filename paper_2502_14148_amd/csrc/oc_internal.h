@@ -303,52 +303,43 @@ constexpr int MLP_OFF_W3 = MLP_OFF_B2 + MLP_NH;
 constexpr int MLP_OFF_B3 = MLP_OFF_W3 + MLP_NOUT * MLP_NH;
 constexpr int MLP_NPARAM = MLP_OFF_B3 + MLP_NOUT;
 
-enum { EPI_STORE = 0, EPI_BIAS = 1, EPI_BIAS_GELU = 2, EPI_GELU_BWD = 3 };
-
-struct GemmArgs {
-  const __bf16* A;
-  int lda, transA;          // transA = 0: A[m][k] at A[m*lda + k]; 1: at A[k*lda + m]
-  const __bf16* B;
-  int ldb, transB;          // transB = 0: B[k][n] at B[k*ldb + n]; 1: at B[n*ldb + k]
-  int M, N, K;              // K a multiple of 32
-  int epi;
-  float* C;
-  int ldc;
-  const float* bias;        // EPI_BIAS, EPI_BIAS_GELU
-  const float* Z;           // EPI_GELU_BWD: pre-activation, same layout as C
-  __bf16* H;                // EPI_BIAS_GELU / EPI_GELU_BWD: BF16 copy of the result
-  int ldh;
-  int ksplit;               // > 1: K split over blockIdx.z (EPI_STORE only), partial
-  float* part;              // results in part[z][M][N], summed in z order into C
-};
-constexpr int MLP_MAX_KSPLIT = 64;
-// FP32 scratch of the split-K partials and the column-sum partials
-constexpr long MLP_PART_FLOATS = (long)MLP_MAX_KSPLIT * MLP_NH * MLP_KIN;
-constexpr int COLSUM_MAX_CHUNKS = 256;
-
 struct MlpParams {
   float* master;            // FP32: W1 | b1 | W2 | b2 | W3 | b3
-  __bf16* W1b;              // 256 x 512 (columns >= 500 zero)
-  __bf16* W2b;              // 256 x 256
-  __bf16* W2bT;             // its transpose (backward pass)
-  __bf16* W3b;              // 32 x 256 (rows >= 4 zero)
-  // the same in MFMA operand order (16-row x 32-k blocks of one kilobyte)
-  __bf16* W1f;              // 16 row blocks x 16 k blocks
+  // BF16 copies in MFMA operand order (blocks of 16 rows x 32 k, one kilobyte)
+  __bf16* W1f;              // 16 row blocks x 16 k blocks (k >= 500 zero)
   __bf16* W2f;              // 16 x 8
+  __bf16* W2Tf;             // 16 x 8, the transpose
   __bf16* W3f;              // 1 x 8 (rows >= 4 zero)
+  __bf16* W3Tf;             // 16 x 1, the transpose (k >= 4 zero)
+};
+
+// Scratch of the gradients of a batch of B rows: the BF16 operands of the
+// weight gradients, per 32 rows (operand blocks of one kilobyte), and partial
+// sums.
+constexpr int TR_MAXWG = 1024;     // workgroups of the row-local kernel
+constexpr int TR_MAXSPLIT = 16;    // splits of the batch in the weight gradients
+constexpr int TR_NB = 520;         // row pitch of the bias sums (b1 | b2 | b3)
+struct MlpTrain {
+  __bf16* xf;               // features: 32 blocks
+  __bf16* h1f;              // activations: 16 blocks each
+  __bf16* h2f;
+  __bf16* dyf;              // output errors: 1 block
+  __bf16* dz2f;             // layer errors: 16 blocks each
+  __bf16* dz1f;
+  float* biasp;             // TR_MAXWG x TR_NB bias sums
+  double* lossp;            // TR_MAXWG squared errors
+  double* loss;             // their sum
+  float* part;              // TR_MAXSPLIT x MLP_NPARAM
 };
 
 __device__ void mlp_write_bf16(const MlpParams& p, int t, float w);
-hipError_t launch_gemm_bf16(const GemmArgs& g, hipStream_t s);
-hipError_t launch_loss_grad(const float* Y, int ldy, const float* T, int B, float* dY, __bf16* dYb,
-                            int ldd, double* partial, int nblocks, hipStream_t s);
-hipError_t launch_colsum(const float* a, int rows, int cols, int lda, float* out, float* part,
-                         hipStream_t s);
 // y (B x 4) = network(x), x: B x 500 FP32 (element-aligned), B a multiple of 32
 hipError_t launch_mlp_forward(const MlpParams& p, const float* x, int B, float* y, hipStream_t s);
-hipError_t launch_features_to_bf16(const float* x, int B, __bf16* xb, hipStream_t s);
-hipError_t launch_adam(const MlpParams& p, const float* grad, float* m1, float* m2, int n, float lr,
-                       int step, hipStream_t s);
+// grad = gradients of the mean squared error (and *t.loss the sum of squared
+// errors); lr > 0: then one Adam step, number `step`, on p with moments m1, m2
+hipError_t launch_mlp_gradients(const MlpParams& p, const MlpTrain& t, const float* x,
+                                const float* target, int B, float* grad, float* m1, float* m2,
+                                float lr, int step, hipStream_t s);
 hipError_t launch_refresh_bf16(const MlpParams& p, int n, hipStream_t s);
 
 // Closure statistics: input mean/std of (u, v, w, b), output mean/std of the
@@ -359,9 +350,6 @@ struct ClosureStats {
   float g_alpha, g_beta, t_ref, s_ref;   // b = g_alpha (T - t_ref) - g_beta (S - s_ref)
   float inv_galpha;                      // temperature flux = buoyancy flux / (g alpha)
 };
-template <class T>
-hipError_t launch_closure_features(const Dims& d, const T* u, const T* v, const T* w, const T* t,
-                                   const T* s, ClosureStats st, __bf16* xb, hipStream_t stream);
 template <class T>
 hipError_t launch_closure_apply(const Dims& d, const float* y, ClosureStats st, double rdz,
                                 T* gu, T* gv, T* gw, T* gt, hipStream_t stream);

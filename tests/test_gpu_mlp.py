@@ -186,3 +186,27 @@ def test_closure_row_lengths(gpu_lib, n, precision):
     """x rows of 32k cells (three groups to a row) and the short rows that
     take the direct gather."""
     test_closure_tendency_parity(gpu_lib, n, precision)
+
+
+@pytest.mark.parametrize("B", [32, 96, 4096, 32800])
+def test_gradient_block_counts(gpu_lib, B):
+    """One 32-row block, a few, split batches, and more blocks than
+    workgroups (1024 of them, the last batch one block over); bars of
+    test_gradient_parity."""
+    p, X, T = _data(9, B)
+    net = gpu_lib.Mlp(B)
+    net.set_params(p)
+    g, loss = net.gradients(_dev(X), _dev(T))
+    g = gpu_lib.unpack_mlp(g.cpu().numpy())
+    Y, cache = cl.forward(p, X, use_bf16=True)
+    go = cl.backward(p, cache, Y, T, use_bf16=True)
+    assert abs(loss - cl.mse(Y, T)) < 2e-3 * cl.mse(Y, T)
+    for k in go:
+        assert rel_l2(g[k], go[k]) < 2e-3 * (5 if k.startswith("b") else 1), (k, rel_l2(g[k], go[k]))
+    # an Adam step takes the same gradients: its first update is
+    # -lr g / (|g| + eps) to FP32 rounding
+    net.train_step(_dev(X), _dev(T), 1e-3, want_loss=False)
+    q = net.get_params()
+    for k in go:
+        step = -1e-3 * g[k] / (np.abs(g[k]) + 1e-8)
+        assert np.max(np.abs((q[k] - p[k]) - step)) < 1e-6, k
