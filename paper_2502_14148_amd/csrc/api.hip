@@ -47,7 +47,7 @@ struct Layout {
   uint64_t baro[15], metric, hzeta, hpx, hpy, hmet;
   uint64_t gc[MAXF];
   uint64_t les_nu, les_kap[OC_MAX_TRACERS], les_d2;
-  uint64_t mask, ibits, cg_x, cg_r, cg_q, cg_aq, cg_part, cg_scal;
+  uint64_t mask, ibits, cg_b, cg_r, cg_idx, cg_s, cg_q, cg_aq, cg_az, cg_part, cg_scal;
   uint64_t zt64, ztT, vfac;
   uint64_t total;
 };
@@ -105,12 +105,16 @@ Layout make_layout(const oc_grid_desc& g, const oc_model_desc& m) {
     const uint64_t nv = align256((uint64_t)g.nx * g.ny * g.nz * 8);
     L.mask = off; off += fb;
     L.ibits = off; off += align256((uint64_t)g.nx * g.ny * g.nz);
-    L.cg_x = off; off += nv;
+    L.cg_b = off; off += nv;
     L.cg_r = off; off += nv;
+    // list vectors: the list may hold almost every cell
+    L.cg_idx = off; off += align256((uint64_t)g.nx * g.ny * g.nz * 4);
+    L.cg_s = off; off += nv;
     L.cg_q = off; off += nv;
     L.cg_aq = off; off += nv;
-    L.cg_part = off; off += align256((uint64_t)IB_PART_CAP * 8);
-    L.cg_scal = off; off += align256((uint64_t)CG_NSCAL * 8);
+    L.cg_az = off; off += nv;
+    L.cg_part = off; off += align256((uint64_t)(IB_PART_CAP + IB_NPART) * 8);
+    L.cg_scal = off; off += align256((uint64_t)CG_NSCAL * 8 + 8);   // and the ticket
   }
   L.zt64 = off; off += align256((uint64_t)zt64_len(g.nz) * 8);
   L.ztT = off; off += align256((uint64_t)ztT_len(g.nz) * esz);
@@ -452,6 +456,52 @@ std::vector<uint8_t> geometry_bits(const oc_model* m, const uint8_t* solid) {
   return out;
 }
 
+// The list of the conjugate-gradient iteration (fluid cells next to an
+// immersed one, ascending), and the levels and rows that hold it (in) and
+// that hold it and its neighbours across open faces (out).
+std::vector<int> boundary_list(oc_model* m, const std::vector<uint8_t>& bits) {
+  const Dims& d = m->dims;
+  std::vector<int> list;
+  int in[4] = {d.nz, -1, d.ny, -1}, out[4] = {d.nz, -1, d.ny, -1};   // k, j: first, last
+  auto see = [](int* r, int j, int k) {
+    r[0] = std::min(r[0], k);
+    r[1] = std::max(r[1], k);
+    r[2] = std::min(r[2], j);
+    r[3] = std::max(r[3], j);
+  };
+  long n = 0;
+  for (int k = 0; k < d.nz; ++k)
+    for (int j = 0; j < d.ny; ++j)
+      for (int i = 0; i < d.nx; ++i, ++n) {
+        const unsigned b = bits[n];
+        if (!(b & IB_FLUID)) continue;
+        unsigned want = IB_XM | IB_XP | IB_YM | IB_YP;
+        if (!d.zb || k > 0) want |= IB_ZM;
+        if (!d.zb || k + 1 < d.nz) want |= IB_ZP;
+        if ((b & want) == want) continue;
+        list.push_back((int)n);
+        see(in, j, k);
+        see(out, j, k);
+        if (b & IB_YM) see(out, (j + d.ny - 1) % d.ny, k);
+        if (b & IB_YP) see(out, (j + 1) % d.ny, k);
+        if (b & IB_ZM) see(out, j, (k + d.nz - 1) % d.nz);
+        if (b & IB_ZP) see(out, j, (k + 1) % d.nz);
+      }
+  if (list.empty()) in[0] = in[1] = in[2] = in[3] = out[0] = out[1] = out[2] = out[3] = 0;
+  SpecBufs& sb = m->cgbox;
+  sb = m->sb;
+  sb.stop = m->cg.scal + CG_DONE;
+  sb.kin0 = in[0];
+  sb.kin1 = in[1] + 1;
+  sb.jin0 = in[2] & ~1;
+  sb.jin1 = (in[3] | 1) + 1;
+  sb.kout0 = out[0];
+  sb.kout1 = out[1] + 1;
+  sb.jout0 = out[2] & ~1;
+  sb.jout1 = (out[3] | 1) + 1;
+  return list;
+}
+
 template <class T>
 int tendency_call(oc_model* m, int in, int out, int stage, double dt, int combine,
                   hipStream_t s) {
@@ -520,116 +570,96 @@ int tendency_call(oc_model* m, int in, int out, int stage, double dt, int combin
   return OC_OK;
 }
 
-// The FFT/DCT solve of the whole box applied to a dense FP64 field: sb.p =
-// L^-1 src (the preconditioner of the immersed-boundary iteration); the last
-// pass also leaves the partial sums of src . sb.p in cg.part (*npart).  The
-// passes do nothing once the iteration's stop flag is set.
-int fft_solve_dense(oc_model* m, const double* src, int* npart, hipStream_t s) {
-  SpecBufs sb = m->sb;
-  sb.stop = m->cg.scal + CG_DONE;
-  {
-    ProfScope ps(m, OC_PROF_FFT_X_FWD, s);
-    OC_CHECK_HIP(launch_poisson_x_forward_dense(m->dims, src, sb, s));
-  }
-  {
-    ProfScope ps(m, OC_PROF_FFT_Y_FWD, s);
-    OC_CHECK_HIP(launch_poisson_y(m->dims, sb, -1, s));
-  }
-  {
-    ProfScope ps(m, OC_PROF_Z_SOLVE, s);
-    OC_CHECK_HIP(launch_poisson_spectral(m->dims, sb, s));
-  }
-  {
-    ProfScope ps(m, OC_PROF_FFT_Y_INV, s);
-    OC_CHECK_HIP(launch_poisson_y(m->dims, sb, 1, s));
-  }
-  {
-    ProfScope ps(m, OC_PROF_FFT_X_INV, s);
-    OC_CHECK_HIP(launch_poisson_x_inverse_dot(m->dims, sb, src, m->cg.part, IB_PART_CAP, npart,
-                                              s));
+// The first npass of the five passes of the whole box's FFT/DCT solve of a
+// dense FP64 field (all five: sb.p = L^-1 src), within the ranges of sb.
+int box_solve(oc_model* m, const double* src, const SpecBufs& sb, int npass, hipStream_t s) {
+  static const int cls[5] = {OC_PROF_FFT_X_FWD, OC_PROF_FFT_Y_FWD, OC_PROF_Z_SOLVE,
+                             OC_PROF_FFT_Y_INV, OC_PROF_FFT_X_INV};
+  for (int pass = 0; pass < npass; ++pass) {
+    ProfScope ps(m, cls[pass], s);
+    OC_CHECK_HIP(launch_poisson_box(m->dims, src, sb, pass, s));
   }
   return OC_OK;
 }
 
 // Pressure correction with an immersed boundary: conjugate gradients on the
-// masked Poisson equation, preconditioned by the FFT solve of the whole box
-// (the residual is zero in immersed cells; the result is masked), until
-// |r| <= cg_tol |b| or cg_maxiter iterations.  The scalars of an iteration
-// stay on the device, and every kernel of an iteration does nothing once the
-// stop flag is set, so the host need not look at the flag after every
-// iteration: it first looks after one iteration fewer than the previous
-// solve took, then after every iteration (solves of successive substeps
-// take similar counts).  Queued iterations past convergence cost launches
-// only.
+// masked Poisson equation, preconditioned by the FFT solve of the whole box,
+// until |r| <= cg_tol |b| or cg_maxiter iterations (immersed.hip describes the
+// iteration; the first one is the iterate P L^-1 b).  The scalars of an
+// iteration stay on the device, and every kernel of an iteration does
+// nothing once the stop flag is set, so the host need not look at the flag
+// after every iteration: it first looks after one iteration fewer than the
+// previous solve took, then after every iteration (solves of successive
+// substeps take similar counts).  Queued iterations past convergence cost
+// launches only.
 template <class T>
 int pressure_call_immersed(oc_model* m, int which, double dt_eff, hipStream_t s) {
   T* u = (T*)m->state[which][0];
   T* v = (T*)m->state[which][1];
   T* w = (T*)m->state[which][2];
-  const T* mask = (const T*)m->mask;
   const Dims& d = m->dims;
   const CgBufs& cg = m->cg;
   const double tol2 = m->md.cg_tol * m->md.cg_tol;
   const int maxit = m->md.cg_maxiter;
   const double* z = m->sb.p;
-  m->p_pending = false;   // sb.p is the iteration's work vector, then the solution
+  const double rdx2 = 1.0 / (m->dx * m->dx), rdy2 = 1.0 / (m->dy * m->dy);
+  const double rdz2 = 1.0 / (m->dz * m->dz);
+  m->p_pending = false;   // sb.p is the iteration's work vector
   {
     ProfScope pc(m, OC_PROF_CG, s);
     OC_CHECK_HIP(launch_ib_rhs<T>(d, u, v, w, m->ibits, 1.0 / dt_eff, 1.0 / m->dx,
                                   1.0 / m->dy, 1.0 / m->dz, cg, s));
-    OC_CHECK_HIP(launch_ib_finalize(cg, CG_FIN_BNORM, tol2, maxit, s));
   }
-  int npart = 0;
-  int rc = fft_solve_dense(m, cg.r, &npart, s);
+  SpecBufs all = m->sb;   // the whole grid in and out
+  all.kin1 = all.kout1 = d.nz;
+  all.jin1 = all.jout1 = d.ny;
+  SpecBufs first = m->cgbox;   // z = L^-1 b is read on the list and its neighbours
+  first.kin0 = first.jin0 = 0;
+  first.kin1 = d.nz;
+  first.jin1 = d.ny;
+  int rc = box_solve(m, cg.b, first, 5, s);
   if (rc) return rc;
   {
     ProfScope pc(m, OC_PROF_CG, s);
-    OC_CHECK_HIP(launch_ib_finalize(cg, CG_FIN_RZ0, tol2, maxit, s, npart));
-    OC_CHECK_HIP(launch_ib_dir(d, m->ibits, cg, z, s));
+    OC_CHECK_HIP(launch_ib_start(d, m->ibits, rdx2, rdy2, rdz2, cg, z, tol2, maxit, s));
   }
-  const double rdx2 = 1.0 / (m->dx * m->dx), rdy2 = 1.0 / (m->dy * m->dy);
-  const double rdz2 = 1.0 / (m->dz * m->dz);
   const int first_look = std::max(1, m->cg_iterations - 1);
-  for (int it = 0; it < maxit; ++it) {
-    {
-      ProfScope pc(m, OC_PROF_CG, s);
-      OC_CHECK_HIP(launch_ib_apply(d, m->ibits, rdx2, rdy2, rdz2, cg, s));
-      OC_CHECK_HIP(launch_ib_finalize(cg, CG_FIN_ALPHA, tol2, maxit, s));
-      OC_CHECK_HIP(launch_ib_update(d, cg, s));
-      OC_CHECK_HIP(launch_ib_finalize(cg, CG_FIN_RES, tol2, maxit, s));
-    }
-    if (it + 1 >= first_look || it + 1 == maxit) {   // the last iteration always looks
+  for (int it = 1;; ++it) {
+    if (it >= first_look || it >= maxit) {   // the last iteration always looks
       OC_CHECK_HIP(hipMemcpyAsync(m->cg_host, cg.scal, CG_NSCAL * sizeof(double),
                                   hipMemcpyDeviceToHost, s));
       OC_CHECK_HIP(hipStreamSynchronize(s));
-      if (m->cg_host[CG_DONE] != 0.0) break;
+      if (m->cg_host[CG_DONE] != 0.0 || it >= maxit) break;
     }
-    rc = fft_solve_dense(m, cg.r, &npart, s);
+    rc = box_solve(m, cg.r, m->cgbox, 5, s);
     if (rc) return rc;
-    {
-      ProfScope pc(m, OC_PROF_CG, s);
-      OC_CHECK_HIP(launch_ib_finalize(cg, CG_FIN_BETA, tol2, maxit, s, npart));
-      OC_CHECK_HIP(launch_ib_dir(d, m->ibits, cg, z, s));
-    }
-  }
-  {
     ProfScope pc(m, OC_PROF_CG, s);
-    OC_CHECK_HIP(launch_ib_xfinal(d, cg, s));
+    OC_CHECK_HIP(launch_ib_iterate(d, m->ibits, rdx2, rdy2, rdz2, cg, z, tol2, maxit, s));
   }
   m->cg_iterations = (int)m->cg_host[CG_IT];
   m->cg_residual = m->cg_host[CG_BNORM2] > 0
                        ? std::sqrt(m->cg_host[CG_RNORM2] / m->cg_host[CG_BNORM2]) : 0.0;
+  // p = L^-1 (b + steps), transformed back and projected in one pass
+  rc = box_solve(m, cg.b, all, 4, s);
+  if (rc) return rc;
   Spacing sp{1.0 / m->dx, 1.0 / m->dy, m->zt64 + zt_rdzc(d.nz), m->zt64 + zt_rdzf(d.nz)};
   {
-    ProfScope pc(m, OC_PROF_CG, s);
-    OC_CHECK_HIP(launch_ib_gauge(d, m->ibits, cg, m->nfluid, s));
-    OC_CHECK_HIP(hipMemcpyAsync(m->sb.p, cg.x, (size_t)d.nx * d.ny * d.nz * sizeof(double),
-                                hipMemcpyDeviceToDevice, s));
-  }
-  {
     ProfScope ps(m, OC_PROF_PROJECT, s);
-    OC_CHECK_HIP(launch_project<T>(d, u, v, w, dt_eff, sp, cg.x, s, nullptr, 1, mask));
+    OC_CHECK_HIP(launch_poisson_x_inverse_project<T>(d, m->sb, u, v, w, dt_eff, sp, s, nullptr, 1,
+                                                     (const T*)m->mask));
   }
+  m->p_pending = true;
+  return OC_OK;
+}
+
+// p of the last solve from its spectrum into sb.p (nothing if it is there);
+// with an immersed boundary masked, and zero mean over the fluid cells.
+int materialise_pressure(oc_model* m, hipStream_t s) {
+  if (!m->p_pending) return OC_OK;
+  OC_CHECK_HIP(launch_poisson_x_inverse(m->dims, m->sb, s));
+  if (m->md.immersed)
+    OC_CHECK_HIP(launch_ib_gauge(m->dims, m->ibits, m->cg, m->sb.p, m->nfluid, s));
+  m->p_pending = false;
   return OC_OK;
 }
 
@@ -1221,10 +1251,20 @@ int set_immersed_call(oc_model* m, const uint8_t* solid, hipStream_t s) {
     set_error("oc_set_immersed: no fluid cell left");
     return OC_ERR_UNSUPPORTED;
   }
+  // the last solve's p belongs to the cells it was solved on
+  int rc = materialise_pressure(m, s);
+  if (rc) return rc;
   OC_CHECK_HIP(hipMemcpyAsync(m->mask, host.data(), host.size(), hipMemcpyHostToDevice, s));
   std::vector<uint8_t> bits = geometry_bits(m, solid);
   OC_CHECK_HIP(hipMemcpyAsync(m->ibits, bits.data(), bits.size(), hipMemcpyHostToDevice, s));
-  const int rc = mask_velocities_call<T>(m, s);
+  std::vector<int> list = boundary_list(m, bits);
+  m->cg.n = (int)list.size();
+  if (!list.empty())
+    OC_CHECK_HIP(hipMemcpyAsync((int*)m->cg.idx, list.data(), list.size() * sizeof(int),
+                                hipMemcpyHostToDevice, s));
+  // off the new list the residual is zero
+  OC_CHECK_HIP(hipMemsetAsync(m->cg.r, 0, (size_t)n * sizeof(double), s));
+  rc = mask_velocities_call<T>(m, s);
   if (rc) return rc;
   OC_CHECK_HIP(hipStreamSynchronize(s));  // the host copy of the mask goes out of scope
   m->nfluid = (double)nfluid;
@@ -1371,12 +1411,18 @@ int oc_model_create(const oc_grid* g, const oc_model_desc* md, void* workspace,
   }
   m->mask = md->immersed ? (void*)(m->ws + L.mask) : nullptr;
   m->ibits = md->immersed ? (uint8_t*)(m->ws + L.ibits) : nullptr;
-  m->cg.x = (double*)(m->ws + L.cg_x);
+  m->cg.b = (double*)(m->ws + L.cg_b);
   m->cg.r = (double*)(m->ws + L.cg_r);
+  m->cg.idx = (const int*)(m->ws + L.cg_idx);
+  m->cg.s = (double*)(m->ws + L.cg_s);
   m->cg.q = (double*)(m->ws + L.cg_q);
   m->cg.aq = (double*)(m->ws + L.cg_aq);
+  m->cg.az = (double*)(m->ws + L.cg_az);
   m->cg.part = (double*)(m->ws + L.cg_part);
+  m->cg.bpart = m->cg.part + IB_PART_CAP;
   m->cg.scal = (double*)(m->ws + L.cg_scal);
+  m->cg.ticket = (unsigned*)(m->cg.scal + CG_NSCAL);
+  m->cg.n = 0;
   m->cg_host = nullptr;
   m->cg_iterations = 0;
   m->cg_residual = 0.0;
@@ -1429,6 +1475,7 @@ int oc_model_create(const oc_grid* g, const oc_model_desc* md, void* workspace,
     if (e == hipSuccess) e = hipMemcpy(m->mask, ones.data(), ones.size(), hipMemcpyHostToDevice);
     std::vector<uint8_t> bits = geometry_bits(m, nullptr);
     if (e == hipSuccess) e = hipMemcpy(m->ibits, bits.data(), bits.size(), hipMemcpyHostToDevice);
+    (void)boundary_list(m, bits);   // empty
     if (e == hipSuccess) e = hipHostMalloc((void**)&m->cg_host, CG_NSCAL * sizeof(double));
   }
   if (e != hipSuccess) {
@@ -1580,10 +1627,8 @@ int oc_get_pressure(oc_model* m, double* buf, int32_t on_device, void* stream) {
   if (m->kind != OC_NONHYDROSTATIC) { set_error("nonhydrostatic model only"); return OC_ERR_UNSUPPORTED; }
   hipStream_t s = (hipStream_t)stream;
   const size_t bytes = (size_t)m->dims.nz * m->dims.ny * m->dims.nx * 8;
-  if (m->p_pending) {
-    OC_CHECK_HIP(launch_poisson_x_inverse(m->dims, m->sb, s));
-    m->p_pending = false;
-  }
+  const int rc = materialise_pressure(m, s);
+  if (rc) return rc;
   OC_CHECK_HIP(hipMemcpyAsync(buf, m->sb.p, bytes,
                               on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, s));
   if (!on_device) OC_CHECK_HIP(hipStreamSynchronize(s));

@@ -234,7 +234,6 @@ int upload_tables(oc_ensemble* e, const EnsTuning& tn, double dt) {
         hs.v[z] = m->state[out][1];
         hs.w[z] = m->state[out][2];
         hs.spec[z] = m->sb.spec;
-        hs.p[z] = m->sb.p;
       }
       OC_CHECK_HIP(hipMemcpy(c.slots[par], &hs, sizeof(hs), hipMemcpyHostToDevice));
     }

@@ -97,11 +97,13 @@ struct oc_model {
   void* les_kap[OC_MAX_TRACERS];
   void* les_d2;
   // immersed boundary: the padded mask (state precision, 1 = fluid), the
-  // conjugate-gradient vectors and scalars, pinned host copy of the scalars,
-  // the number of fluid cells and the last solve's statistics
+  // conjugate-gradient vectors and scalars, the ranges of the spectral buffers
+  // that hold the list's residual and need its solution, pinned host copy
+  // of the scalars, the number of fluid cells and the last solve's statistics
   void* mask;
   uint8_t* ibits;        // per-cell geometry bytes (IB_*), dense
   CgBufs cg;
+  SpecBufs cgbox;        // sb with the list's ranges
   double* cg_host;
   double nfluid;
   int cg_iterations;

@@ -210,6 +210,12 @@ struct SpecBufs {
   int nxp;                   // row pitch: nxh rounded up to 8 (128-byte rows)
   const double* stop = nullptr;  // optional device flag: while *stop != 0 the
                                  // passes return at once (a converged iteration)
+  // A right-hand side that is zero outside levels [kin0, kin1) and rows
+  // [jin0, jin1) (even bounds), and a solution wanted only on levels [kout0,
+  // kout1) and rows [jout0, jout1): the passes skip what these rule out
+  // (launch_poisson_box; the other launchers take the whole grid and leave
+  // these at 0).
+  int kin0 = 0, kin1 = 0, jin0 = 0, jin1 = 0, kout0 = 0, kout1 = 0, jout0 = 0, jout1 = 0;
 };
 
 // Row pitch of the half spectrum in complex elements: column groups of 8 start
@@ -437,7 +443,6 @@ struct PoissonSlots {
   void* v[ENS_MAX_SLOTS];
   void* w[ENS_MAX_SLOTS];
   double2* spec[ENS_MAX_SLOTS];
-  double* p[ENS_MAX_SLOTS];
 };
 template <class T>
 hipError_t launch_poisson_x_forward(const Dims& d, const T* u, const T* v, const T* w,
@@ -449,61 +454,63 @@ hipError_t launch_poisson_y(const Dims& d, const SpecBufs& sb, int dir, hipStrea
                             const PoissonSlots* bs = nullptr, int nslots = 1);
 hipError_t launch_poisson_spectral(const Dims& d, const SpecBufs& sb, hipStream_t s,
                                    const PoissonSlots* bs = nullptr, int nslots = 1);
-hipError_t launch_poisson_x_inverse(const Dims& d, const SpecBufs& sb, hipStream_t s,
-                                    const PoissonSlots* bs = nullptr, int nslots = 1);
-template <class T>
-hipError_t launch_project(const Dims& d, T* u, T* v, T* w, double scale, const Spacing& sp,
-                          const double* p, hipStream_t s, const PoissonSlots* bs = nullptr,
-                          int nslots = 1, const T* mask = nullptr);
+hipError_t launch_poisson_x_inverse(const Dims& d, const SpecBufs& sb, hipStream_t s);
+// sb.p = L^-1 src of a dense FP64 field: passes 0 (x) to 4 (x inverse),
+// restricted to the ranges of sb (src is zero outside its in-ranges, sb.p
+// written in its out-ranges)
+hipError_t launch_poisson_box(const Dims& d, const double* src, const SpecBufs& sb, int pass,
+                              hipStream_t s);
 // The inverse x pass fused with the projection: u, v, w -= scale grad p with
 // p taken from sb.spec on the fly; sb.p is not written (launch
 // launch_poisson_x_inverse on the same spectrum for it).
 template <class T>
 hipError_t launch_poisson_x_inverse_project(const Dims& d, const SpecBufs& sb, T* u, T* v, T* w,
                                             double scale, const Spacing& sp, hipStream_t s,
-                                            const PoissonSlots* bs = nullptr, int nslots = 1);
-// The forward x transform of a dense FP64 (nz, ny, nx) field into sb.spec
-// (the first pass of the FFT solve applied to a given right-hand side).
-hipError_t launch_poisson_x_forward_dense(const Dims& d, const double* src, const SpecBufs& sb,
-                                          hipStream_t s);
-// The inverse x pass that also leaves partial sums of rdot . p (one per
-// workgroup, *npart of them, at most part_cap) in part.
-hipError_t launch_poisson_x_inverse_dot(const Dims& d, const SpecBufs& sb, const double* rdot,
-                                        double* part, int part_cap, int* npart, hipStream_t s);
-
+                                            const PoissonSlots* bs = nullptr, int nslots = 1,
+                                            const T* mask = nullptr);
 // ---- Immersed boundaries (immersed.hip): preconditioned conjugate gradients
-// on dense FP64 (nz, ny, nx) vectors.  Reducing kernels run IB_NPART
-// workgroups and leave one partial sum each in part; launch_ib_finalize adds
-// them in a fixed order and updates the scalars in scal (indices CG_*).
-constexpr int IB_NPART = 4096;
-constexpr int IB_PART_CAP = 16384;   // room for the partials of the fused inverse pass
-enum { CG_RZ = 0, CG_ALPHA, CG_BETA, CG_BNORM2, CG_RNORM2, CG_IT, CG_DONE, CG_MEAN, CG_NSCAL };
-enum { CG_FIN_BNORM = 0, CG_FIN_RZ0, CG_FIN_ALPHA, CG_FIN_RES, CG_FIN_BETA, CG_FIN_MEAN };
+// on the fluid cells next to immersed ones (the list idx; off it the residual
+// of the box solve is zero).  Reducing kernels leave one partial sum per
+// workgroup in part; the last workgroup to finish adds them in a fixed order
+// and updates the scalars in scal (indices CG_*).
+constexpr int IB_NPART = 4096;       // workgroups of the right-hand side's kernel
+constexpr int IB_LPART = 1024;       // most workgroups of the list kernels
+constexpr int IB_PART_CAP = 3 * IB_LPART;   // partial sums (at most three per workgroup)
+enum { CG_RZ = 0, CG_ALPHA, CG_BETA, CG_BNORM2, CG_RNORM2, CG_IT, CG_DONE, CG_MEAN, CG_QAQ, CG_NSCAL };
 struct CgBufs {
-  double* x;     // iterate (the pressure)
-  double* r;     // residual
-  double* q;     // search direction
-  double* aq;    // A q
-  double* part;  // IB_NPART partial sums
-  double* scal;  // CG_NSCAL scalars
+  double* b;         // dense: right-hand side; on the list, the steps taken
+  double* r;         // dense: residual, zero off the list
+  const int* idx;    // the list: dense indices, ascending
+  double* s;         // compact, per list entry: q = P L^-1 s (search direction)
+  double* q;
+  double* aq;        // A q
+  double* az;        // A z of this iteration
+  double* part;      // IB_PART_CAP
+  double* bpart;     // IB_NPART partial sums of b^2
+  double* scal;      // CG_NSCAL scalars
+  unsigned* ticket;  // workgroups done (zero between kernels)
+  int n;             // list entries
 };
 // Per-cell geometry byte (dense, x fastest): the cell is fluid, and which of
 // its faces are open (both neighbours fluid; walls closed).
 enum { IB_XM = 1, IB_XP = 2, IB_YM = 4, IB_YP = 8, IB_ZM = 16, IB_ZP = 32, IB_FLUID = 64 };
+// b = div(u~) / dt_eff in fluid cells, 0 in immersed ones, and |b|^2
 template <class T>
 hipError_t launch_ib_rhs(const Dims& d, const T* u, const T* v, const T* w,
                          const uint8_t* bits, double inv_dt, double rdx, double rdy, double rdz,
                          const CgBufs& cg, hipStream_t s);
-hipError_t launch_ib_apply(const Dims& d, const uint8_t* bits, double rdx2, double rdy2,
-                           double rdz2, const CgBufs& cg, hipStream_t s);
-hipError_t launch_ib_update(const Dims& d, const CgBufs& cg, hipStream_t s);
-hipError_t launch_ib_dir(const Dims& d, const uint8_t* bits, const CgBufs& cg, const double* z,
-                         hipStream_t s);
-hipError_t launch_ib_gauge(const Dims& d, const uint8_t* bits, const CgBufs& cg, double nfluid,
+// After z = L^-1 b: the first iterate P z; r = b - A P z on the list, |r|^2
+// and the stopping test.
+hipError_t launch_ib_start(const Dims& d, const uint8_t* bits, double rdx2, double rdy2,
+                           double rdz2, const CgBufs& cg, const double* z, double tol2, int maxiter,
                            hipStream_t s);
-hipError_t launch_ib_finalize(const CgBufs& cg, int what, double tol2, int maxiter,
-                              hipStream_t s, int npart = IB_NPART);
-hipError_t launch_ib_xfinal(const Dims& d, const CgBufs& cg, hipStream_t s);
+// One iteration after z = L^-1 r: A z, the scalars, and the updates.
+hipError_t launch_ib_iterate(const Dims& d, const uint8_t* bits, double rdx2, double rdy2,
+                             double rdz2, const CgBufs& cg, const double* z, double tol2,
+                             int maxiter, hipStream_t s);
+// p -= its mean over the fluid cells there; p = 0 in immersed cells.
+hipError_t launch_ib_gauge(const Dims& d, const uint8_t* bits, const CgBufs& cg, double* p,
+                           double nfluid, hipStream_t s);
 template <class T>
 hipError_t launch_ib_mask_velocity(const Dims& d, T* u, T* v, T* w, const T* mask,
                                    hipStream_t s);

@@ -279,9 +279,9 @@ __global__ void __launch_bounds__(NT) fwd_x_kernel(Dims d, const T* __restrict__
   __shared__ double2 buf[LP * N];
   __shared__ double2 tws[N];
   stage_twiddles<N>(tws, sb.twx);
-  const int k = blockIdx.y;
+  const int k = blockIdx.y + sb.kin0;
   const int npairs = d.ny / 2;
-  const int pair0 = blockIdx.x * LP;
+  const int pair0 = blockIdx.x * LP + sb.jin0 / 2;
   // A thread takes four consecutive points of both lines of a pair (16-byte
   // row loads; rows carry no alignment, the loads need none) and stores
   // the packed values (line 2pr, line 2pr+1) at buf[l N + i .. + 3].
@@ -354,8 +354,10 @@ __global__ void __launch_bounds__(NT) fwd_x_kernel(Dims d, const T* __restrict__
 
 // ---------------------------------------------------------------------------
 // Passes 2 and 4: complex FFT along y for W consecutive kx columns.
+// BOX: restricted to the ranges of sb (forward: rows outside [jin0, jin1) are
+// zero and were not written; inverse: only rows [jout0, jout1) are kept).
 // ---------------------------------------------------------------------------
-template <int N, int DIR>
+template <int N, int DIR, bool BOX>
 __global__ void __launch_bounds__(NT) y_kernel(Dims d, SpecBufs sb,
                                                const PoissonSlots* __restrict__ bs) {
   if (sb.stop && *glb(sb.stop) != 0.0) return;
@@ -366,7 +368,8 @@ __global__ void __launch_bounds__(NT) y_kernel(Dims d, SpecBufs sb,
   stage_twiddles<N>(tws, sb.twy);
   // the forward pass takes the planes in the reverse of the order the x pass
   // wrote them, so it starts on the ones most likely still in the caches
-  const int k = DIR < 0 ? (int)gridDim.y - 1 - (int)blockIdx.y : (int)blockIdx.y;
+  int k = DIR < 0 ? (int)gridDim.y - 1 - (int)blockIdx.y : (int)blockIdx.y;
+  if (BOX) k += DIR < 0 ? sb.kin0 : sb.kout0;
   const int kx0 = blockIdx.x * W;
   const int nxh = sb.nxh, nxp = sb.nxp;
   double2* plane = sb.spec + (long)k * d.ny * nxp + kx0;
@@ -374,10 +377,12 @@ __global__ void __launch_bounds__(NT) y_kernel(Dims d, SpecBufs sb,
   fft_lines_io<N, W, NT, DIR, 8>(
       buf, tws,
       [&](int c, int y) {
-        return c < ncol ? ld2(plane, (long)y * nxp + c) : make_double2(0.0, 0.0);
+        const bool in = c < ncol && (!BOX || DIR > 0 || (y >= sb.jin0 && y < sb.jin1));
+        return in ? ld2(plane, (long)y * nxp + c) : make_double2(0.0, 0.0);
       },
       [&](int c, int y, double2 x) {
-        if (c < ncol) st2(plane, (long)y * nxp + c, x);
+        if (c < ncol && (!BOX || DIR < 0 || (y >= sb.jout0 && y < sb.jout1)))
+          st2(plane, (long)y * nxp + c, x);
       });
 }
 
@@ -454,8 +459,9 @@ struct ZPairs {
   }
 };
 
-// Four waves per SIMD: four blocks per CU, as many as the LDS holds.
-template <int N, bool BOUNDED>
+// Four waves per SIMD: four blocks per CU, as many as the LDS holds.  BOX: only
+// levels [kin0, kin1) hold input, only [kout0, kout1) are stored.
+template <int N, bool BOUNDED, bool BOX>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4)))
     z_kernel(Dims d, SpecBufs sb, double norm, const PoissonSlots* __restrict__ bs) {
   if (sb.stop && *glb(sb.stop) != 0.0) return;
@@ -476,12 +482,15 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4)))
   // reordering) on walls, level n when periodic
   auto level = [](int n) { return BOUNDED ? makhoul_src(n, N) : n; };
   fft_lines_from<N, W, NT, -1, 8>(buf, tws, [&](int c, int n) {
-    return c < ncol ? ld2(col, (long)level(n) * zs + c) : make_double2(0.0, 0.0);
+    const int l = level(n);
+    const bool in = c < ncol && (!BOX || (l >= sb.kin0 && l < sb.kin1));
+    return in ? ld2(col, (long)l * zs + c) : make_double2(0.0, 0.0);
   });
   pairs.apply(buf, sb.dctz);
   __syncthreads();
   fft_lines_to<N, 1, W, NT, 1, 8>(buf, tws, [&](int c, int n, double2 x) {
-    if (c < ncol) st2(col, (long)level(n) * zs + c, x);
+    const int l = level(n);
+    if (c < ncol && (!BOX || (l >= sb.kout0 && l < sb.kout1))) st2(col, (long)l * zs + c, x);
   });
 }
 
@@ -638,28 +647,17 @@ __global__ void __launch_bounds__(NT) z_tridiag_kernel(Dims d, SpecBufs sb, doub
 // ---------------------------------------------------------------------------
 // Pass 5: complex-to-real inverse FFT along x for line pairs -> p.
 // ---------------------------------------------------------------------------
-// rdot != null: also the partial sum of rdot . p over the values this
-// workgroup writes, into part[blockIdx.y * gridDim.x + blockIdx.x] (the r . z
-// of the immersed-boundary iteration).
 template <int N>
-__global__ void __launch_bounds__(NT) inv_x_kernel(Dims d, SpecBufs sb,
-                                                   const PoissonSlots* __restrict__ bs,
-                                                   const double* __restrict__ rdot,
-                                                   double* __restrict__ part) {
+__global__ void __launch_bounds__(NT) inv_x_kernel(Dims d, SpecBufs sb) {
   if (sb.stop && *glb(sb.stop) != 0.0) return;
-  if (bs) {
-    sb.spec = bs->spec[blockIdx.z];
-    sb.p = bs->p[blockIdx.z];
-  }
   const auto pout = glb(sb.p);
-  const auto grdot = glb(rdot);
   constexpr int LP = XCfg<N>::LP;
   __shared__ double2 buf[LP * N];
   __shared__ double2 tws[N];
   stage_twiddles<N>(tws, sb.twx);
-  const int k = blockIdx.y;
+  const int k = blockIdx.y + sb.kout0;
   const int npairs = d.ny / 2;
-  const int pair0 = blockIdx.x * LP;
+  const int pair0 = blockIdx.x * LP + sb.jout0 / 2;
   constexpr int LOADS = (LP * N + NT - 1) / NT;
 #pragma unroll
   for (int q = 0; q < LOADS; ++q) {
@@ -680,7 +678,6 @@ __global__ void __launch_bounds__(NT) inv_x_kernel(Dims d, SpecBufs sb,
   }
   __syncthreads();
   fft_lines<N, 1, LP, NT, 1, false>(buf, N, 1, tws);
-  double acc = 0.0;
   for (int t = threadIdx.x; t < LP * N; t += NT) {
     const int l = t / N, i = t % N;
     const int pr = pair0 + l;
@@ -688,106 +685,6 @@ __global__ void __launch_bounds__(NT) inv_x_kernel(Dims d, SpecBufs sb,
     const long base = ((long)k * d.ny + 2 * pr) * d.nx + i;
     pout[base] = buf[t].x;
     pout[base + d.nx] = buf[t].y;
-    if (rdot) acc += grdot[base] * buf[t].x + grdot[base + d.nx] * buf[t].y;
-  }
-  if (rdot) {
-    __shared__ double red[NT];
-    red[threadIdx.x] = acc;
-    __syncthreads();
-#pragma unroll
-    for (int h = NT / 2; h > 0; h >>= 1) {
-      if ((int)threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
-      __syncthreads();
-    }
-    if (threadIdx.x == 0) glb(part)[blockIdx.y * gridDim.x + blockIdx.x] = red[0];
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Projection u -= scale grad p at interior faces (wall faces of w untouched).
-// A workgroup covers 64 x 4 columns and marches up PJ_KC planes, keeping the
-// pressure of the plane below in a register, so p is fetched once per cell
-// (plus one plane per chunk).
-// ---------------------------------------------------------------------------
-constexpr int PJ_X = 64, PJ_Y = 4, PJ_KC = 8;
-
-// mask != null (immersed boundary): velocities on closed faces are set to 0.
-template <class T>
-__global__ void __launch_bounds__(PJ_X * PJ_Y) project_kernel(
-    Dims d, T* __restrict__ u, T* __restrict__ v, T* __restrict__ w, double scale, double rdx,
-    double rdy, const double* __restrict__ rdzf, const double* __restrict__ p,
-    const PoissonSlots* __restrict__ bs, const T* __restrict__ mask) {
-  if (bs) {
-    const int z = blockIdx.z;
-    u = (T*)bs->u[z];
-    v = (T*)bs->v[z];
-    w = (T*)bs->w[z];
-    p = bs->p[z];
-  }
-  // Workgroups are dealt round-robin to the 8 XCDs; renumber them so that
-  // each XCD takes a contiguous run of tiles (x fastest, then y, then the z
-  // chunk), and the cache lines shared by neighbouring tiles stay in one L2.
-  const int nbx = (d.nx + PJ_X - 1) / PJ_X;
-  const int ntile = (int)(gridDim.x * gridDim.y);
-  int lin = (int)(blockIdx.x + blockIdx.y * gridDim.x);
-  if (ntile % 8 == 0) lin = (lin % 8) * (ntile / 8) + lin / 8;
-  const int txy = lin % (int)gridDim.x;
-  const int i = (txy % nbx) * PJ_X + (int)(threadIdx.x % PJ_X);
-  const int j = (txy / nbx) * PJ_Y + (int)(threadIdx.x / PJ_X);
-  if (i >= d.nx || j >= d.ny) return;
-  const int k0 = (lin / (int)gridDim.x) * PJ_KC;
-  const int k1 = min(k0 + PJ_KC, d.nz);
-  const long plane = (long)d.nx * d.ny;
-  const auto pc = glb(p) + (long)j * d.nx + i;
-  const auto gu = glb(u), gv = glb(v), gw = glb(w);
-  const auto gmask = glb(mask);
-  const long oxm = ((i == 0) ? d.nx - 1 : i - 1) - i;
-  const long oym = (long)(((j == 0) ? d.ny - 1 : j - 1) - j) * d.nx;
-  // pressure below the first plane of the chunk (periodic wrap in z)
-  double pb = 0.0;
-  if (k0 > 0) pb = pc[(long)(k0 - 1) * plane];
-  else if (!d.zb) pb = pc[(long)(d.nz - 1) * plane];
-  // planes in batches of PJ_B: all loads of a batch are issued before its
-  // stores (the stores may alias later loads of the same field)
-  constexpr int PJ_B = 4;
-  for (int kb = k0; kb < k1; kb += PJ_B) {
-    double p0[PJ_B], pxm[PJ_B], pym[PJ_B];
-    T uu[PJ_B], vv[PJ_B], ww[PJ_B];
-#pragma unroll
-    for (int q = 0; q < PJ_B; ++q) {
-      if (kb + q < k1) {
-        const long t = (long)(kb + q) * plane;
-        p0[q] = pc[t];
-        pxm[q] = pc[t + oxm];
-        pym[q] = pc[t + oym];
-        const long c = pidx(d, i, j, kb + q);
-        uu[q] = gu[c];
-        vv[q] = gv[c];
-        ww[q] = gw[c];
-      }
-    }
-#pragma unroll
-    for (int q = 0; q < PJ_B; ++q) {
-      const int k = kb + q;
-      if (k < k1) {
-        T un = (T)((double)uu[q] - scale * (p0[q] - pxm[q]) * rdx);
-        T vn = (T)((double)vv[q] - scale * (p0[q] - pym[q]) * rdy);
-        T wn = ww[q];
-        if (!d.zb || k > 0) wn = (T)((double)wn - scale * (p0[q] - pb) * rdzf[k]);
-        pb = p0[q];
-        if (mask) {
-          const long c = pidx(d, i, j, k);
-          const T m0 = gmask[c];
-          un = un * (m0 * gmask[c - 1]);
-          vn = vn * (m0 * gmask[c - d.sy]);
-          if (!d.zb || k > 0) wn = wn * (m0 * gmask[c - d.sz]);
-        }
-        // the final velocities, with their halo images
-        store_with_images(u, d, i, j, k, un, false);
-        store_with_images(v, d, i, j, k, vn, false);
-        store_with_images(w, d, i, j, k, wn, true);
-      }
-    }
   }
 }
 
@@ -820,11 +717,12 @@ template <int N> struct PXCfg {
   static constexpr int LV = N == 96 ? 2 : 1;
 };
 
-template <class T, int N>
+// MASK (immersed boundary): velocities on closed faces are set to 0.
+template <class T, int N, bool MASK>
 __global__ void __launch_bounds__(NT) inv_x_project_kernel(
     Dims d, SpecBufs sb, T* __restrict__ u, T* __restrict__ v, T* __restrict__ w, double scale,
     double rdx, double rdy, const double* __restrict__ rdzf, int rb, int nblk, int nch,
-    const PoissonSlots* __restrict__ bs) {
+    const PoissonSlots* __restrict__ bs, const T* __restrict__ mask) {
   // Workgroups are dealt round-robin to the 8 XCDs: XCD x takes workgroups
   // x, x + 8, ...; renumber them so that each XCD works on a contiguous run
   // (the chunks of a column, then the next column), whose shared rows and
@@ -946,9 +844,16 @@ __global__ void __launch_bounds__(NT) inv_x_project_kernel(
             const double pxm = pat(lv, r, i == 0 ? N - 1 : i - 1);
             const double pym = pat(lv, r - 1, i);
             const double pzm = lv == 0 ? pb[q] : pat(lv - 1, r, i);
-            const T un = (T)((double)uu[lv][q] - scale * (p0 - pxm) * rdx);
-            const T vn = (T)((double)vv[lv][q] - scale * (p0 - pym) * rdy);
-            const T wn = wk ? (T)((double)ww[lv][q] - scale * (p0 - pzm) * rz) : ww[lv][q];
+            T un = (T)((double)uu[lv][q] - scale * (p0 - pxm) * rdx);
+            T vn = (T)((double)vv[lv][q] - scale * (p0 - pym) * rdy);
+            T wn = wk ? (T)((double)ww[lv][q] - scale * (p0 - pzm) * rz) : ww[lv][q];
+            if (MASK) {
+              const auto gm = glb(mask) + pidx(d, i, j, k);
+              const T m0 = gm[0];
+              un = un * (m0 * gm[-1]);
+              vn = vn * (m0 * gm[-d.sy]);
+              if (wk) wn = wn * (m0 * gm[-d.sz]);
+            }
             store_with_images(u, d, i, j, k, un, false);
             store_with_images(v, d, i, j, k, vn, false);
             store_with_images(w, d, i, j, k, wn, true);
@@ -1002,30 +907,15 @@ hipError_t launch_poisson_x_forward(const Dims& d, const T* u, const T* v, const
   return hipGetLastError();
 }
 
-hipError_t launch_poisson_x_forward_dense(const Dims& d, const double* src, const SpecBufs& sb,
-                                          hipStream_t s) {
-#define OC_LAUNCH_FXD(N)                                                                   \
-  {                                                                                        \
-    dim3 grid((d.ny / 2 + XCfg<N>::LP - 1) / XCfg<N>::LP, d.nz, 1);                       \
-    hipLaunchKernelGGL((fwd_x_kernel<double, N>), grid, dim3(NT), 0, s, d,                \
-                       (const double*)nullptr, (const double*)nullptr,                     \
-                       (const double*)nullptr, 0.0, 0.0, 0.0, (const double*)nullptr, sb,  \
-                       (const PoissonSlots*)nullptr, src);                                 \
-  }
-  OC_FFT_DISPATCH(d.nx, OC_LAUNCH_FXD)
-#undef OC_LAUNCH_FXD
-  return hipGetLastError();
-}
-
 hipError_t launch_poisson_y(const Dims& d, const SpecBufs& sb, int dir, hipStream_t s,
                             const PoissonSlots* bs, int nslots) {
 #define OC_LAUNCH_Y(N)                                                                     \
   {                                                                                        \
     dim3 grid((sb.nxh + YZCfg<N>::W - 1) / YZCfg<N>::W, d.nz, nslots);                    \
     if (dir < 0)                                                                           \
-      hipLaunchKernelGGL((y_kernel<N, -1>), grid, dim3(NT), 0, s, d, sb, bs);             \
+      hipLaunchKernelGGL((y_kernel<N, -1, false>), grid, dim3(NT), 0, s, d, sb, bs);             \
     else                                                                                   \
-      hipLaunchKernelGGL((y_kernel<N, 1>), grid, dim3(NT), 0, s, d, sb, bs);              \
+      hipLaunchKernelGGL((y_kernel<N, 1, false>), grid, dim3(NT), 0, s, d, sb, bs);              \
   }
   OC_FFT_DISPATCH(d.ny, OC_LAUNCH_Y)
 #undef OC_LAUNCH_Y
@@ -1039,9 +929,9 @@ hipError_t launch_poisson_spectral(const Dims& d, const SpecBufs& sb, hipStream_
   {                                                                                        \
     dim3 grid((sb.nxh + YZCfg<N>::W - 1) / YZCfg<N>::W, d.ny, nslots);                    \
     if (d.zb)                                                                              \
-      hipLaunchKernelGGL((z_kernel<N, true>), grid, dim3(NT), 0, s, d, sb, norm, bs);     \
+      hipLaunchKernelGGL((z_kernel<N, true, false>), grid, dim3(NT), 0, s, d, sb, norm, bs);     \
     else                                                                                   \
-      hipLaunchKernelGGL((z_kernel<N, false>), grid, dim3(NT), 0, s, d, sb, norm, bs);    \
+      hipLaunchKernelGGL((z_kernel<N, false, false>), grid, dim3(NT), 0, s, d, sb, norm, bs);    \
   }
   OC_FFT_DISPATCH(d.nz, OC_LAUNCH_Z)
 #undef OC_LAUNCH_Z
@@ -1058,16 +948,73 @@ hipError_t launch_poisson_tridiag(const Dims& d, const SpecBufs& sb, const doubl
   return hipGetLastError();
 }
 
-hipError_t launch_poisson_x_inverse(const Dims& d, const SpecBufs& sb, hipStream_t s,
-                                    const PoissonSlots* bs, int nslots) {
+hipError_t launch_poisson_x_inverse(const Dims& d, const SpecBufs& sb, hipStream_t s) {
 #define OC_LAUNCH_XI(N)                                                                    \
   {                                                                                        \
-    dim3 grid((d.ny / 2 + XCfg<N>::LP - 1) / XCfg<N>::LP, d.nz, nslots);                  \
-    hipLaunchKernelGGL((inv_x_kernel<N>), grid, dim3(NT), 0, s, d, sb, bs,                \
-                       (const double*)nullptr, (double*)nullptr);                          \
+    dim3 grid((d.ny / 2 + XCfg<N>::LP - 1) / XCfg<N>::LP, d.nz);                          \
+    hipLaunchKernelGGL((inv_x_kernel<N>), grid, dim3(NT), 0, s, d, sb);                   \
   }
   OC_FFT_DISPATCH(d.nx, OC_LAUNCH_XI)
 #undef OC_LAUNCH_XI
+  return hipGetLastError();
+}
+
+// Row pairs of [j0, j1) (even bounds) in groups of lp.
+static unsigned pair_groups(int j0, int j1, int lp) {
+  return (unsigned)(((j1 - j0) / 2 + lp - 1) / lp);
+}
+
+hipError_t launch_poisson_box(const Dims& d, const double* src, const SpecBufs& sb, int pass,
+                              hipStream_t s) {
+  const double norm = 1.0 / ((double)d.nx * d.ny * d.nz);
+  const unsigned nki = sb.kin1 - sb.kin0, nko = sb.kout1 - sb.kout0;
+  switch (pass) {
+  case 0:
+#define OC_LAUNCH_FXD(N)                                                                   \
+  hipLaunchKernelGGL((fwd_x_kernel<double, N>),                                            \
+                     dim3(pair_groups(sb.jin0, sb.jin1, XCfg<N>::LP), nki), dim3(NT), 0, s, d, \
+                     (const double*)nullptr, (const double*)nullptr, (const double*)nullptr, \
+                     0.0, 0.0, 0.0, (const double*)nullptr, sb, (const PoissonSlots*)nullptr, src);
+  OC_FFT_DISPATCH(d.nx, OC_LAUNCH_FXD)
+#undef OC_LAUNCH_FXD
+    break;
+  case 1:
+#define OC_LAUNCH_Y(N)                                                                     \
+  hipLaunchKernelGGL((y_kernel<N, -1, true>), dim3((sb.nxh + YZCfg<N>::W - 1) / YZCfg<N>::W, nki), \
+                     dim3(NT), 0, s, d, sb, (const PoissonSlots*)nullptr);
+  OC_FFT_DISPATCH(d.ny, OC_LAUNCH_Y)
+#undef OC_LAUNCH_Y
+    break;
+  case 2:
+#define OC_LAUNCH_Z(N)                                                                     \
+  {                                                                                        \
+    dim3 grid((sb.nxh + YZCfg<N>::W - 1) / YZCfg<N>::W, d.ny);                            \
+    if (d.zb)                                                                              \
+      hipLaunchKernelGGL((z_kernel<N, true, true>), grid, dim3(NT), 0, s, d, sb, norm,    \
+                         (const PoissonSlots*)nullptr);                                    \
+    else                                                                                   \
+      hipLaunchKernelGGL((z_kernel<N, false, true>), grid, dim3(NT), 0, s, d, sb, norm,   \
+                         (const PoissonSlots*)nullptr);                                    \
+  }
+  OC_FFT_DISPATCH(d.nz, OC_LAUNCH_Z)
+#undef OC_LAUNCH_Z
+    break;
+  case 3:
+#define OC_LAUNCH_Y(N)                                                                     \
+  hipLaunchKernelGGL((y_kernel<N, 1, true>), dim3((sb.nxh + YZCfg<N>::W - 1) / YZCfg<N>::W, nko), \
+                     dim3(NT), 0, s, d, sb, (const PoissonSlots*)nullptr);
+  OC_FFT_DISPATCH(d.ny, OC_LAUNCH_Y)
+#undef OC_LAUNCH_Y
+    break;
+  case 4:
+#define OC_LAUNCH_XI(N)                                                                    \
+  hipLaunchKernelGGL((inv_x_kernel<N>), dim3(pair_groups(sb.jout0, sb.jout1, XCfg<N>::LP), nko), \
+                     dim3(NT), 0, s, d, sb);
+  OC_FFT_DISPATCH(d.nx, OC_LAUNCH_XI)
+#undef OC_LAUNCH_XI
+    break;
+  default: return hipErrorInvalidValue;
+  }
   return hipGetLastError();
 }
 
@@ -1101,44 +1048,20 @@ static int resident_slots(const void* kernel) {
 template <class T>
 hipError_t launch_poisson_x_inverse_project(const Dims& d, const SpecBufs& sb, T* u, T* v, T* w,
                                             double scale, const Spacing& sp, hipStream_t s,
-                                            const PoissonSlots* bs, int nslots) {
+                                            const PoissonSlots* bs, int nslots, const T* mask) {
 #define OC_LAUNCH_XIP(N)                                                                   \
   {                                                                                        \
     constexpr int RB = 2 * PXCfg<N>::L - 1;                                                \
     const int nblk = (d.ny + RB - 1) / RB, rb = (d.ny + nblk - 1) / nblk;                  \
-    static const int slots = resident_slots((const void*)inv_x_project_kernel<T, N>);     \
-    const int ncol = nblk * nslots, nch = px_chunks(d.nz, ncol, slots);                    \
-    hipLaunchKernelGGL((inv_x_project_kernel<T, N>), dim3(ncol * nch), dim3(NT), 0, s, d, sb, \
-                       u, v, w, scale, sp.rdx, sp.rdy, sp.rdzf, rb, nblk, nch, bs);        \
+    const auto kernel = mask ? inv_x_project_kernel<T, N, true> : inv_x_project_kernel<T, N, false>; \
+    static const int slots[2] = {resident_slots((const void*)inv_x_project_kernel<T, N, false>), \
+                                 resident_slots((const void*)inv_x_project_kernel<T, N, true>)}; \
+    const int ncol = nblk * nslots, nch = px_chunks(d.nz, ncol, slots[mask ? 1 : 0]);      \
+    hipLaunchKernelGGL(kernel, dim3(ncol * nch), dim3(NT), 0, s, d, sb, u, v, w, scale, sp.rdx, \
+                       sp.rdy, sp.rdzf, rb, nblk, nch, bs, mask);                          \
   }
   OC_FFT_DISPATCH(d.nx, OC_LAUNCH_XIP)
 #undef OC_LAUNCH_XIP
-  return hipGetLastError();
-}
-
-hipError_t launch_poisson_x_inverse_dot(const Dims& d, const SpecBufs& sb, const double* rdot,
-                                        double* part, int part_cap, int* npart, hipStream_t s) {
-#define OC_LAUNCH_XID(N)                                                                   \
-  {                                                                                        \
-    dim3 grid((d.ny / 2 + XCfg<N>::LP - 1) / XCfg<N>::LP, d.nz, 1);                       \
-    *npart = (int)(grid.x * grid.y);                                                       \
-    if (*npart > part_cap) return hipErrorInvalidValue;                                    \
-    hipLaunchKernelGGL((inv_x_kernel<N>), grid, dim3(NT), 0, s, d, sb,                    \
-                       (const PoissonSlots*)nullptr, rdot, part);                          \
-  }
-  OC_FFT_DISPATCH(d.nx, OC_LAUNCH_XID)
-#undef OC_LAUNCH_XID
-  return hipGetLastError();
-}
-
-template <class T>
-hipError_t launch_project(const Dims& d, T* u, T* v, T* w, double scale, const Spacing& sp,
-                          const double* p, hipStream_t s, const PoissonSlots* bs, int nslots,
-                          const T* mask) {
-  const unsigned nb = (unsigned)(((d.nx + PJ_X - 1) / PJ_X) * ((d.ny + PJ_Y - 1) / PJ_Y));
-  hipLaunchKernelGGL(project_kernel<T>, dim3(nb, (d.nz + PJ_KC - 1) / PJ_KC, nslots),
-                     dim3(PJ_X * PJ_Y), 0, s, d, u, v, w, scale, sp.rdx, sp.rdy, sp.rdzf, p, bs,
-                     mask);
   return hipGetLastError();
 }
 
@@ -1153,16 +1076,11 @@ template hipError_t launch_poisson_x_forward<double>(const Dims&, const double*,
 template hipError_t launch_poisson_x_inverse_project<float>(const Dims&, const SpecBufs&, float*,
                                                             float*, float*, double,
                                                             const Spacing&, hipStream_t,
-                                                            const PoissonSlots*, int);
+                                                            const PoissonSlots*, int, const float*);
 template hipError_t launch_poisson_x_inverse_project<double>(const Dims&, const SpecBufs&,
                                                              double*, double*, double*, double,
                                                              const Spacing&, hipStream_t,
-                                                             const PoissonSlots*, int);
-template hipError_t launch_project<float>(const Dims&, float*, float*, float*, double,
-                                          const Spacing&, const double*, hipStream_t,
-                                          const PoissonSlots*, int, const float*);
-template hipError_t launch_project<double>(const Dims&, double*, double*, double*, double,
-                                           const Spacing&, const double*, hipStream_t,
-                                           const PoissonSlots*, int, const double*);
+                                                             const PoissonSlots*, int,
+                                                             const double*);
 
 }  // namespace oc

@@ -176,6 +176,57 @@ def test_immersed_restrictions(gpu_lib):
         plain.pressure_stats()
 
 
+def _scatter(ph, frac, seed):
+    """Immersed cells scattered over the box, also on its edges: lists of
+    boundary cells that reach every row and level and wrap around."""
+    solid = np.random.default_rng(seed).random((ph.nz, ph.ny, ph.nx)) < frac
+    solid[0, 0, :3] = solid[-1, -1, -2:] = solid[2, 0, 5] = solid[3, -1, 5] = True
+    return solid
+
+
+@pytest.mark.parametrize("bounded,n,frac", [(True, (32, 32, 32), 0.03), (False, (16, 16, 16), 0.02),
+                                            (True, (8, 8, 8), 0.01)])
+def test_immersed_pressure_scattered_cells(gpu_lib, bounded, n, frac):
+    """Ranges that cover the whole grid, periodic z, and a list of more than
+    3072 cells (5 thousand at 32^3: two launches per iteration)."""
+    ph = _conv(n) if bounded else inputs.periodic_box_physics(n[0])
+    ph = dataclasses.replace(ph, solid=_scatter(ph, frac, 5))
+    s = inputs.random_state(ph, seed=23, divergence_free=False)
+    m = gpu_lib.Model(ph, "fp64")
+    m.set_states(s)
+    m.pressure_solve(0.37)
+    it, res = m.pressure_stats()
+    assert 1 <= it <= 80 and res <= ph.cg_tol, (it, res)
+    w_in = s["w"].copy()
+    if bounded:
+        w_in[0] = w_in[-1] = 0.0
+    u, v, w, p = immersed.project_immersed(s["u"], s["v"], w_in, 0.37, ph)
+    assert rel_l2(m.get_pressure(), p) <= P_TOL
+    for name, ref in (("u", u), ("v", v), ("w", w)):
+        assert rel_l2(m.get_state(name), ref) <= TOL["fp64"], name
+
+
+def test_immersed_pressure_read_after_new_cells(gpu_lib):
+    """p of a solve belongs to the cells it was solved on, also when it is
+    read after oc_set_immersed; a state at rest takes no iteration."""
+    ph, _ = make_case("seamount_32x32x16")
+    s = inputs.random_state(ph, seed=21, divergence_free=False)
+    got = []
+    for new_cells in (False, True):
+        m = gpu_lib.Model(ph, "fp64")
+        m.set_states(s)
+        m.pressure_solve(0.37)
+        if new_cells:
+            m.set_immersed(np.zeros((ph.nz, ph.ny, ph.nx), dtype=bool))
+        got.append(m.get_pressure())
+    assert np.array_equal(got[0], got[1]) and np.all(got[0][ph.solid] == 0)
+    for name in ("u", "v", "w"):
+        m.set_state(name, np.zeros(m.shape_of(name)))
+    m.pressure_solve(0.37)
+    assert m.pressure_stats() == (0, 0.0)
+    assert np.all(m.get_pressure() == 0)
+
+
 N, B = 256, 24
 
 
