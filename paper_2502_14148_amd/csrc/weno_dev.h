@@ -62,26 +62,24 @@ __device__ inline T rec6(T m3, T m2, T m1, T p0, T p1, T p2, T vel, T eps) {
   if (SCHEME == SCHEME_LINEAR)
     return (T(2) * a - T(13) * b + T(47) * c + T(27) * d - T(3) * e) * T(1.0 / 60.0);
   const T d1 = b - a, d2 = c - b, d3 = d - c, d4 = e - d;
-  // ideal weights (1/10, 6/10, 3/10) folded into the candidate deviations
-  const T e0 = T(5.0 / 60.0) * d2 - T(2.0 / 60.0) * d1;
-  const T e1 = T(6.0 / 60.0) * d2 + T(12.0 / 60.0) * d3;
-  const T e2 = T(12.0 / 60.0) * d3 - T(3.0 / 60.0) * d4;
   const T t0 = d2 - d1, t1 = d3 - d2, t2 = d4 - d3;
-  const T u0 = T(3) * d2 - d1, u1 = d2 + d3, u2 = d4 - T(3) * d3;
-  const T e4 = T(4) * eps;
-  const T s0 = fmad(T(13.0 / 3.0) * t0, t0, fmad(u0, u0, e4));
-  const T s1 = fmad(T(13.0 / 3.0) * t1, t1, fmad(u1, u1, e4));
-  const T s2 = fmad(T(13.0 / 3.0) * t2, t2, fmad(u2, u2, e4));
+  const T q2 = fmad(d2, d2, eps), q3 = fmad(d3, d3, eps);
+  const T s0 = fmad(t0, fmad(T(4.0 / 3.0), t0, d2), q2);
+  const T s1 = fmad(t1, fmad(T(4.0 / 3.0), t1, d2), q2);
+  const T s2 = fmad(t2, fmad(T(4.0 / 3.0), t2, -d3), q3);
   const T tau = fabs(s0 - s2);
   const T s1s = s1 * s1;
-  const T g0 = tau * (s1 * rcp(s0));
-  const T g2 = tau * (s1 * rcp(s2));
+  const T g = tau * s1 * rcp(s0 * s2);
+  const T g0 = g * s2, g2 = g * s0;
   const T a0 = fmad(g0, g0, s1s);
-  const T a1 = fmad(tau, tau, s1s);
-  const T a2 = fmad(g2, g2, s1s);
-  const T num = a0 * e0 + a1 * e1 + a2 * e2;
-  const T den = T(0.1) * a0 + T(0.6) * a1 + T(0.3) * a2;
-  return fmad(num, rcp(den), c);
+  const T a1 = T(6) * fmad(tau, tau, s1s);
+  const T a2 = T(3) * fmad(g2, g2, s1s);
+  const T e0 = fmad(T(2.0 / 3.0), t0, d2);
+  const T e1 = fmad(T(2.0 / 3.0), t1, d2);
+  const T e2 = fmad(T(-1.0 / 3.0), t2, d3);
+  const T num = fmad(a0, e0, fmad(a1, e1, a2 * e2));
+  const T den = a0 + a1 + a2;
+  return fmad(T(0.5), num * rcp(den), c);
 }
 
 // Centred reconstruction of order 2R - 2 at the midpoint of a[R-2] and
