@@ -233,3 +233,33 @@ def test_profile_classes_restrict_event_recording(gpu_lib):
     for k in ("tendency", "fft_x_fwd", "fft_y_fwd", "z_solve", "fft_y_inv", "project"):
         assert p[k][1] == 3, (k, p[k])
     assert p["fft_x_inv"][1] == 0   # fused into the projection
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("dtype", ["float32", "float64"])
+def test_state_copies_at_element_aligned_addresses(gpu_lib, precision, dtype):
+    """Device buffers that start one element into an allocation, on the
+    shortest rows and on w's extra level: set and get return the values as
+    rounded by the types on the way, and touch nothing beside the buffer."""
+    import torch
+    ph = inputs.convection_physics((8, 8, 16), (16.0, 16.0, 16.0))
+    m = gpu_lib.Model(ph, precision)
+    dt = getattr(torch, dtype)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    for name in m.fields:
+        shape = m.shape_of(name)
+        n = int(np.prod(shape))
+        x = torch.randn(n, generator=g, device="cuda", dtype=torch.float64).to(torch.float32)
+        if name == "w":
+            x.reshape(shape)[0] = x.reshape(shape)[-1] = 0.0
+        buf = torch.full((n + 2,), 7.0, dtype=dt, device="cuda")
+        buf[1:-1] = x.to(dt)
+        m.set_state(name, buf[1:-1].reshape(shape))
+        out = torch.full((n + 2,), 7.0, dtype=dt, device="cuda")
+        m.get_state(name, out=out[1:-1].reshape(shape))
+        assert float(out[0]) == float(out[-1]) == 7.0
+        got = out[1:-1].double()
+        # FP32 models keep T and S as anomalies: one rounding of the anomaly
+        # (ulp of 35) and one of the value
+        tol = 8e-6 if precision == "fp32" and name in ("T", "S") else 0.0
+        assert float((got - x.double()).abs().max()) <= tol, name
