@@ -33,14 +33,13 @@
 // loads) land on the same XCD and its L2.
 #pragma once
 
+#include <algorithm>
+
 #include "oc_internal.h"
 #include "weno_dev.h"
 
 #ifndef OC_TEND_FLUXBAR
 #define OC_TEND_FLUXBAR 0
-#endif
-#ifndef OC_TEND_KC_DIV
-#define OC_TEND_KC_DIV 1024
 #endif
 #ifndef OC_TEND_WAVES
 #define OC_TEND_WAVES 4
@@ -597,6 +596,26 @@ __global__ void __launch_bounds__(TX * TY)
 
 }  // namespace tz
 
+// Levels per workgroup.  Grids whose columns come to fewer than 512
+// workgroups of four levels (two per CU) are bound by the latency of the
+// levels a workgroup walks one after the other (4 to 8 us each), so they take
+// the fewest levels, down to one, that stay within 512 workgroups: us at 4 ->
+// the chosen number of levels, 32^3 FP64 30.0 -> 12.2 (1), 64^3 FP32 24.3 ->
+// 15.1 (1), 64^3 FP64 33.1 -> 27.0 (2), 128x64x64 FP32 25.3 -> 23.2 (2), 64^3
+// WENO9 42.8 -> 31.4 (2).  With more columns the chip is full and a chunk's
+// first window and bottom fluxes count: about 1024 workgroups (128^3 FP32 65 us
+// with 512 to 1024, 69 with 2048, 77 with 4096), 2048 of the three-waves-
+// per-SIMD WENO7/9 kernels (128^3 WENO9 165 us, 176 with 1024).
+inline int levels_per_workgroup(int nz, long tiles, int R) {
+  if (tiles * ((nz + 3) / 4) < 512) {
+    int kc = 1;
+    while (tiles * ((nz + kc - 1) / kc) > 512) ++kc;
+    return kc;
+  }
+  const long kc = (long)nz * tiles / (R > 3 ? 2048 : 1024);
+  return (int)std::min<long>(std::min(64, nz), std::max<long>(4, kc));
+}
+
 // Launch the single-model kernel of radius R; scheme is tz::SCHEME_*.
 // Tracer counts above MAXNTR are not instantiated (refused).
 template <class T, int R, int WTX, int WTY, int MAXNTR = 4>
@@ -606,9 +625,7 @@ hipError_t launch_tendency_radius(const Dims& d, const FieldSet<T>& fs, const Te
   const int TX = wide ? WTX : 8, TY = wide ? WTY : 8;
   if (d.nx % TX || d.ny % TY || d.h < R) return hipErrorInvalidValue;
   const int nbx = d.nx / TX, nby = d.ny / TY;
-  int kc = (int)((long)d.nz * nbx * nby / OC_TEND_KC_DIV);
-  kc = kc < 4 ? 4 : (kc > 64 ? 64 : kc);
-  if (kc > d.nz) kc = d.nz;
+  const int kc = levels_per_workgroup(d.nz, (long)nbx * nby, R);
   const int nbz = (d.nz + kc - 1) / kc;
   const dim3 grid(nbx * nby * nbz);
   FieldSet<T> fb = fs;

@@ -263,3 +263,21 @@ def test_state_copies_at_element_aligned_addresses(gpu_lib, precision, dtype):
         # (ulp of 35) and one of the value
         tol = 8e-6 if precision == "fp32" and name in ("T", "S") else 0.0
         assert float((got - x.double()).abs().max()) <= tol, name
+
+
+@pytest.mark.parametrize("n,precision", [((64, 64, 32), "fp32"), ((64, 64, 96), "fp64"),
+                                         ((64, 32, 96), "fp64"), ((128, 64, 96), "fp32")])
+def test_tendency_parity_by_levels_per_workgroup(gpu_lib, n, precision):
+    """Grids whose workgroups walk one, three, two and three levels (the
+    latency-bound split), the last chunk shorter where the levels do not
+    divide evenly."""
+    ph = small_convection(*n)
+    s = _prep(inputs.random_state(ph, seed=31, vel=0.1, tracer_means=(ph.t_ref, ph.s_ref)), ph,
+              precision)
+    m = gpu_lib.Model(ph, precision)
+    m.set_states(s)
+    m.tendencies()
+    G = td.tendencies(timestep.make_state(s, ph), ph)
+    for name in m.fields:
+        err = rel_l2(m.get_tendency(name), G[name])
+        assert err <= TOL[precision], (n, name, err)
