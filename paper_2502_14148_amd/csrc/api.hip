@@ -86,7 +86,7 @@ Layout make_layout(const oc_grid_desc& g, const oc_model_desc& m) {
     // upper levels' partial column sums of GU, GV (V-like: ny + 1 rows)
     const uint64_t a2 = align256((uint64_t)(g.ny + 1) * g.nx * 8);
     for (int q = 0; q < 15; ++q) { L.baro[q] = off; off += a2; }
-    L.metric = off; off += align256((uint64_t)(5 * (g.ny + 1)) * 8);
+    L.metric = off; off += align256((uint64_t)(3 * (g.ny + 1)) * 8);
     L.hzeta = off; off += fb;
     L.hpx = off; off += fb;
     L.hpy = off; off += fb;
@@ -982,8 +982,9 @@ void fill_tables(const oc_grid_desc& g, std::vector<double>& twx, std::vector<do
   lam(lamz, g.nz, dz, g.topology_z == OC_BOUNDED);
 }
 
-// Thin-shell metrics of a lat-lon grid, packed as len_u | dx_u | len_v |
-// dy_v | area, each padded to ny + 1 entries.
+// Row factors of the barotropic substeps on a lat-lon grid (thin shell): the
+// length of y face j | 1 / area of row j | 1 / dx of row j, ny + 1 entries
+// each.
 void fill_latlon_metrics(const oc_grid_desc& g, std::vector<double>& met) {
   const double pi = 3.14159265358979323846;
   const int ny = g.ny;
@@ -991,21 +992,16 @@ void fill_latlon_metrics(const oc_grid_desc& g, std::vector<double>& met) {
   const double dphi = g.ly / ny * pi / 180.0;
   const double phi0 = g.y0 * pi / 180.0;
   const double R = g.radius;
-  met.assign(5 * (size_t)(ny + 1), 0.0);
-  double* len_u = met.data();
-  double* dx_u = len_u + (ny + 1);
-  double* len_v = dx_u + (ny + 1);
-  double* dy_v = len_v + (ny + 1);
-  double* area = dy_v + (ny + 1);
+  met.assign(3 * (size_t)(ny + 1), 0.0);
+  double* len_v = met.data();
+  double* rarea = len_v + (ny + 1);
+  double* rdx = rarea + (ny + 1);
   for (int j = 0; j <= ny; ++j) {
     const double phf = phi0 + j * dphi;
     len_v[j] = R * std::cos(phf) * dlam;
-    dy_v[j] = R * dphi;
     if (j < ny) {
-      const double phc = phf + 0.5 * dphi;
-      len_u[j] = R * dphi;
-      dx_u[j] = R * std::cos(phc) * dlam;
-      area[j] = R * R * dlam * (std::sin(phf + dphi) - std::sin(phf));
+      rdx[j] = 1.0 / (R * std::cos(phf + 0.5 * dphi) * dlam);
+      rarea[j] = 1.0 / (R * R * dlam * (std::sin(phf + dphi) - std::sin(phf)));
     }
   }
 }
@@ -1048,11 +1044,13 @@ BaroBufs baro_bufs(oc_model* m) {
   b.etab = m->etab;
   b.Ub = m->ubar;
   b.Vb = m->vbar;
-  b.len_u = m->metric;
-  b.dx_u = m->metric + (ny + 1);
-  b.len_v = m->metric + 2 * (ny + 1);
-  b.dy_v = m->metric + 3 * (ny + 1);
-  b.area = m->metric + 4 * (ny + 1);
+  const double dy = m->gd.radius * (m->gd.ly / ny * 3.14159265358979323846 / 180.0);
+  b.len_v = m->metric;
+  b.rarea = m->metric + (ny + 1);
+  b.rdx = m->metric + 2 * (ny + 1);
+  b.len_u = dy;
+  b.rdy = 1.0 / dy;
+  b.first = b.last = 0;
   b.nx = m->dims.nx;
   b.ny = ny;
   return b;
@@ -1202,29 +1200,23 @@ int hydro_steps(oc_model* m, double dt, int N, int M, const double* a, int nstep
 
 template <class T>
 int free_surface_call(oc_model* m, double dt, int N, int M, const double* a, hipStream_t s) {
-  const long n2 = (long)(m->dims.ny + 1) * m->dims.nx;
-  OC_CHECK_HIP(launch_baro_fill(m->etab, 0.0, n2, s));
-  OC_CHECK_HIP(launch_baro_fill(m->ubar, 0.0, n2, s));
-  OC_CHECK_HIP(launch_baro_fill(m->vbar, 0.0, n2, s));
   const double dtau = dt / N;
   const double gH = m->md.g * m->md.depth;
   for (int n = 0; n < M;) {
     const int ns = std::min(baro_max_fused(), M - n);
     BaroBufs b = baro_bufs(m);
+    b.first = n == 0;
+    b.last = n + ns == M;
     OC_CHECK_HIP(launch_baro_substeps(b, dtau, gH, a + n, ns, s));
     m->bcur = 1 - m->bcur;
     n += ns;
   }
-  // correction of the baroclinic velocity: its depth integral becomes Ubar
+  // the barotropic state now holds the averages (its restart); correction of
+  // the baroclinic velocity: its depth integral becomes Ubar
   const double dz = m->gd.lz / m->gd.nz;
-  OC_CHECK_HIP(launch_baro_correct<T>(m->dims, (T*)m->state[m->cur][OC_U], m->ubar, 0,
-                                      m->dims.ny, dz, m->md.depth, s));
-  OC_CHECK_HIP(launch_baro_correct<T>(m->dims, (T*)m->state[m->cur][OC_V], m->vbar, 1,
-                                      m->dims.ny, dz, m->md.depth, s));
-  // restart of the barotropic state from the averages
-  OC_CHECK_HIP(launch_baro_copy(m->eta[m->bcur], m->etab, (long)m->dims.ny * m->dims.nx, s));
-  OC_CHECK_HIP(launch_baro_copy(m->ubt[m->bcur], m->ubar, (long)m->dims.ny * m->dims.nx, s));
-  OC_CHECK_HIP(launch_baro_copy(m->vbt[m->bcur], m->vbar, n2, s));
+  OC_CHECK_HIP(launch_baro_correct<T>(m->dims, (T*)m->state[m->cur][OC_U],
+                                      (T*)m->state[m->cur][OC_V], m->ubt[m->bcur], m->vbt[m->bcur],
+                                      dz, m->md.depth, s));
   return OC_OK;
 }
 

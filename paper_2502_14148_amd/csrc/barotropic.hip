@@ -6,129 +6,204 @@
 // substep to the other.  Each workgroup recomputes the substeps on a halo
 // around its tile, so neither the forward (eta) and backward (U, V) halves
 // of a substep nor successive substeps need a grid-wide barrier.  The
-// running averages are accumulated in place in FP64.  All 2D arrays are
+// running averages are accumulated in FP64; the last launch of a step writes
+// them in place of the state, which restarts from them.  All 2D arrays are
 // dense FP64, x fastest; x is periodic, y has walls (V = 0 on faces 0 and
 // ny).
+#include "gaddr.h"
 #include "oc_internal.h"
 
 namespace oc {
 
 namespace {
 
-// Own tile of a workgroup (one cell per thread) and the substeps per launch:
-// on the 1440 x 560 sector, 32 x 32 tiles took 0.82 ms per 59 substeps (plus
-// correction and restart) with 6 substeps per launch, 0.83 with 5, 0.86
-// with 4; 32 x 16 tiles 0.95 and 32 x 8 tiles 1.10 with 4.
-constexpr int BTX = 32, BTY = 32;
-
-// Up to BHS substeps in one launch (temporal blocking).  A workgroup owns a
-// BTX x BTY tile and stages eta, U, V, GU, GV on the tile widened by BHS
-// cells on every side (plus the U column and V row beyond) in LDS.  Each
-// substep is valid on a region one cell narrower per side than the last
-// (eta needs U, V one cell right/above; U, V need eta one cell left/below),
-// so after ns <= BHS substeps the own tile is exact.  Rows outside the
-// domain hold zeros and the wall faces V(0), V(ny) stay zero; x wraps
-// periodically.  The running averages of the own cells take the substeps'
-// terms one at a time, in substep order.
-constexpr int BHS = 6;
-constexpr int BEX = BTX + 2 * BHS, BEY = BTY + 2 * BHS;   // widened tile
-constexpr int BPX = BEX + 1, BPY = BEY + 1;               // + U column, V row
+// Up to BHS substeps in one launch.  A workgroup takes a widened tile of 64 x
+// BH cells, of which the inner (64 - 2 BHS) x (BH - 2 BHS) are its own.  A wave
+// holds the 64 columns of BRW rows in registers: eta, U, V and the forcing of
+// a cell never go to LDS.  The x neighbours come from the next lane by DPP,
+// the y neighbours from the next register, and only the row at each side of
+// a wave through LDS (two 512-byte rows per wave and substep).  Each substep
+// is valid on a region one cell narrower per side than the last (eta needs
+// U, V one cell right/above; U, V need eta one cell left/below), so after ns
+// <= BHS substeps the own tile is exact; what the edge lanes and rows compute
+// from missing neighbours never reaches it.  Rows outside the domain have
+// zero coefficients and hold zeros, and the wall faces V(0), V(ny) stay
+// zero; x wraps periodically.
+//
+// Within a launch the transports are scaled, u = dtau U and v = dtau V, so that
+// a substep is
+//   eta -= (L_u (u_{i+1} - u_i) + L_v,{j+1} v_{j+1} - L_v,j v_j) / A,
+//   u += dtau^2 GU - g H dtau^2 / dx (eta_i - eta_{i-1}),  v likewise,
+// 14 FP64 operations per cell with the running averages and no division (the
+// row factors and their inverses are formed once).  Bound by the
+// state's 140 bytes per cell and launch and by the 2.1 cells computed per
+// own cell.  On the 1440 x 560 sector a substep took 9.6 us with the tile in LDS
+// (three divisions per cell, six substeps per launch), 3.8 us now.  Rows per
+// wave x waves, substeps per launch, us for the 59 substeps and a correction
+// of 8 levels: 4 x 16, 12: 244; 4 x 16, 10: 257; 4 x 16, 14: 297; 8 x 8, 12:
+// 261; 5 x 16, 12: 260; 6 x 8, 6: 270; 3 x 16, 12: 303 (LDS tile: 577).
+constexpr int BRW = 4, BNW = 16, BH = BRW * BNW, BHS = 12;
+constexpr int BOX = 64 - 2 * BHS, BOY = BH - 2 * BHS;   // own tile
+static_assert(BOX > 0 && BOY > 0, "an own tile is left");
 struct BaroWeights {
   double w[BHS];
 };
 
-__global__ void __launch_bounds__(BTX * BTY) baro_multi_kernel(BaroBufs b, double dtau,
-                                                               double gH, BaroWeights wts,
-                                                               int ns) {
-  __shared__ double E[BPY][BPX], Us[BPY][BPX], Vs[BPY][BPX], Gu[BPY][BPX], Gv[BPY][BPX];
-  const int i0 = blockIdx.x * BTX - BHS, j0 = blockIdx.y * BTY - BHS;   // corner of the widened tile
-  const int tid = threadIdx.x;
-  for (int e = tid; e < BPX * BPY; e += BTX * BTY) {
-    const int y = e / BPX, x = e - y * BPX;
-    int gi = (i0 + x) % b.nx;
-    if (gi < 0) gi += b.nx;
-    const int gj = j0 + y;
-    double ev = 0.0, uv = 0.0, vv = 0.0, gu = 0.0, gv = 0.0;
-    if (gj >= 0 && gj < b.ny) {
-      const long c = (long)gj * b.nx + gi;
-      ev = b.eta[c];
-      uv = b.U[c];
-      gu = b.GU[c];
-      if (gj > 0) {
-        vv = b.V[c];
-        gv = b.GV[c];
-      }
-    }
-    E[y][x] = ev;
-    Us[y][x] = uv;
-    Vs[y][x] = vv;
-    Gu[y][x] = gu;
-    Gv[y][x] = gv;
+// x of the next (previous) lane; 0 past the wave's end
+template <int CTRL>
+__device__ inline double lane_shift(double x) {
+  const unsigned long long v = __builtin_bit_cast(unsigned long long, x);
+  const unsigned lo = __builtin_amdgcn_update_dpp(0u, (unsigned)v, CTRL, 0xf, 0xf, true);
+  const unsigned hi = __builtin_amdgcn_update_dpp(0u, (unsigned)(v >> 32), CTRL, 0xf, 0xf, true);
+  return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+__device__ inline double lane_next(double x) { return lane_shift<0x130>(x); }   // wave_shl:1
+__device__ inline double lane_prev(double x) { return lane_shift<0x138>(x); }   // wave_shr:1
+
+__global__ void __launch_bounds__(64 * BNW) baro_multi_kernel(BaroBufs b, double dtau, double gH,
+                                                              BaroWeights wts, int ns) {
+  __shared__ double vrow[BNW][64], erow[BNW][64];   // a wave's first row of v, last of e
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int gx = (int)blockIdx.x * BOX - BHS + lane;
+  int gi = gx % b.nx;
+  if (gi < 0) gi += b.nx;
+  const int j0 = (int)blockIdx.y * BOY - BHS + wave * BRW;   // the wave's first row
+  const double K = gH * dtau * dtau, dtau2 = dtau * dtau;
+  double e[BRW], u[BRW], v[BRW], gu[BRW], gv[BRW], se[BRW], su[BRW], sv[BRW];
+  double lv[BRW + 1], ra[BRW], kx[BRW], ky[BRW];   // uniform
+  lv[BRW] = b.len_v[min(max(j0 + BRW, 0), b.ny)];
+#pragma unroll
+  for (int r = 0; r < BRW; ++r) {
+    const int gj = j0 + r;
+    const bool in = gj >= 0 && gj < b.ny, vin = gj > 0 && gj < b.ny;   // uniform
+    const int jc = min(max(gj, 0), b.ny - 1);
+    lv[r] = b.len_v[jc];
+    ra[r] = in ? b.rarea[jc] : 0.0;
+    kx[r] = in ? K * b.rdx[jc] : 0.0;
+    ky[r] = vin ? K * b.rdy : 0.0;
+    const long c = (long)jc * b.nx + gi;
+    e[r] = in ? b.eta[c] : 0.0;
+    u[r] = in ? b.U[c] : 0.0;
+    gu[r] = in ? b.GU[c] : 0.0;
+    v[r] = vin ? b.V[c] : 0.0;
+    gv[r] = vin ? b.GV[c] : 0.0;
+    se[r] = su[r] = sv[r] = 0.0;
   }
-  // own cell of this thread and its running averages
-  const int tx = tid % BTX, ty = tid / BTX;
-  const int oi = i0 + BHS + tx, oj = j0 + BHS + ty;
-  const bool own = oi < b.nx && oj < b.ny;
-  const long oc = (long)oj * b.nx + oi;
-  double ea = 0.0, ua = 0.0, va = 0.0;
-  if (own) {
-    ea = b.etab[oc];
-    ua = b.Ub[oc];
-    va = b.Vb[oc];
+#pragma unroll
+  for (int r = 0; r < BRW; ++r) {
+    u[r] *= dtau;
+    v[r] *= dtau;
+    gu[r] *= dtau2;
+    gv[r] *= dtau2;
   }
+  vrow[wave][lane] = v[0];
   __syncthreads();
-  for (int sstep = 0; sstep < ns; ++sstep) {
-    // eta^{n+1} = eta^n - dtau div(U^n, V^n) on rows 0..BEY-1, columns 0..BEX-1
-    for (int e = tid; e < BEX * BEY; e += BTX * BTY) {
-      const int y = e / BEX, x = e - y * BEX;
-      const int gj = j0 + y;
-      if (gj >= 0 && gj < b.ny) {
-        const double fx = b.len_u[gj] * (Us[y][x + 1] - Us[y][x]);
-        const double fy = b.len_v[gj + 1] * Vs[y + 1][x] - b.len_v[gj] * Vs[y][x];
-        E[y][x] = E[y][x] - dtau * ((fx + fy) / b.area[gj]);
-      }
+  for (int s = 0; s < ns; ++s) {
+    const double vtop = wave + 1 < BNW ? vrow[wave + 1][lane] : 0.0;
+    const double wn = wts.w[s];
+#pragma unroll
+    for (int r = 0; r < BRW; ++r) {
+      const double v1 = r + 1 < BRW ? v[r + 1] : vtop;
+      double f = b.len_u * (lane_next(u[r]) - u[r]);
+      f = fma(lv[r + 1], v1, f);
+      f = fma(-lv[r], v[r], f);
+      e[r] = fma(-ra[r], f, e[r]);
+      se[r] = fma(wn, e[r], se[r]);
     }
+    erow[wave][lane] = e[BRW - 1];
     __syncthreads();
-    // eta is not written again before the next substep's first barrier
-    const double wn = wts.w[sstep];
-    if (own) ea += wn * E[BHS + ty][BHS + tx];
-    // U^{n+1}, V^{n+1} from eta^{n+1} (columns / rows 1.. of the widened tile)
-    for (int e = tid; e < BEX * BEY; e += BTX * BTY) {
-      const int y = e / BEX, x = e - y * BEX;
-      const int gj = j0 + y;
-      if (gj >= 0 && gj < b.ny) {
-        const double en = E[y][x];
-        if (x > 0) Us[y][x] = Us[y][x] - dtau * (gH * (en - E[y][x - 1]) / b.dx_u[gj] - Gu[y][x]);
-        if (y > 0)
-          Vs[y][x] = (gj > 0)
-                         ? Vs[y][x] - dtau * (gH * (en - E[y - 1][x]) / b.dy_v[gj] - Gv[y][x])
-                         : 0.0;
-      }
+    const double ebot = wave > 0 ? erow[wave - 1][lane] : 0.0;
+#pragma unroll
+    for (int r = 0; r < BRW; ++r) {
+      const double e1 = r > 0 ? e[r - 1] : ebot;
+      u[r] = fma(-kx[r], e[r] - lane_prev(e[r]), u[r]) + gu[r];
+      v[r] = fma(-ky[r], e[r] - e1, v[r]) + gv[r];
+      su[r] = fma(wn, u[r], su[r]);
+      sv[r] = fma(wn, v[r], sv[r]);
     }
+    vrow[wave][lane] = v[0];
     __syncthreads();
-    // U and V are not written again before the next substep's second barrier
-    if (own) {
-      ua += wn * Us[BHS + ty][BHS + tx];
-      va += wn * Vs[BHS + ty][BHS + tx];
+  }
+  // the own cells (x: a tile may reach past the last column)
+  if (lane < BHS || lane >= BHS + BOX || gx >= b.nx) return;
+  const double rt = 1.0 / dtau;
+#pragma unroll
+  for (int r = 0; r < BRW; ++r) {
+    const int gj = j0 + r, ty = wave * BRW + r;
+    if (ty < BHS || ty >= BHS + BOY || gj >= b.ny) continue;
+    const long c = (long)gj * b.nx + gx;
+    double ea = se[r], ua = su[r] * rt, va = sv[r] * rt;
+    if (!b.first) {
+      ea += b.etab[c];
+      ua += b.Ub[c];
+      va += b.Vb[c];
+    }
+    if (b.last) {
+      b.eta1[c] = ea;
+      b.U1[c] = ua;
+      b.V1[c] = va;
+      if (gj == b.ny - 1) b.V1[c + b.nx] = 0.0;   // the northern wall
+    } else {
+      b.eta1[c] = e[r];
+      b.U1[c] = u[r] * rt;
+      b.V1[c] = v[r] * rt;
+      b.etab[c] = ea;
+      b.Ub[c] = ua;
+      b.Vb[c] = va;
     }
   }
-  if (!own) return;
-  b.eta1[oc] = E[BHS + ty][BHS + tx];
-  b.U1[oc] = Us[BHS + ty][BHS + tx];
-  b.V1[oc] = Vs[BHS + ty][BHS + tx];
-  b.etab[oc] = ea;
-  b.Ub[oc] = ua;
-  b.Vb[oc] = va;
+}
+
+// u <- u + (Ubar - dz sum_k u) / H on every column of u (rows 0..ny-1) and v
+// (the interior faces 1..ny-1), z = 0 and 1 of the grid.  Levels are fetched
+// CKB at a time so that their loads are in flight together; the second read
+// of a column comes from the caches.  Bound by HBM (16 bytes per cell of u and
+// v).  1440 x 560 x 50 FP32: 223 us in two launches of 64-column groups with
+// 64-bit addresses (a group's rows share a cache line with the next group's,
+// on another XCD), 172 us with 256 columns and uniform level bases; columns
+// kept in registers between the passes measured 166 us, not worth a kernel
+// per column height.
+template <class T>
+struct CorrectArgs {
+  T* f[2];
+  const double* bar[2];
+};
+template <class T>
+__global__ void __launch_bounds__(256) baro_correct_kernel(Dims d, CorrectArgs<T> a, double dz,
+                                                           double inv_h) {
+  const int i = blockIdx.x * 256 + threadIdx.x, z = blockIdx.z, j = z + (int)blockIdx.y;
+  if (i >= d.nx || j >= d.ny) return;
+  // the column's byte offset within a level; levels are a uniform base apart
+  const unsigned off = (unsigned)pidx(d, i, j, -d.h) * (unsigned)sizeof(T);
+  T* const f = a.f[z] + (long)d.h * d.sz;
+  const double bar = glb(a.bar[z])[(long)j * d.nx + i];
+  constexpr int CKB = 10;
+  double sum = 0.0;
+  for (int k0 = 0; k0 < d.nz; k0 += CKB) {
+    T x[CKB];
+#pragma unroll
+    for (int q = 0; q < CKB; ++q)
+      x[q] = at(uniform_ptr(f + (long)min(k0 + q, d.nz - 1) * d.sz), off);
+#pragma unroll
+    for (int q = 0; q < CKB; ++q)
+      if (k0 + q < d.nz) sum += (double)x[q];
+  }
+  const double corr = (bar - dz * sum) * inv_h;
+  for (int k0 = 0; k0 < d.nz; k0 += CKB) {
+    T x[CKB];
+#pragma unroll
+    for (int q = 0; q < CKB; ++q)
+      x[q] = at(uniform_ptr(f + (long)min(k0 + q, d.nz - 1) * d.sz), off);
+#pragma unroll
+    for (int q = 0; q < CKB; ++q)
+      if (k0 + q < d.nz) at(uniform_ptr(f + (long)(k0 + q) * d.sz), off) = (T)((double)x[q] + corr);
+  }
 }
 
 __global__ void baro_fill_kernel(double* a, double v, long n) {
   const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
   if (t < n) a[t] = v;
-}
-
-__global__ void baro_copy_kernel(double* dst, const double* src, long n) {
-  const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < n) dst[t] = src[t];
 }
 
 // u <- u + (Ubar - dz sum_k u) / H on every column of a 3D field stored in
@@ -169,12 +244,6 @@ hipError_t launch_baro_fill(double* a, double v, long n, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_baro_copy(double* dst, const double* src, long n, hipStream_t s) {
-  hipLaunchKernelGGL(baro_copy_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, dst,
-                     src, n);
-  return hipGetLastError();
-}
-
 int baro_max_fused() { return BHS; }
 
 hipError_t launch_baro_substeps(const BaroBufs& b, double dtau, double gH, const double* wn,
@@ -182,24 +251,23 @@ hipError_t launch_baro_substeps(const BaroBufs& b, double dtau, double gH, const
   if (ns < 1 || ns > BHS) return hipErrorInvalidValue;
   BaroWeights w{};
   for (int q = 0; q < ns; ++q) w.w[q] = wn[q];
-  dim3 grid((b.nx + BTX - 1) / BTX, (b.ny + BTY - 1) / BTY);
-  hipLaunchKernelGGL(baro_multi_kernel, grid, dim3(BTX * BTY), 0, s, b, dtau, gH, w, ns);
+  dim3 grid((b.nx + BOX - 1) / BOX, (b.ny + BOY - 1) / BOY);
+  hipLaunchKernelGGL(baro_multi_kernel, grid, dim3(64 * BNW), 0, s, b, dtau, gH, w, ns);
   return hipGetLastError();
 }
 
 template <class T>
-hipError_t launch_baro_correct(const Dims& d, T* f, const double* bar, int j_lo, int j_hi,
+hipError_t launch_baro_correct(const Dims& d, T* u, T* v, const double* ubar, const double* vbar,
                                double dz, double depth, hipStream_t s) {
-  if (j_hi <= j_lo) return hipSuccess;
-  dim3 grid((d.nx + 63) / 64, j_hi - j_lo);
-  hipLaunchKernelGGL(baro_correct_kernel<T>, grid, dim3(64), 0, s, d, f, bar, j_lo, j_hi, dz,
-                     1.0 / depth);
+  const dim3 grid((d.nx + 255) / 256, d.ny, 2), nt(256);
+  const CorrectArgs<T> a{{u, v}, {ubar, vbar}};
+  hipLaunchKernelGGL(baro_correct_kernel<T>, grid, nt, 0, s, d, a, dz, 1.0 / depth);
   return hipGetLastError();
 }
 
-template hipError_t launch_baro_correct<float>(const Dims&, float*, const double*, int, int, double,
-                                               double, hipStream_t);
-template hipError_t launch_baro_correct<double>(const Dims&, double*, const double*, int, int,
-                                                double, double, hipStream_t);
+template hipError_t launch_baro_correct<float>(const Dims&, float*, float*, const double*,
+                                               const double*, double, double, hipStream_t);
+template hipError_t launch_baro_correct<double>(const Dims&, double*, double*, const double*,
+                                                const double*, double, double, hipStream_t);
 
 }  // namespace oc

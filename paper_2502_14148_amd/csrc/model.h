@@ -75,7 +75,7 @@ struct oc_model {
   double* etab;
   double* ubar;
   double* vbar;
-  double* metric;        // len_u | dx_u | len_v | dy_v | area
+  double* metric;        // row factors of the substeps: len_v | 1/area | 1/dx
   int bcur;
   // hydrostatic baroclinic step: diagnostic fields (state precision,
   // padded), row tables, surface stress, and the QAB2 / refresh flags

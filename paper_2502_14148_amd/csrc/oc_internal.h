@@ -236,23 +236,22 @@ struct BaroBufs {
   double* etab;
   double* Ub;
   double* Vb;
-  const double* len_u;   // (ny)     length of an x face
-  const double* dx_u;    // (ny)     centre distance across an x face
   const double* len_v;   // (ny + 1) length of a y face
-  const double* dy_v;    // (ny + 1) centre distance across a y face
-  const double* area;    // (ny)     cell area
+  const double* rarea;   // (ny)     1 / cell area
+  const double* rdx;     // (ny)     1 / centre distance across an x face
+  double len_u, rdy;     // length of an x face, 1 / centre distance across a y face
+  int first, last;       // averages start from zero; they replace the state
   int nx, ny;
 };
 
 hipError_t launch_baro_fill(double* a, double v, long n, hipStream_t s);
-hipError_t launch_baro_copy(double* dst, const double* src, long n, hipStream_t s);
 // ns (1..baro_max_fused()) barotropic substeps in one launch, with the
 // averaging weights wn[0..ns-1] (host array).
 int baro_max_fused();
 hipError_t launch_baro_substeps(const BaroBufs& b, double dtau, double gH, const double* wn,
                                 int ns, hipStream_t s);
 template <class T>
-hipError_t launch_baro_correct(const Dims& d, T* f, const double* bar, int j_lo, int j_hi,
+hipError_t launch_baro_correct(const Dims& d, T* u, T* v, const double* ubar, const double* vbar,
                                double dz, double depth, hipStream_t s);
 
 // ---- Baroclinic step of the hydrostatic model

@@ -83,3 +83,20 @@ def test_volume_conserved_on_gpu(gpu_lib):
         m.free_surface_substeps(600.0, 30, inputs.averaging_weights(30))
     vol = np.sum(met.area[:, None] * m.get_state("eta")[0])
     assert abs(vol - vol0) < 1e-12 * np.sum(met.area[:, None] * np.abs(b["eta"][0]))
+
+
+@pytest.mark.parametrize("n,N,M", [((40, 40, 8), 20, 12), ((40, 48, 8), 20, 13),
+                                   ((48, 8, 8), 20, 25), ((8, 40, 16), 10, 1),
+                                   ((88, 80, 72), 20, 24)])
+def test_substeps_tile_edges(gpu_lib, n, N, M):
+    """Domains of exactly one 40 x 40 own tile, of a little more, narrower
+    than the widened tile (x wraps more than once), and counts of substeps
+    around whole launches of 12."""
+    run_case(gpu_lib, inputs.sector_physics(n), "fp64", N, M, seed=11)
+
+
+def test_substeps_without_gravity(gpu_lib):
+    """g = 0: the transports move under the forcing alone."""
+    ph = inputs.sector_physics((48, 16, 8))
+    ph.g = 0.0
+    run_case(gpu_lib, ph, "fp64", 10, 19, seed=12)
