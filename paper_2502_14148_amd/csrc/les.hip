@@ -10,9 +10,11 @@
 //     kappa_e = max(0, -C sum_k Delta_k^2 d_k u_i d_k c d_i c / |grad c|^2).
 //
 // Two kernels per substage; each workgroup owns a column tile and marches
-// up a chunk of levels, keeping three levels (k-1, k, k+1, with a one-cell
-// halo) of every field it reads in LDS rings, so each value is fetched from
-// memory once per tile instead of once per neighbour that reads it:
+// up a chunk of levels, keeping four levels (k-1, k, k+1 in use, k+2 on its
+// way; with a one-cell halo) of every field it reads in LDS rings, so each
+// value is fetched from memory once per tile instead of once per neighbour
+// that reads it.  The buffer unit copies level k+2 into its slot while level k
+// is computed (load-to-LDS), with one barrier per level:
 //   1. the eddy viscosity (and AMD's per-tracer diffusivity) at the centres
 //      from the resolved gradients: diagonal strain at the centre, the
 //      off-diagonal components on the twelve surrounding edges (squared then
@@ -22,22 +24,34 @@
 //      C-grid locations, edge viscosities the mean of four centres) and
 //      d_i(kappa_e d_i c) of the tracers (face diffusivities the mean of two
 //      centres); no flux through the walls.  The tendency kernel adds them.
+// The kernels are instantiated for the number of fields they read, which sets
+// their LDS and with it the resident workgroups, and the compiler keeps every
+// ring offset an immediate.  What bounds them: vector issue together with the
+// waits of a level.  At 256x256x128 FP32 (2 tracers, Smagorinsky-Lilly) the
+// viscosity pass issues 198 vector and 28 LDS instructions per cell and wave
+// (42 us at one per cycle; 39 us of memory traffic at 5.2 TB/s) and takes 80 us,
+// the fluxes 234 and 42 (50 us; 71 us of traffic) and take 116 us.  With the
+// levels brought through registers into a three-level ring, two barriers per
+// level and field loops up to the largest tracer count the same passes took
+// 100 and 166 us; one substage of both (with the launches between), before and
+// now: Smagorinsky-Lilly 276 -> 200 us, AMD 312 -> 246 us, 64^3 75 -> 15.5 us.
+#include <algorithm>
+
 #include "oc_internal.h"
+#include "tendency_tile.h"
 
 namespace oc {
 
 namespace {
 
-// Tiles: TX x TY columns, chunks of LES_KC levels.  Workgroups are dealt
+// Tiles: TX x TY columns, chunks of kc levels.  Workgroups are dealt
 // round-robin to the 8 XCDs; renumbering them gives each XCD a contiguous
 // run of tiles, so the halo rows shared by neighbouring tiles stay in one L2.
-constexpr int LES_KC = 16;
-
 struct LesTile {
   int i0, j0, kb, ke;
 };
 
-__device__ inline LesTile les_tile(const Dims& d, int tx, int ty) {
+__device__ inline LesTile les_tile(const Dims& d, int tx, int ty, int kc) {
   const unsigned nb = gridDim.x;
   unsigned b = blockIdx.x;
   if (nb % 8 == 0) b = (b % 8) * (nb / 8) + b / 8;
@@ -45,91 +59,102 @@ __device__ inline LesTile les_tile(const Dims& d, int tx, int ty) {
   LesTile t;
   t.i0 = (int)(b % nbx) * tx;
   t.j0 = (int)((b / nbx) % nby) * ty;
-  t.kb = (int)(b / (nbx * nby)) * LES_KC;
-  t.ke = min(t.kb + LES_KC, d.nz);
+  t.kb = (int)(b / (nbx * nby)) * kc;
+  t.ke = min(t.kb + kc, d.nz);
   return t;
 }
 
-// Values of field f around the own cell, read from the LDS rings: level
-// k + dk sits at ring offset off[dk + 1] of the field's three planes.
-template <class T, int PX, int PL>
+// Values of field f around the own cell, read from the LDS rings: at[dk + 1]
+// is the position (-1, -1) of the own cell's neighbourhood in level k + dk of
+// field 0, so that every access is a compile-time offset from it.
+template <class T, int PX, int PLP>
 struct Ring {
-  const T* S;      // ring planes of all fields, 3 PL each
-  int L;           // own position in a plane
-  int off[3];      // plane offsets of levels k-1, k, k+1
+  const T* S;      // ring planes of all fields, 4 PLP each
+  int at[3];
   __device__ T operator()(int f, int di, int dj, int dk) const {
-    return S[f * 3 * PL + off[dk + 1] + L + dj * PX + di];
+    return S[at[dk + 1] + f * 4 * PLP + (dj + 1) * PX + di + 1];
   }
 };
 
-// Load level kk of nf <= NFMAX fields into ring slot `slot` (tile plus a
-// one-cell halo).  Every load of the level is issued before the first LDS
-// store, so the fetches overlap.  goff: the thread's element offsets within
-// a level, relative to the tile corner.
-template <class T, int TX, int TY, int NFMAX>
-__device__ inline void les_fill(T* S, const T* const* fld, int nf, const Dims& d, const LesTile& t,
-                                const int* goff, int slot, int kk) {
-  constexpr int PX = TX + 2, PY = TY + 2, PL = PX * PY, NT = TX * TY;
-  constexpr int NR = (PL + NT - 1) / NT;
-  const long base = (long)(kk + d.h) * d.sz + (long)(t.j0 - 1 + d.h) * d.sy + (t.i0 - 1 + d.h);
-  T v[NFMAX][NR];
+// The z-march of a tile over NF fields: cell(k, ring, out) computes the NO
+// results of the own cell of every level, with the rings holding levels k-1,
+// k, k+1, and put(i, j, k, out) stores them.  The stores of a level are issued
+// at the start of the next one: the wait for the copies at a level's end is a
+// wait for every memory operation, and this way the stores have had a level's
+// time as well.
+template <class T, int TX, int TY, int NF, int NO, class Cell, class Put>
+__device__ inline void les_march(const Dims& d, const T* const (&fld)[NF], int kc, Cell cell,
+                                 Put put) {
+  constexpr int PX = TX + 2, PY = TY + 2, NT = TX * TY, ES = (int)sizeof(T);
+  using PC = tz::PlaneCopy<PX, PY, NT, ES>;
+  constexpr int PLP = PC::PLP;
+  __shared__ T S[NF * 4 * PLP];
+  const LesTile t = les_tile(d, TX, TY, kc);
+  const int tid = threadIdx.x, tx = tid % TX, ty = tid / TX;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  // per-lane byte offsets of the copied plane dwords from the tile corner
+  const int sy = (int)d.sy;
+  auto dword_off = [&](int j) -> uint32_t {
+    if (j > PC::PLD - 1) j = PC::PLD - 1;
+    const int e = j / PC::DPE, half = j - e * PC::DPE;
+    const int ly = e / PX, lx = e - ly * PX;
+    return (uint32_t)((ly * sy + lx) * ES + half * 4);
+  };
+  uint32_t goff[PC::NR + PC::MAXC];
 #pragma unroll
-  for (int f = 0; f < NFMAX; ++f)
-    if (f < nf) {
-      const auto src = glb(fld[f]) + base;
+  for (int r = 0; r < PC::NR; ++r) goff[r] = dword_off(r * NT + tid);
 #pragma unroll
-      for (int r = 0; r < NR; ++r)
-        if (PL % NT == 0 || threadIdx.x + r * NT < PL) v[f][r] = src[goff[r]];
-    }
+  for (int c = 0; c < PC::MAXC; ++c)
+    goff[PC::NR + c] = dword_off(PC::NR * NT + (wave + c * PC::NWV) * 64 + lane);
+  const uint32_t corner = (uint32_t)(((t.j0 - 1 + d.h) * sy + (t.i0 - 1 + d.h)) * ES);
+  const uint32_t lvb = (uint32_t)d.sz * ES;
+  auto copy_level = [&](int kk) {
+    const uint32_t so = (uint32_t)(kk + d.h) * lvb + corner;
 #pragma unroll
-  for (int f = 0; f < NFMAX; ++f)
-    if (f < nf) {
-      T* dst = S + f * 3 * PL + slot * PL;
+    for (int f = 0; f < NF; ++f) {
+      const __amdgpu_buffer_rsrc_t rs = tz::make_rsrc((const char*)fld[f]);
+      T* dst = S + (f * 4 + (kk & 3)) * PLP;
 #pragma unroll
-      for (int r = 0; r < NR; ++r) {
-        const int e = threadIdx.x + r * NT;
-        if (PL % NT == 0 || e < PL) dst[e] = v[f][r];
+      for (int r = 0; r < PC::NR; ++r)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (void*)(dst + (r * NT + wave * 64) / PC::DPE),
+                                                 4, goff[r], so, 0, 0);
+#pragma unroll
+      for (int c = 0; c < PC::MAXC; ++c) {
+        const int ch = wave + c * PC::NWV;
+        if (ch < PC::NCH)
+          __builtin_amdgcn_raw_ptr_buffer_load_lds(
+              rs, (void*)(dst + (PC::NR * NT + ch * 64) / PC::DPE), 4, goff[PC::NR + c], so, 0, 0);
       }
     }
-}
-
-// The z-march of a tile: cell(i, j, k, ring) runs for every cell of every
-// level, with the rings holding levels k-1, k, k+1.
-template <class T, int TX, int TY, int NFMAX, class Cell>
-__device__ inline void les_march(const Dims& d, const T* const* fld, int nf, Cell cell) {
-  constexpr int PX = TX + 2, PY = TY + 2, PL = PX * PY;
-  __shared__ T S[NFMAX * 3 * PL];
-  constexpr int NT = TX * TY, NR = (PL + NT - 1) / NT;
-  const LesTile t = les_tile(d, TX, TY);
-  const int tx = threadIdx.x % TX, ty = threadIdx.x / TX;
-  int goff[NR];
-#pragma unroll
-  for (int q = 0; q < NR; ++q) {
-    const int e = threadIdx.x + q * NT;
-    const int ly = e / PX, lx = e - ly * PX;
-    goff[q] = (int)(ly * d.sy) + lx;
-  }
-  les_fill<T, TX, TY, NFMAX>(S, fld, nf, d, t, goff, (t.kb + 2) % 3, t.kb - 1);
-  les_fill<T, TX, TY, NFMAX>(S, fld, nf, d, t, goff, t.kb % 3, t.kb);
-  Ring<T, PX, PL> r;
+  };
+  copy_level(t.kb - 1);
+  copy_level(t.kb);
+  copy_level(t.kb + 1);
+  tz::wait_vm();
+  __syncthreads();
+  Ring<T, PX, PLP> r;
   r.S = S;
-  r.L = (ty + 1) * PX + (tx + 1);
+  const int L = ty * PX + tx;
+  T out[NO];
   for (int k = t.kb; k < t.ke; ++k) {
-    __syncthreads();  // the slot of level k-2 is free
-    les_fill<T, TX, TY, NFMAX>(S, fld, nf, d, t, goff, (k + 1) % 3, k + 1);
+    if (k > t.kb) put(t.i0 + tx, t.j0 + ty, k - 1, out);
+    // level k - 2 is read by no one since the last barrier
+    if (k + 1 < t.ke) copy_level(k + 2);
+    r.at[0] = tz::opaque(((k + 3) & 3) * PLP + L);
+    r.at[1] = tz::opaque((k & 3) * PLP + L);
+    r.at[2] = tz::opaque(((k + 1) & 3) * PLP + L);
+    cell(k, r, out);
+    tz::wait_vm();      // this wave's copies have landed
     __syncthreads();
-    r.off[0] = ((k + 2) % 3) * PL;
-    r.off[1] = (k % 3) * PL;
-    r.off[2] = ((k + 1) % 3) * PL;
-    cell(t.i0 + tx, t.j0 + ty, k, r);
   }
+  put(t.i0 + tx, t.j0 + ty, t.ke - 1, out);
 }
 
 // Ring fields of the viscosity pass: 0 u, 1 v, 2 w, then the tracers
 // (Smagorinsky-Lilly: T and S when buoyant; AMD: every tracer).
-template <class T, int KIND, class R>
-__device__ inline void les_viscosity_cell(const Dims& d, const LesArgs<T>& a, int i, int j, int k,
-                                          const R& r) {
+template <class T, int KIND, int NTR, class R>
+__device__ inline void les_viscosity_cell(const Dims& d, const LesArgs<T>& a, int k, const R& r,
+                                          T* out) {
   auto U = [&](int di, int dj, int dk) { return r(0, di, dj, dk); };
   auto V = [&](int di, int dj, int dk) { return r(1, di, dj, dk); };
   auto W = [&](int di, int dj, int dk) { return r(2, di, dj, dk); };
@@ -172,7 +197,7 @@ __device__ inline void les_viscosity_cell(const Dims& d, const LesArgs<T>& a, in
       }
     const T s2 = T(2) * (ux * ux + vy * vy + wz * wz) + (sxy2 + sxz2 + syz2);  // 4 x (1/4) sums
     T n2 = T(0);
-    if (a.buoyancy) {
+    if (NTR == 2) {   // buoyant
       auto b = [&](int dk) {
         return a.g_alpha * (r(3, 0, 0, dk) - a.t_ref) - a.g_beta * (r(4, 0, 0, dk) - a.s_ref);
       };
@@ -209,7 +234,8 @@ __device__ inline void les_viscosity_cell(const Dims& d, const LesArgs<T>& a, in
       }
     nu = (den > T(0)) ? fmax(T(0), -a.camd * num / den) : T(0);
     // per-tracer diffusivities
-    for (int q = 0; q < a.ntr; ++q) {
+#pragma unroll
+    for (int q = 0; q < NTR; ++q) {
       auto C = [&](int di, int dj, int dk) { return r(3 + q, di, dj, dk); };
       const T c0 = C(0, 0, 0);
       const T gx = T(0.5) * (C(1, 0, 0) - C(-1, 0, 0)) * rdx;
@@ -224,35 +250,39 @@ __device__ inline void les_viscosity_cell(const Dims& d, const LesArgs<T>& a, in
         for (int ii = 0; ii < 3; ++ii) kn += D2[kk] * G[ii][kk] * gc[kk] * gc[ii];
       const T kd = gc[0] * gc[0] + gc[1] * gc[1] + gc[2] * gc[2];
       const T kap = (kd > T(0)) ? fmax(T(0), -a.camd * kn / kd) : T(0);
-      store_with_images(a.kap[q], d, i, j, k, kap, false);
+      out[1 + q] = kap;
     }
   }
-  store_with_images(a.nu, d, i, j, k, nu, false);
+  out[0] = nu;
 }
 
-template <class T, int KIND, int TX, int TY>
-__global__ void __launch_bounds__(TX * TY) les_viscosity_kernel(Dims d, LesArgs<T> a) {
-  const T* fld[3 + OC_MAX_TRACERS] = {a.u, a.v, a.w};
-  int nf = 3;
-  if (KIND == OC_LES_SMAGORINSKY) {
-    if (a.buoyancy) { fld[3] = a.c0; fld[4] = a.c1; nf = 5; }
-  } else {
-    for (int q = 0; q < a.ntr; ++q) fld[3 + q] = a.tr[q];
-    nf = 3 + a.ntr;
-  }
-  les_march<T, TX, TY, 3 + OC_MAX_TRACERS>(
-      d, fld, nf, [&](int i, int j, int k, const auto& r) {
-        les_viscosity_cell<T, KIND>(d, a, i, j, k, r);
+// NTR: AMD: the tracers; Smagorinsky-Lilly: 2 (T and S) when buoyant, else 0.
+template <class T, int KIND, int NTR, int TX, int TY>
+__global__ void __launch_bounds__(TX * TY) les_viscosity_kernel(Dims d, LesArgs<T> a, int kc) {
+  const T* fld[3 + NTR];
+  fld[0] = a.u;
+  fld[1] = a.v;
+  fld[2] = a.w;
+#pragma unroll
+  for (int q = 0; q < NTR; ++q)
+    fld[3 + q] = KIND == OC_LES_SMAGORINSKY ? (q ? a.c1 : a.c0) : a.tr[q];
+  constexpr int NO = KIND == OC_LES_AMD ? 1 + NTR : 1;   // nu, AMD's kappas
+  les_march<T, TX, TY, 3 + NTR, NO>(
+      d, fld, kc,
+      [&](int k, const auto& r, T* out) { les_viscosity_cell<T, KIND, NTR>(d, a, k, r, out); },
+      [&](int i, int j, int k, const T* out) {
+        store_with_images(a.nu, d, i, j, k, out[0], false);
+#pragma unroll
+        for (int q = 1; q < NO; ++q) store_with_images(a.kap[q - 1], d, i, j, k, out[q], false);
       });
 }
 
 // The closure tendencies of the cell index (i, j, k): u at x face i, v at y
 // face j, w at z face k, tracers at the centre.  Ring fields: 0 u, 1 v, 2 w,
-// 3 nu, 4 + q tracer q, 4 + ntr + q AMD's kappa of tracer q.
-template <class T, class R>
-__device__ inline void les_flux_cell(const Dims& d, const LesArgs<T>& a, int i, int j, int k,
-                                     const R& r) {
-  const long c = pidx(d, i, j, k);
+// 3 nu, 4 + q tracer q, 4 + NTR + q AMD's kappa of tracer q.
+template <class T, int NTR, bool AMD, class R>
+__device__ inline void les_flux_cell(const Dims& d, const LesArgs<T>& a, int k, const R& r,
+                                     T* out) {
   auto U = [&](int di, int dj, int dk) { return r(0, di, dj, dk); };
   auto V = [&](int di, int dj, int dk) { return r(1, di, dj, dk); };
   auto W = [&](int di, int dj, int dk) { return r(2, di, dj, dk); };
@@ -289,14 +319,14 @@ __device__ inline void les_flux_cell(const Dims& d, const LesArgs<T>& a, int i, 
     const T t0 = T(2) * N(-1, 0, 0) * (U(0, 0, 0) - U(-1, 0, 0)) * rdx;
     const T t1 = T(2) * N(0, 0, 0) * (U(1, 0, 0) - U(0, 0, 0)) * rdx;
     const T g = (t1 - t0) * rdx + (txy(0, 1) - txy(0, 0)) * rdy + (txz(0, 1) - txz(0, 0)) * rzc;
-    glb(a.gc[0])[c] = g;
+    out[0] = g;
   }
   // v at y face j
   {
     const T t0 = T(2) * N(0, -1, 0) * (V(0, 0, 0) - V(0, -1, 0)) * rdy;
     const T t1 = T(2) * N(0, 0, 0) * (V(0, 1, 0) - V(0, 0, 0)) * rdy;
     const T g = (txy(1, 0) - txy(0, 0)) * rdx + (t1 - t0) * rdy + (tyz(0, 1) - tyz(0, 0)) * rzc;
-    glb(a.gc[1])[c] = g;
+    out[1] = g;
   }
   // w at z face k (the w cell spans the centres k-1, k: thickness dzf_k);
   // txz and tyz on face k are the q = 0 stresses of the edges with x face
@@ -308,14 +338,15 @@ __device__ inline void les_flux_cell(const Dims& d, const LesArgs<T>& a, int i, 
       const T t1 = T(2) * N(0, 0, 0) * (W(0, 0, 1) - W(0, 0, 0)) * rzc;
       g = (txz(1, 0) - txz(0, 0)) * rdx + (tyz(1, 0) - tyz(0, 0)) * rdy + (t1 - t0) * rzf0;
     }
-    glb(a.gc[2])[c] = g;
+    out[2] = g;
   }
   // tracers: d_i(kappa d_i c), face diffusivities the mean of two centres
-  for (int q = 0; q < a.ntr; ++q) {
-    const int fk = a.kap[q] ? 4 + a.ntr + q : 3;
+#pragma unroll
+  for (int q = 0; q < NTR; ++q) {
+    const int fk = AMD ? 4 + NTR + q : 3;
     auto C = [&](int di, int dj, int dk) { return r(4 + q, di, dj, dk); };
     auto K = [&](int di, int dj, int dk) { return r(fk, di, dj, dk); };
-    const T s = a.kap[q] ? T(1) : a.rpr;
+    const T s = AMD ? T(1) : a.rpr;
     const T c0 = C(0, 0, 0), k0 = K(0, 0, 0);
     const T fxm = T(0.5) * (K(-1, 0, 0) + k0) * (c0 - C(-1, 0, 0)) * rdx;
     const T fxp = T(0.5) * (k0 + K(1, 0, 0)) * (C(1, 0, 0) - c0) * rdx;
@@ -323,45 +354,81 @@ __device__ inline void les_flux_cell(const Dims& d, const LesArgs<T>& a, int i, 
     const T fyp = T(0.5) * (k0 + K(0, 1, 0)) * (C(0, 1, 0) - c0) * rdy;
     const T fzm = wall0 ? T(0) : T(0.5) * (K(0, 0, -1) + k0) * (c0 - C(0, 0, -1)) * rzf0;
     const T fzp = wall1 ? T(0) : T(0.5) * (k0 + K(0, 0, 1)) * (C(0, 0, 1) - c0) * rzf1;
-    glb(a.gc[3 + q])[c] = s * ((fxp - fxm) * rdx + (fyp - fym) * rdy + (fzp - fzm) * rzc);
+    out[3 + q] = s * ((fxp - fxm) * rdx + (fyp - fym) * rdy + (fzp - fzm) * rzc);
   }
 }
 
-template <class T, int TX, int TY>
-__global__ void __launch_bounds__(TX * TY) les_flux_kernel(Dims d, LesArgs<T> a) {
-  const T* fld[4 + 2 * OC_MAX_TRACERS] = {a.u, a.v, a.w, a.nu};
-  int nf = 4;
-  for (int q = 0; q < a.ntr; ++q) fld[nf++] = a.tr[q];
-  if (a.kap[0])
-    for (int q = 0; q < a.ntr; ++q) fld[nf++] = a.kap[q];
-  les_march<T, TX, TY, 4 + 2 * OC_MAX_TRACERS>(
-      d, fld, nf, [&](int i, int j, int k, const auto& r) { les_flux_cell<T>(d, a, i, j, k, r); });
+template <class T, int NTR, bool AMD, int TX, int TY>
+__global__ void __launch_bounds__(TX * TY) les_flux_kernel(Dims d, LesArgs<T> a, int kc) {
+  constexpr int NF = 4 + (AMD ? 2 : 1) * NTR;
+  const T* fld[NF];
+  fld[0] = a.u;
+  fld[1] = a.v;
+  fld[2] = a.w;
+  fld[3] = a.nu;
+#pragma unroll
+  for (int q = 0; q < NTR; ++q) {
+    fld[4 + q] = a.tr[q];
+    if (AMD) fld[4 + NTR + q] = a.kap[q];
+  }
+  les_march<T, TX, TY, NF, 3 + NTR>(
+      d, fld, kc,
+      [&](int k, const auto& r, T* out) { les_flux_cell<T, NTR, AMD>(d, a, k, r, out); },
+      [&](int i, int j, int k, const T* out) {
+        const long c = pidx(d, i, j, k);
+#pragma unroll
+        for (int f = 0; f < 3 + NTR; ++f) glb(a.gc[f])[c] = out[f];
+      });
 }
 
 }  // namespace
 
-template <class T, int TX, int TY>
+template <class T, int NTR, int TX, int TY>
 hipError_t launch_les_tiles(const Dims& d, const LesArgs<T>& a, int kind, hipStream_t s) {
-  const dim3 grid((d.nx / TX) * (d.ny / TY) * ((d.nz + LES_KC - 1) / LES_KC));
-  if (kind == OC_LES_SMAGORINSKY)
-    hipLaunchKernelGGL((les_viscosity_kernel<T, OC_LES_SMAGORINSKY, TX, TY>), grid, dim3(TX * TY), 0,
-                       s, d, a);
-  else if (kind == OC_LES_AMD)
-    hipLaunchKernelGGL((les_viscosity_kernel<T, OC_LES_AMD, TX, TY>), grid, dim3(TX * TY), 0, s, d,
-                       a);
-  else
+  const int tiles = (d.nx / TX) * (d.ny / TY);
+  // Levels per workgroup.  A chunk copies two levels more than it computes,
+  // and a workgroup's levels run one after the other, so a chunk is as long as
+  // 2048 workgroups allow (8 per CU), within 2..16.  One substage with at most
+  // 8, 16 and 32 levels: 256x256x128 FP32 Smagorinsky-Lilly 201, 200, 193 us,
+  // AMD (its 8 fields' rings leave 2 workgroups per CU) 248, 246, 267 us; 64^3
+  // with 2 levels 15.5 us, with the fixed 16 of before 75 us.
+  const int kc = std::min(d.nz, std::max(2, (int)std::min(16L, (long)d.nz * tiles / 2048)));
+  const dim3 grid(tiles * ((d.nz + kc - 1) / kc)), nt(TX * TY);
+  if (kind == OC_LES_SMAGORINSKY) {
+    if (a.buoyancy)
+      hipLaunchKernelGGL((les_viscosity_kernel<T, OC_LES_SMAGORINSKY, 2, TX, TY>), grid, nt, 0, s, d,
+                         a, kc);
+    else
+      hipLaunchKernelGGL((les_viscosity_kernel<T, OC_LES_SMAGORINSKY, 0, TX, TY>), grid, nt, 0, s, d,
+                         a, kc);
+    hipLaunchKernelGGL((les_flux_kernel<T, NTR, false, TX, TY>), grid, nt, 0, s, d, a, kc);
+  } else if (kind == OC_LES_AMD) {
+    hipLaunchKernelGGL((les_viscosity_kernel<T, OC_LES_AMD, NTR, TX, TY>), grid, nt, 0, s, d, a, kc);
+    hipLaunchKernelGGL((les_flux_kernel<T, NTR, true, TX, TY>), grid, nt, 0, s, d, a, kc);
+  } else {
     return hipErrorInvalidValue;
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((les_flux_kernel<T, TX, TY>), grid, dim3(TX * TY), 0, s, d, a);
+  }
   return hipGetLastError();
+}
+
+template <class T, int TX, int TY>
+hipError_t launch_les_tracers(const Dims& d, const LesArgs<T>& a, int kind, hipStream_t s) {
+  switch (a.ntr) {
+    case 1: return launch_les_tiles<T, 1, TX, TY>(d, a, kind, s);
+    case 2: return launch_les_tiles<T, 2, TX, TY>(d, a, kind, s);
+    case 3: return launch_les_tiles<T, 3, TX, TY>(d, a, kind, s);
+    default: return launch_les_tiles<T, 4, TX, TY>(d, a, kind, s);
+  }
 }
 
 template <class T>
 hipError_t launch_les(const Dims& d, const LesArgs<T>& a, int kind, hipStream_t s) {
-  if (a.ntr < 1 || a.ntr > OC_MAX_TRACERS || d.h < 1) return hipErrorInvalidValue;
-  if (d.nx % 32 == 0 && d.ny % 8 == 0) return launch_les_tiles<T, 32, 8>(d, a, kind, s);
-  if (d.nx % 8 == 0 && d.ny % 8 == 0) return launch_les_tiles<T, 8, 8>(d, a, kind, s);
+  // a field's byte offsets take 32 bits (the model's layout ensures it)
+  if (a.ntr < 1 || a.ntr > OC_MAX_TRACERS || d.h < 1 ||
+      (uint64_t)padded_elems(d) * sizeof(T) > 0xFFFFFFFFull)
+    return hipErrorInvalidValue;
+  if (d.nx % 32 == 0 && d.ny % 8 == 0) return launch_les_tracers<T, 32, 8>(d, a, kind, s);
+  if (d.nx % 8 == 0 && d.ny % 8 == 0) return launch_les_tracers<T, 8, 8>(d, a, kind, s);
   return hipErrorInvalidValue;
 }
 

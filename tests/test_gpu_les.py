@@ -82,6 +82,32 @@ def test_les_rk3_parity(gpu_lib, les, precision):
         assert err <= TOL[precision], (les, name, err)
 
 
+@pytest.mark.parametrize("les,n,tracers,precision", [
+    ("smagorinsky", (8, 8, 9), ("c",), "fp64"),
+    ("smagorinsky", (32, 8, 9), ("T", "S", "c"), "fp32"),
+    ("amd", (16, 16, 9), ("T", "S", "c", "e"), "fp64"),
+    ("amd", (32, 16, 33), ("c",), "fp32"),
+    ("smagorinsky", (128, 128, 97), ("T", "S"), "fp32"),
+    ("amd", (128, 128, 97), ("T", "S", "c"), "fp64")])
+def test_les_tracer_counts_and_chunks(gpu_lib, les, n, tracers, precision):
+    """Every tracer count, with and without buoyancy, on both tile sizes, with
+    chunks of two and three levels whose last one holds a single level."""
+    ph, _ = _case(les, n=n, stretched=True)
+    ph.tracers, ph.buoyancy = tracers, tracers[0] == "T"
+    if not ph.buoyancy:
+        ph.top_flux = {}
+    s = inputs.random_state(ph, seed=12, vel=5e-2, tracer_scale=0.05,
+                            tracer_means=(20.0, 35.0, 1.0, 2.0)[:len(tracers)])
+    s = _prep(s, precision)
+    m = gpu_lib.Model(ph, precision)
+    m.set_states(s)
+    m.tendencies()
+    G = td.tendencies(timestep.make_state(s, ph), ph)
+    for name in m.fields:
+        err = rel_l2(m.get_tendency(name), G[name])
+        assert err <= TOL[precision] * (10 if precision == "fp32" else 1), (les, n, name, err)
+
+
 def test_les_restrictions(gpu_lib):
     ph, s = _case("amd")
     m = gpu_lib.Model(ph, "fp32")
