@@ -89,7 +89,24 @@ int vertical_factors_len(int nz) { return 5 * nz + 2 * VCH; }
 
 namespace {
 
-template <class T>
+// A uniform value the compiler can derive nothing from (nor hoist what follows
+// from it out of a loop).
+template <class P>
+__device__ inline P opaque(P p) {
+  asm volatile("" : "+s"(p));
+  return p;
+}
+
+// CM: levels per chunk at most, which are the column's registers.  Memory
+// bound (67 us at 5.2 TB/s for the 5 fields of 256x256x128 FP32, each read
+// and written once): what counts is the waves in flight, so the registers are
+// held to the column itself (the level addresses are uniform, 32 bits per
+// lane), and the stores, so the halo images are not tested for level by level.
+// 5 fields, with every chunk of 32 levels at most and the images tested at
+// each level, and now: 256x256x128 FP32 149 -> 91 us, 256x256x200 FP32
+// 199 -> 168, 128x128x64 FP64 37.5 -> 24, 128x128x256 FP64 95 -> 87, 64x64x32
+// FP32 15 -> 9.6.  (16 chunks instead of 8: 123 us for the first.)
+template <class T, int CM>
 __global__ void __launch_bounds__(64 * VCH) vimplicit_kernel(Dims d, VImplicitArgs<T> a) {
   __shared__ T endv[VCH][64];
   __shared__ T startv[VCH][64];
@@ -121,15 +138,27 @@ __global__ void __launch_bounds__(64 * VCH) vimplicit_kernel(Dims d, VImplicitAr
   const int q0 = c * C;
   const int q1 = min(q0 + C, n);
   const long sz = d.sz;
-  T* __restrict__ base = f + pidx(d, i, j, k0);
-  T x[VCMAX];
+  const int H = d.h;
+  const uint32_t own = (uint32_t)((j + H) * (int)d.sy + i + H);
+  T x[CM];
+  {
+    const T* lv = f + (long)(k0 + q0 + H) * sz;
 #pragma unroll
-  for (int r = 0; r < VCMAX; ++r)
-    if (valid && q0 + r < q1) x[r] = base[(long)(q0 + r) * sz];
+    for (int r = 0; r < CM; ++r) {
+      if (q0 + r < q1) x[r] = lv[own];
+      lv += sz;
+    }
+  }
+  T pe[VCH], qs[VCH];
+#pragma unroll
+  for (int cc = 0; cc < VCH; ++cc) {
+    pe[cc] = PE[cc];
+    qs[cc] = QS[cc];
+  }
   // forward recurrence within the chunk, from zero
   T dl = T(0);
 #pragma unroll
-  for (int r = 0; r < VCMAX; ++r) {
+  for (int r = 0; r < CM; ++r) {
     const int q = q0 + r;
     if (q < q1) {
       dl = A[q] * dl + I[q] * x[r];
@@ -139,11 +168,17 @@ __global__ void __launch_bounds__(64 * VCH) vimplicit_kernel(Dims d, VImplicitAr
   endv[c][lane] = dl;
   __syncthreads();
   T din = T(0);
-  for (int cc = 0; cc < c; ++cc) din = PE[cc] * din + endv[cc][lane];
+  {
+    T ev[VCH];
+#pragma unroll
+    for (int cc = 0; cc < VCH - 1; ++cc) ev[cc] = endv[cc][lane];
+#pragma unroll
+    for (int cc = 0; cc < VCH - 1; ++cc) din = cc < c ? pe[cc] * din + ev[cc] : din;
+  }
   // backward recurrence within the chunk (after the forward correction)
   T xl = T(0);
 #pragma unroll
-  for (int r = VCMAX - 1; r >= 0; --r) {
+  for (int r = CM - 1; r >= 0; --r) {
     const int q = q0 + r;
     if (q < q1) {
       xl = (x[r] + P[q] * din) + B[q] * xl;
@@ -153,45 +188,52 @@ __global__ void __launch_bounds__(64 * VCH) vimplicit_kernel(Dims d, VImplicitAr
   startv[c][lane] = xl;
   __syncthreads();
   T xin = T(0);
-  for (int cc = VCH - 1; cc > c; --cc) xin = QS[cc] * xin + startv[cc][lane];
+  {
+    T sv[VCH];
+#pragma unroll
+    for (int cc = VCH - 1; cc > 0; --cc) sv[cc] = startv[cc][lane];
+#pragma unroll
+    for (int cc = VCH - 1; cc > 0; --cc) xin = cc > c ? qs[cc] * xin + sv[cc] : xin;
+  }
   if (!valid) return;
 #pragma unroll
-  for (int r = 0; r < VCMAX; ++r) x[r] += Q[min(q0 + r, n - 1)] * xin;
-  // plain stores, plus the periodic x / y images of the h columns next to
-  // each side (per-lane offsets, masked off everywhere else; a column of an
-  // axis shorter than 2H has an image at both ends)
-  const long sy = d.sy;
-  const int H = d.h;
-  const long oxa = (i < H) ? d.nx : 0, oxb = (i >= d.nx - H) ? -(long)d.nx : 0;
-  const long oya = (j < H) ? d.ny * sy : 0, oyb = (j >= d.ny - H) ? -(long)d.ny * sy : 0;
+  for (int r = 0; r < CM; ++r) x[r] += Q[min(q0 + r, n - 1)] * xin;
+  // The column, then its periodic x / y images (of the h columns next to each
+  // side; one at both ends of an axis shorter than 2H): image m is shifted by
+  // a length of x (m % 3 = 1 up, 2 down) and of y (m / 3).  A combination that
+  // no lane has is passed over whole, so the interior pays for it once per
+  // column and not once per level.
+  const bool edge = k0 + q0 <= H || k0 + q1 >= d.nz - H;   // levels with mirror images
+#pragma unroll 1
+  for (int m = 0; m < 9; ++m) {
+    const int mx = m % 3, my = m / 3;
+    const bool has = (mx == 0 || (mx == 1 ? i < H : i >= d.nx - H)) &&
+                     (my == 0 || (my == 1 ? j < H : j >= d.ny - H));
+    if (!has) continue;
+    const uint32_t at = own + (uint32_t)((mx == 1 ? d.nx : mx == 2 ? -d.nx : 0) +
+                                         (my == 1 ? d.ny : my == 2 ? -d.ny : 0) * (int)d.sy);
+    // (opaque: the level addresses and signed values are formed here instead
+    // of being kept for all levels across the combinations, which spills)
+    const int kb = opaque(k0 + q0), nl = opaque(q1 - q0), odd = opaque(wface);
+    T* lv = f + (long)(kb + H) * sz;
 #pragma unroll
-  for (int r = 0; r < VCMAX; ++r) {
-    const int q = q0 + r;
-    if (q < q1) {
-      T* p = base + (long)q * sz;
-      p[0] = x[r];
-      if (oxa) p[oxa] = x[r];
-      if (oxb) p[oxb] = x[r];
-      if (oya) {
-        p[oya] = x[r];
-        if (oxa) p[oya + oxa] = x[r];
-        if (oxb) p[oya + oxb] = x[r];
-      }
-      if (oyb) {
-        p[oyb] = x[r];
-        if (oxa) p[oyb + oxa] = x[r];
-        if (oxb) p[oyb + oxb] = x[r];
-      }
+    for (int r = 0; r < CM; ++r) {
+      if (r < nl) lv[at] = x[r];
+      lv += sz;
     }
-  }
-  // the mirror images of the levels next to the walls (first and last
-  // chunks only; uniform across the wavefront)
-  if (k0 + q0 <= H || k0 + q1 >= d.nz - H) {
+    if (edge) {
+      // mirror images of the levels next to the walls: even for a centred
+      // field, odd about the wall faces for w
 #pragma unroll
-    for (int r = 0; r < VCMAX; ++r) {
-      const int q = q0 + r, k = k0 + q;
-      if (q < q1 && (k <= H || k >= d.nz - H))
-        store_with_images(f, d, i, j, k, x[r], wface != 0);
+      for (int r = 0; r < CM; ++r) {
+        const int k = kb + r;
+        if (r < nl) {
+          const T v = odd ? -x[r] : x[r];
+          const int lo = wface ? -k : -1 - k, hi = wface ? 2 * d.nz - k : 2 * d.nz - 1 - k;
+          if (lo >= -H) f[(long)(lo + H) * sz + at] = v;
+          if (hi < d.nz + H) f[(long)(hi + H) * sz + at] = v;
+        }
+      }
     }
   }
 }
@@ -203,8 +245,19 @@ hipError_t launch_vertical_implicit(const Dims& d, const VImplicitArgs<T>& a, in
                                     hipStream_t s) {
   if (!d.zb || d.nz > VCH * VCMAX || nfields < 1 || nfields > MAXF) return hipErrorInvalidValue;
   const int cols = d.nx * d.ny;
-  hipLaunchKernelGGL(vimplicit_kernel<T>, dim3((cols + 63) / 64, nfields), dim3(64 * VCH), 0, s,
-                     d, a);
+  const dim3 grid((cols + 63) / 64, nfields), nt(64 * VCH);
+  // by the levels of a chunk: the larger bounds hold more registers (18, 22,
+  // 30 and 58 in FP32) and issue the loops of empty levels, 149 against 108 us
+  // at 256x256x128 with 32 in place of 16
+  const int C = vertical_chunk(d.nz);
+  if (C <= 4)
+    hipLaunchKernelGGL((vimplicit_kernel<T, 4>), grid, nt, 0, s, d, a);
+  else if (C <= 8)
+    hipLaunchKernelGGL((vimplicit_kernel<T, 8>), grid, nt, 0, s, d, a);
+  else if (C <= 16)
+    hipLaunchKernelGGL((vimplicit_kernel<T, 16>), grid, nt, 0, s, d, a);
+  else
+    hipLaunchKernelGGL((vimplicit_kernel<T, 32>), grid, nt, 0, s, d, a);
   return hipGetLastError();
 }
 

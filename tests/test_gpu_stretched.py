@@ -105,6 +105,31 @@ def test_implicit_vertical_diffusion_parity(gpu_lib, case, precision):
 
 
 @pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("n,advection", [((8, 8, 9), "weno9z"), ((16, 8, 33), "weno5z"),
+                                         ((32, 8, 100), "weno5z"), ((8, 16, 130), "weno7z"),
+                                         ((8, 8, 256), "weno5z")])
+def test_implicit_column_lengths(gpu_lib, n, advection, precision):
+    """Columns of every chunk length (2, 5, 13, 17 and 32 levels; some with an
+    empty last chunk), and axes as short as their halos, whose columns have
+    images at both ends: the tendencies that follow read those images."""
+    ph = _phys(n, 1.5, True)
+    ph.advection = advection
+    s = _prep(_state(ph, 6), precision)
+    m = gpu_lib.Model(ph, precision)
+    m.set_states(s)
+    m.implicit_vertical_diffusion(0.8)
+    for name in m.fields:
+        ref = implicit.implicit_diffusion(name, s[name], ph, 0.8)
+        err = rel_l2(m.get_state(name), ref)
+        assert err <= TOL[precision], (n, name, err)
+    m.tendencies()
+    G = td.tendencies(timestep.make_state({n: m.get_state(n) for n in m.fields}, ph), ph)
+    for name in ("u", "v", "w", "T"):
+        err = rel_l2(m.get_tendency(name), G[name])
+        assert err <= TOL[precision] * (10 if precision == "fp32" else 1), (n, name, err)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
 @pytest.mark.parametrize("case", list(CASES))
 def test_stretched_rk3_step_parity(gpu_lib, case, precision):
     ph = CASES[case]()
