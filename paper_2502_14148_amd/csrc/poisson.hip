@@ -12,8 +12,9 @@
 //      eigenvalue, and the inverse transform, all in LDS; on a stretched z a
 //      tridiagonal solve per (kx, ky) mode instead;
 //   4. y: inverse FFT;
-//   5. x: complex-to-real inverse FFT -> p.
-// Then a projection kernel applies u -= dt_eff grad p.
+//   5. x: complex-to-real inverse FFT, fused with the projection
+//      u -= dt_eff grad p (p itself is formed from the x-spectrum when asked
+//      for).
 //
 // Transforms are radix-8/4/2/3 Stockham passes in LDS, one radix-R butterfly
 // per thread per pass, twiddles from FP64 tables.
@@ -706,16 +707,82 @@ __global__ void __launch_bounds__(NT) inv_x_kernel(Dims d, SpecBufs sb) {
 // ---------------------------------------------------------------------------
 
 // Lines per level and levels per transform of the fused pass: four lines
-// (7 rows) at length 256, about 512 / N at the shorter lengths, which keeps
-// a thread's cells per level at four or fewer and its registers near 150
-// (three waves per SIMD).  Length 96 transforms two levels at once: with
-// one, fewer than half of the threads have a first-pass butterfly, and two
-// cost no resident wave there (measured in the 48-member ensemble: 223 ->
-// 200 us per launch; at 128 and 64 the second level costs a wave and time).
+// (7 rows) at length 256, 512 / N at the shorter lengths, which keeps a
+// thread's cells per level at four or fewer and its registers under 128 there
+// (four waves per SIMD, FP32).  Length 96 takes four lines of two levels: its
+// first pass has 24 butterflies a line and gets 32 lanes.  Whole solves with
+// these, with half the lines, and with half the lines and twice the levels:
+// 128^3 FP32 71.6, 75.0 (twice the levels alone), 70.6 us; 96x64x128 FP64
+// 46.4, 47.3 (one level), 47.9; 64^3 29.5, 29.8, 28.7.
+//
+// A line belongs to one wavefront throughout its passes (TPL lanes each), so
+// the passes need no barrier; the lines are double buffered, which leaves one
+// barrier per iteration.  The kernel is memory bound at 256^3 (538 MB: 104 us
+// at 5.2 TB/s, 120 us measured, 133 us with a barrier around every pass, the
+// image tests at every store and 64-bit offsets per cell) and bound by the
+// latency of an iteration on small grids, where registers decide: whole solves
+// 128^3 FP32 75.6 -> 71.6 us, 96^3 FP32 52.9 -> 47.6, 96x64x128 FP64 48 ->
+// 46.4, 256^3 FP32 328 -> 314.
 template <int N> struct PXCfg {
-  static constexpr int L = N >= 256 ? 4 : (512 / N > 2 ? 512 / N : 2);
+  static constexpr int L = N >= 256 || N == 96 ? 4 : 512 / N;
   static constexpr int LV = N == 96 ? 2 : 1;
+  // threads of a line, all of one wavefront
+  static constexpr int TPL = N == 96 ? 32 : N / 4;
 };
+
+// ld2 from a uniform address and a 32-bit index.
+__device__ inline double2 ld2u(const double2* p, uint32_t i) {
+  const oc_dbl2 v = ((const __attribute__((address_space(1))) oc_dbl2*)p)[i];
+  return make_double2(v.x, v.y);
+}
+
+// What one lane wrote to LDS is seen by the other lanes of its wavefront past
+// this point (LDS serves a wavefront's accesses in order; this keeps the
+// compiler from reordering them).
+__device__ inline void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// The Stockham passes from sub-transform length NS on of one line of length N
+// by TPL lanes of one wavefront (t: the lane's index among them).
+template <int N, int NS, int TPL, int DIR>
+__device__ inline void fft_wave_line(double2* line, int t, const double2* tw) {
+  if constexpr (NS < N) {
+    constexpr int R = pass_radix<N / NS, 4>(), M = N / R, BPT = (M + TPL - 1) / TPL;
+    double2 v[BPT][R];
+    wave_sync();
+#pragma unroll
+    for (int q = 0; q < BPT; ++q) {
+      const int jj = t + q * TPL;
+      if (M % TPL == 0 || jj < M) {
+        const int k = jj % NS;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          double2 x = line[jj + r * M];
+          if (r > 0) {
+            double2 w = tw[(r * k) * (N / (NS * R))];
+            if (DIR > 0) w = cconj(w);
+            x = cmul(x, w);
+          }
+          v[q][r] = x;
+        }
+        dft<R, DIR>(v[q]);
+      }
+    }
+    wave_sync();
+#pragma unroll
+    for (int q = 0; q < BPT; ++q) {
+      const int jj = t + q * TPL;
+      if (M % TPL == 0 || jj < M) {
+        const int e = (jj / NS) * NS * R + jj % NS;
+#pragma unroll
+        for (int r = 0; r < R; ++r) line[e + r * NS] = v[q][r];
+      }
+    }
+    fft_wave_line<N, NS * R, TPL, DIR>(line, t, tw);
+  }
+}
 
 // MASK (immersed boundary): velocities on closed faces are set to 0.
 template <class T, int N, bool MASK>
@@ -740,8 +807,8 @@ __global__ void __launch_bounds__(NT) inv_x_project_kernel(
   }
   constexpr int L = PXCfg<N>::L, LV = PXCfg<N>::LV, LT = L * LV;
   constexpr int RB = 2 * L - 1, CELLS = RB * N;
-  constexpr int R0 = pass_radix<N, 4>();
-  __shared__ double2 buf[LT * N];
+  constexpr int R0 = pass_radix<N, 4>(), TPL = PXCfg<N>::TPL;
+  __shared__ double2 bufs[2][LT * N];
   __shared__ double2 tws[N];
   stage_twiddles<N>(tws, sb.twx);
   const int j0 = (colm % nblk) * rb;   // rb <= RB rows per block
@@ -762,21 +829,26 @@ __global__ void __launch_bounds__(NT) inv_x_project_kernel(
   // iteration's loads are issued right after this one's first pass, so they
   // travel while this one is transformed and projected.
   constexpr int M0 = N / R0;
-  static_assert(LT * M0 <= NT, "one first-pass butterfly per thread");
-  const int bl = (int)threadIdx.x / M0, bj = (int)threadIdx.x % M0;
-  const bool bact = (int)threadIdx.x < LT * M0;
-  const int bv = bl / L, blv = bl % L;   // the line's level in the iteration, its index
+  static_assert(LT * TPL <= NT && M0 <= TPL && 64 % TPL == 0,
+                "one first-pass butterfly per thread, a line within a wavefront");
+  const int tid = (int)threadIdx.x, bl = tid / TPL, bj = tid % TPL;
+  const bool bact = bl < LT && (M0 == TPL || bj < M0);
+  // the line's level in the iteration (one per wavefront) and its index there
+  static_assert(R0 == 4 && (LV == 1 || L * TPL % 64 == 0), "a level's lines fill wavefronts");
+  const int bv = LV == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid) / (L * TPL), blv = bl % L;
   const int ja = (blv == 0 && j0 == 0) ? ny - 1 : j0 - 1 + 2 * blv, jb = j0 + 2 * blv;
   const bool has_a = bact && (blv == 0 || ja < jend), has_b = bact && jb < jend;
+  const uint32_t ma = (uint32_t)(ja * nxp), mb = (uint32_t)(jb * nxp);
+  double2* buf = bufs[0];
   double2 fa[R0], fb[R0];
   auto fetch = [&](int s) {
     const bool ok = s + bv < ns;
-    const long lvl = (long)(ok ? lev(s + bv) : 0) * ny;
+    const double2* lvl = sb.spec + (long)(ok ? lev(s + bv) : 0) * ny * nxp;
 #pragma unroll
     for (int r = 0; r < R0; ++r) {
-      const int n = bj + r * M0, m = n <= N / 2 ? n : N - n;
-      fa[r] = (ok && has_a) ? ld2(sb.spec, (lvl + ja) * nxp + m) : make_double2(0.0, 0.0);
-      fb[r] = (ok && has_b) ? ld2(sb.spec, (lvl + jb) * nxp + m) : make_double2(0.0, 0.0);
+      const uint32_t m = (uint32_t)(r < 2 ? bj + r * M0 : N - r * M0 - bj);
+      fa[r] = (ok && has_a) ? ld2u(lvl, ma + m) : make_double2(0.0, 0.0);
+      fb[r] = (ok && has_b) ? ld2u(lvl, mb + m) : make_double2(0.0, 0.0);
     }
   };
   auto first = [&]() {
@@ -791,82 +863,116 @@ __global__ void __launch_bounds__(NT) inv_x_project_kernel(
 #pragma unroll
       for (int r = 0; r < R0; ++r) buf[bl * N + bj * R0 + r] = x[r];
     }
-    __syncthreads();
   };
-  auto rest = [&]() { fft_lines<N, R0, LT, NT, 1, false>(buf, N, 1, tws); };
-  // p of the iteration's level vv at row r of the block (r = -1: the row
-  // below) and column i
-  auto pat = [&](int vv, int r, int i) -> double {
-    const double2 z = buf[(vv * L + ((r + 1) >> 1)) * N + i];
-    return (r & 1) ? z.x : z.y;
+  auto rest = [&]() {
+    if (bl < LT) fft_wave_line<N, R0, TPL, 1>(buf + bl * N, bj, tws);
   };
-  // a thread's cells of a level: c = tid + q NT
-  constexpr int CPL = (CELLS + NT - 1) / NT;
+  // A thread's cells of a level are c = tid + q NT, rows c / N of the block.
+  // Where NT is a multiple of N they are one column, NT / N rows apart, and
+  // every offset is that of the first cell plus one that is uniform (state)
+  // or constant (LDS).
+  constexpr int CPL = (CELLS + NT - 1) / NT, RS = NT / N;
+  constexpr bool COL = NT % N == 0;
+  const int r0 = NT == N ? 0 : tid / N, i0 = NT == N ? tid : tid % N;
+  const int nrow = jend - j0;
+  auto row = [&](int q) { return COL ? q * RS + r0 : (tid + q * NT) / N; };
+  auto col = [&](int q) { return COL ? i0 : (tid + q * NT) % N; };
+  auto rows_up = [&](int q) -> long { return COL ? (long)q * RS * d.sy : 0; };   // uniform
+  uint32_t cell[COL ? 1 : CPL];
+#pragma unroll
+  for (int q = 0; q < (COL ? 1 : CPL); ++q)
+    cell[q] = (uint32_t)((j0 + row(q) + d.h) * (int)d.sy + col(q) + d.h);
+  // p of level vv of the iteration at row r of the block (r = -1: the row
+  // below) and column i: row 2l - 1 is the real part of line l, row 2l the
+  // imaginary part
+  auto at = [&](int r, int i) { return 2 * (((r + 1) >> 1) * N + i) + (~r & 1); };
+  auto pat = [&](int vv, int q, int dr, int i) -> double {
+    const int o = COL && RS % 2 == 0 ? q * RS * N + at(r0 + dr, i) : at(row(q) + dr, i);
+    return ((const double*)buf)[vv * 2 * L * N + o];
+  };
   double pb[CPL];   // p of the level below the iteration's first level
   fetch(0);
+  __syncthreads();   // the twiddles
   for (int s = 0; s < ns; s += LV) {
+    buf = bufs[(s / LV) & 1];
     // the velocities of the projected levels, in flight during the transform
     T uu[LV][CPL], vv[LV][CPL], ww[LV][CPL];
 #pragma unroll
     for (int lv = 0; lv < LV; ++lv) {
       const int sv = s + lv;
       if (sv < ns && !(below && sv == 0)) {
-        const int k = lev(sv);
+        const long kz = (long)(lev(sv) + d.h) * d.sz;
 #pragma unroll
-        for (int q = 0; q < CPL; ++q) {
-          const int c = threadIdx.x + q * NT, j = j0 + c / N;
-          if ((CELLS % NT == 0 || c < CELLS) && j < jend) {
-            const long o = pidx(d, c % N, j, k);
-            uu[lv][q] = gu[o];
-            vv[lv][q] = gv[o];
-            ww[lv][q] = gw[o];
+        for (int q = 0; q < CPL; ++q)
+          if (row(q) < nrow) {
+            const long up = kz + rows_up(q);
+            const uint32_t o = cell[COL ? 0 : q];
+            uu[lv][q] = (gu + up)[o];
+            vv[lv][q] = (gv + up)[o];
+            ww[lv][q] = (gw + up)[o];
           }
-        }
       }
     }
-    if (s > 0) __syncthreads();   // the lines of the previous iteration are read
     first();
     if (s + LV < ns) fetch(s + LV);
     rest();
+    __syncthreads();
 #pragma unroll
     for (int lv = 0; lv < LV; ++lv) {
       const int sv = s + lv;
       if (sv < ns && !(below && sv == 0)) {
-        const int k = lev(sv);
+        const int k = lev(sv), H = d.h;
+        const long kz = (long)(k + H) * d.sz;
         const double rz = rdzf[k];
         const bool wk = !d.zb || k > 0;
+        const bool edge_k = k <= H || k >= d.nz - H;   // levels with images in z
 #pragma unroll
         for (int q = 0; q < CPL; ++q) {
-          const int c = threadIdx.x + q * NT;
-          const int r = c / N, i = c % N, j = j0 + r;
-          if ((CELLS % NT == 0 || c < CELLS) && j < jend) {
-            const double p0 = pat(lv, r, i);
-            const double pxm = pat(lv, r, i == 0 ? N - 1 : i - 1);
-            const double pym = pat(lv, r - 1, i);
-            const double pzm = lv == 0 ? pb[q] : pat(lv - 1, r, i);
+          const int i = col(q), j = j0 + row(q);
+          if (row(q) < nrow) {
+            const double p0 = pat(lv, q, 0, i);
+            const double pxm = pat(lv, q, 0, i == 0 ? N - 1 : i - 1);
+            const double pym = pat(lv, q, -1, i);
+            const double pzm = lv == 0 ? pb[q] : pat(lv - 1, q, 0, i);
             T un = (T)((double)uu[lv][q] - scale * (p0 - pxm) * rdx);
             T vn = (T)((double)vv[lv][q] - scale * (p0 - pym) * rdy);
             T wn = wk ? (T)((double)ww[lv][q] - scale * (p0 - pzm) * rz) : ww[lv][q];
+            const long up = kz + rows_up(q);
+            const uint32_t o = cell[COL ? 0 : q];
             if (MASK) {
-              const auto gm = glb(mask) + pidx(d, i, j, k);
-              const T m0 = gm[0];
-              un = un * (m0 * gm[-1]);
-              vn = vn * (m0 * gm[-d.sy]);
-              if (wk) wn = wn * (m0 * gm[-d.sz]);
+              const auto gm = glb(mask) + up;
+              const T m0 = gm[o];
+              un = un * (m0 * (gm - 1)[o]);
+              vn = vn * (m0 * (gm - d.sy)[o]);
+              if (wk) wn = wn * (m0 * (gm - d.sz)[o]);
             }
-            store_with_images(u, d, i, j, k, un, false);
-            store_with_images(v, d, i, j, k, vn, false);
-            store_with_images(w, d, i, j, k, wn, true);
+            const auto pu = gu + up, pv = gv + up, pw = gw + up;
+            pu[o] = un;
+            pv[o] = vn;
+            pw[o] = wn;
+            // halo images: in x alone but for the few rows and levels next to
+            // an end of theirs
+            if (edge_k || j < H || j >= ny - H) {
+              // (opaque: the offsets of these few images are formed here, not
+              // kept in registers across the levels: 156 -> 127 of them at
+              // length 128.  At 256 that gains no wave and costs 1 %.)
+              int io = i, jo = j;
+              if (N < 256) asm volatile("" : "+v"(io), "+v"(jo));
+              store_with_images(u, d, io, jo, k, un, false, false);
+              store_with_images(v, d, io, jo, k, vn, false, false);
+              store_with_images(w, d, io, jo, k, wn, true, false);
+            } else {
+              if (i < H) { (pu + N)[o] = un; (pv + N)[o] = vn; (pw + N)[o] = wn; }
+              if (i >= N - H) { (pu - N)[o] = un; (pv - N)[o] = vn; (pw - N)[o] = wn; }
+            }
           }
         }
       }
     }
     // p of the iteration's last level, below the next iteration's first
 #pragma unroll
-    for (int q = 0; q < CPL; ++q) {
-      const int c = threadIdx.x + q * NT;
-      if (CELLS % NT == 0 || c < CELLS) pb[q] = pat(LV - 1, c / N, c % N);
-    }
+    for (int q = 0; q < CPL; ++q)
+      if (row(q) < nrow) pb[q] = pat(LV - 1, q, 0, col(q));
   }
 }
 

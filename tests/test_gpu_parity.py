@@ -281,3 +281,33 @@ def test_tendency_parity_by_levels_per_workgroup(gpu_lib, n, precision):
     for name in m.fields:
         err = rel_l2(m.get_tendency(name), G[name])
         assert err <= TOL[precision], (n, name, err)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("n,advection", [((8, 8, 8), "weno9z"), ((16, 96, 8), "weno5z"),
+                                         ((32, 64, 16), "weno5z"), ((64, 16, 32), "weno7z"),
+                                         ((96, 32, 16), "weno5z"), ((128, 8, 32), "weno5z"),
+                                         ((256, 16, 8), "weno5z")])
+def test_projection_row_blocks(gpu_lib, n, advection, precision):
+    """The projection at every transform length, with whole and short row
+    blocks, axes shorter than two halos, and the halo images it writes: a
+    tendency evaluation reads them."""
+    ph = small_convection(*n)
+    ph.advection = advection
+    s = _prep(inputs.random_state(ph, seed=41, vel=0.1, divergence_free=False,
+                                  tracer_means=(ph.t_ref, ph.s_ref)), ph, precision)
+    m = gpu_lib.Model(ph, precision)
+    m.set_states(s)
+    m.pressure_solve(0.37)
+    w_in = s["w"].copy()
+    w_in[0] = w_in[-1] = 0.0
+    u, v, w, p = pressure.project(s["u"], s["v"], w_in, 0.37, ph)
+    assert rel_l2(m.get_pressure(), p) <= 1e-12
+    for name, ref in (("u", u), ("v", v), ("w", w)):
+        err = rel_l2(m.get_state(name), ref)
+        assert err <= TOL[precision], (n, name, err)
+    m.tendencies()
+    G = td.tendencies(timestep.make_state({f: m.get_state(f) for f in m.fields}, ph), ph)
+    for name in ("u", "v", "w", "T"):
+        err = rel_l2(m.get_tendency(name), G[name])
+        assert err <= TOL[precision] * (10 if precision == "fp32" else 1), (n, name, err)
