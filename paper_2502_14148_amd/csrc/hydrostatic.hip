@@ -47,7 +47,12 @@ constexpr int HTX = 64, HTY = 4;
 constexpr int DKB = 8;
 
 // Column scans over the columns i, j in [-2, n + 2] (what the tendency
-// kernel reads of zeta and w).  Workgroups are renumbered XCD-contiguous
+// kernel reads of zeta and w): the workgroups of grid row 0 take the vorticity
+// and w, those of row 1 the pressure gradients (twice the loads in flight;
+// memory bound: 1440x560x50 FP32 moves 1.5 GB in 364 us, 4.2 TB/s; one
+// workgroup for both took 369 us, and a whole step at 360x160x50 245 against
+// 238 us).
+// Workgroups are renumbered XCD-contiguous
 // (x fastest), so the neighbouring rows a column reads were fetched into the
 // same L2 by the workgroups just before it.
 template <class T>
@@ -69,7 +74,7 @@ __global__ void __launch_bounds__(HTX * HTY) hydro_diag_kernel(HydroBufs<T> a) {
   // vertical vorticity at corner (x face i, y face j) and, on the columns
   // i in [-1, nx), j in [0, ny), w on the faces from the floor up: one pass
   // over the levels, so that u and v are fetched once for both
-  {
+  if (blockIdx.y == 0) {
     const T dxj = (T)m.dxc[j + d.h], dxjm = (T)m.dxc[j - 1 + d.h];
     const T rza = T(1) / (T)m.areaz[j + d.h];
     const bool wcol = i >= -1 && i < d.nx && j >= 0 && j < d.ny;
@@ -104,7 +109,7 @@ __global__ void __launch_bounds__(HTX * HTY) hydro_diag_kernel(HydroBufs<T> a) {
 
   // pressure-gradient terms, integrated from the surface down:
   //   px = (p_i - p_{i-1}) / dx at u points, py = (p_j - p_{j-1}) / dy at v points
-  if (i >= 0 && i < d.nx && j >= 0 && j < d.ny) {
+  if (blockIdx.y == 1 && i >= 0 && i < d.nx && j >= 0 && j < d.ny) {
     const T rdx = T(1) / (T)m.dxc[j + d.h];
     const T rdy = T(1) / dy;
     const bool vpt = j > 0;
@@ -153,6 +158,14 @@ __device__ inline T rec(T m3, T m2, T m1, T p0, T p1, T p2, T vel, T eps) {
 // then the cell, u-point and v-point tendencies.  Vertical reconstructions
 // use per-thread register windows along z, and the fluxes through the lower
 // face are carried up from the level below.
+//
+// Bound by vector issue (711 instructions per cell and wave, 0.73 ms at
+// 1440x560x50 FP32) and memory (3.2 GB read with the halos, 1.5 GB written, 0.9 ms
+// at 5.2 TB/s) together: 1.13 ms.  Everything a level reads from memory itself is
+// therefore requested at its start, and its stores are not waited for.  With the
+// loads where their values are used and five wavefronts per SIMD to hide them (now
+// four) it took 1.21 ms; whole steps FP64 720x280x50 1269 -> 1014 us.  Dealing the
+// tiles in blocks instead of rows to an XCD was slower (8 tiles wide: +4 % of a step).
 constexpr int TTX = 32, TTY = 8;
 constexpr int P_TX = TTX + 6, P_TY = TTY + 6;       // T, S: x, y in [-3, T + 2]
 constexpr int P_ZX = TTX + 5, P_ZY = TTY + 5;       // zeta: [-2, T + 2]
@@ -243,19 +256,8 @@ struct StageCopy {
 // load-to-LDS copies among them).
 __device__ inline void wait_vm() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-// FP32: registers capped for five wavefronts per SIMD (a few spilled values,
-// 4 % faster than four wavefronts); FP64 keeps its registers.
-#ifndef OC_HYDRO_WAVES32
-#define OC_HYDRO_WAVES32 5
-#endif
-#ifndef OC_HYDRO_CHUNKS
-#define OC_HYDRO_CHUNKS 2
-#endif
-template <class T>
-constexpr int hydro_tend_waves() { return sizeof(T) == 4 ? OC_HYDRO_WAVES32 : 1; }
-
 template <class T, int SCHEME>
-__global__ void __launch_bounds__(TTX * TTY, hydro_tend_waves<T>())
+__global__ void __launch_bounds__(TTX * TTY)
     hydro_tend_kernel(HydroBufs<T> a, HydroStep<T> st) {
   using SC = StageCopy<T>;
   __shared__ T P[2][SC::LEN];
@@ -368,6 +370,27 @@ __global__ void __launch_bounds__(TTX * TTY, hydro_tend_waves<T>())
     // the next level's planes are copied while this level computes (into the
     // other buffer, whose last readers finished before the previous barrier)
     if (k + 1 < ke) copy_level(k + 1);
+    // the window values of level k + 4 and this level's own values from memory,
+    // in flight during the tracer fluxes
+    T u4 = T(0), v4 = T(0), t4 = T(0), s4 = T(0);
+    if (active && k + 1 < d.nz) {
+      const long kn = kz + 4 * sz;  // level k + 4 (at most nz + 2, inside the halo)
+      u4 = at(uniform_ptr(a.u + kn), cb);
+      v4 = at(uniform_ptr(a.v + kn), cb);
+      t4 = at(uniform_ptr(a.t + kn), cb);
+      s4 = at(uniform_ptr(a.s + kn), cb);
+    }
+    T pxk = T(0), pyk = T(0), gu0 = T(0), gv0 = T(0), gt0[2] = {T(0), T(0)};
+    if (active) {
+      pxk = at(uniform_ptr(a.px + kz), cb);
+      pyk = vpt ? at(uniform_ptr(a.py + kz), cb) : T(0);
+      if (!first) {
+        gu0 = at(uniform_ptr(a.Gu + kz), cb);
+        gv0 = at(uniform_ptr(a.Gv + kz), cb);
+        gt0[0] = at(uniform_ptr(a.Gt + kz), cb);
+        gt0[1] = at(uniform_ptr(a.Gs + kz), cb);
+      }
+    }
 
     // ---- tracer fluxes through the x faces (west of each column) and the
     // y faces (south of each row) of the tile; then the east and north edge
@@ -474,11 +497,11 @@ __global__ void __launch_bounds__(TTX * TTY, hydro_tend_waves<T>())
         const T ke_w = T(0.25) * (u_w * u_w + u_c * u_c + v_w * v_w + v_nw * v_nw);
         T G = zh * vb + fc * vb;
         G -= (ke - ke_w) * rdxc;
-        G -= at(uniform_ptr(a.px + kz), cb);
+        G -= pxk;
         G -= (Fu1 - Fu) * rdz - u_c * (Wu1 - Wu) * rdz;
         G += (Nu1 - Nu) * rdz;
         T comb = a1 * G;
-        if (!first) comb -= a0 * at(uniform_ptr(a.Gu + kz), cb);
+        if (!first) comb -= a0 * gu0;
         at(uniform_ptr(a.Gu + kz), cb) = G;
         at(uniform_ptr(a.uo + kz), cb) = u_c + dt * comb;
         gu += (double)comb;
@@ -493,11 +516,11 @@ __global__ void __launch_bounds__(TTX * TTY, hydro_tend_waves<T>())
         const T ke_s = T(0.25) * (u_s * u_s + u_se * u_se + v_s * v_s + v_c * v_c);
         T G = -(zh * ub) - ff * ub;
         G -= (ke - ke_s) * rdy;
-        G -= at(uniform_ptr(a.py + kz), cb);
+        G -= pyk;
         G -= (Fv1 - Fv) * rdz - v_c * (Wv1 - Wv) * rdz;
         G += (Nv1 - Nv) * rdz;
         T comb = a1 * G;
-        if (!first) comb -= a0 * at(uniform_ptr(a.Gv + kz), cb);
+        if (!first) comb -= a0 * gv0;
         at(uniform_ptr(a.Gv + kz), cb) = G;
         at(uniform_ptr(a.vo + kz), cb) = v_c + dt * comb;
         gv += (double)comb;
@@ -515,7 +538,7 @@ __global__ void __launch_bounds__(TTX * TTY, hydro_tend_waves<T>())
         const T G = -((fx1 - fx0) + (fy1 - fy0) + (Fz1 - Fz0)) * rvol;
         global_ptr<T> Gq = uniform_ptr((q ? a.Gs : a.Gt) + kz);
         T comb = a1 * G;
-        if (!first) comb -= a0 * at(Gq, cb);
+        if (!first) comb -= a0 * gt0[q];
         at(Gq, cb) = G;
         at(uniform_ptr((q ? a.so : a.to) + kz), cb) = cc + dt * comb;
       }
@@ -529,17 +552,14 @@ __global__ void __launch_bounds__(TTX * TTY, hydro_tend_waves<T>())
         tw[o] = tw[o + 1];
         sw[o] = sw[o + 1];
       }
-      if (k + 1 < d.nz) {
-        const long kn = kz + 4 * sz;  // level k + 4 (at most nz + 2, inside the halo)
-        uw[5] = at(uniform_ptr(a.u + kn), cb);
-        vw[5] = at(uniform_ptr(a.v + kn), cb);
-        tw[5] = at(uniform_ptr(a.t + kn), cb);
-        sw[5] = at(uniform_ptr(a.s + kn), cb);
-      }
+      uw[5] = u4; vw[5] = v4; tw[5] = t4; sw[5] = s4;
     }
     // the copies of level k + 1 have landed (this wave's), and every wave is
-    // done with this level's planes and flux arrays
-    wait_vm();
+    // done with this level's planes and flux arrays.  Memory operations retire
+    // in the order they were issued, and a wave with an active lane has issued
+    // its eight stores after the copies: they need not be waited for.
+    if (__any(active)) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+    else wait_vm();
     __syncthreads();
   }
   if (active) {
@@ -568,51 +588,62 @@ __global__ void hydro_gsum_kernel(double* __restrict__ gub, double* __restrict__
 
 // Halo images of the prognostic fields: x periodic; y walls with even
 // mirrors for u, T, S and an odd mirror about the wall faces for v (whose
-// wall faces are set to zero); z walls with even mirrors.
-template <class T>
-__device__ inline void hydro_halo_point(const Dims& d, T* u, T* v, T* t, T* s, int i, int j,
-                                        int k) {
-  const bool xin = i >= 0 && i < d.nx, yin = j >= 0 && j < d.ny, zin = k >= 0 && k < d.nz;
-  const bool vwall = (j == 0 || j == d.ny);
-  const bool c_interior = xin && yin && zin;
-  const bool v_interior = xin && zin && j > 0 && j < d.ny;
-  if (c_interior && v_interior) return;
-  const long p = pidx(d, i, j, k);
-  const int si = (i < 0) ? i + d.nx : (i >= d.nx ? i - d.nx : i);
-  const int sk = (k < 0) ? -1 - k : (k >= d.nz ? 2 * d.nz - 1 - k : k);
-  if (!c_interior) {
-    const int sj = (j < 0) ? -1 - j : (j >= d.ny ? 2 * d.ny - 1 - j : j);
-    const long src = pidx(d, si, sj, sk);
-    u[p] = u[src];
-    t[p] = t[src];
-    s[p] = s[src];
-  }
-  if (!v_interior) {
-    if (vwall) {
-      v[p] = T(0);
-    } else {
-      const int sj = (j < 0) ? -j : (j > d.ny ? 2 * d.ny - j : j);
-      const T sg = (j < 0 || j > d.ny) ? T(-1) : T(1);
-      v[p] = sg * v[pidx(d, si, sj, sk)];
-    }
-  }
-}
-
-// One workgroup per padded row (j, k): rows outside the interior, and the
-// rows of v's wall faces (j = 0, ny), are filled across their whole length;
-// the other rows have only their x halos.
+// wall faces are set to zero); z walls with even mirrors.  Every source is an
+// interior point, none is written.
+//
+// One wavefront per padded row (j, k): rows outside the interior, and the
+// rows of v's wall faces (j = 0, ny), are filled across their whole length,
+// HB columns per lane whose loads travel together; the other rows have only
+// their x halos.  1440x560x50 FP32 (214 MB, 41 us at 5.2 TB/s): 87 us with one
+// column at a time, whose loads wait for the stores before them, now 54 us.
+constexpr int HB = 8;
 template <class T>
 __global__ void __launch_bounds__(64) hydro_halo_kernel(Dims d, T* u, T* v, T* t, T* s) {
   const int j = (int)(blockIdx.x % (unsigned)d.py) - d.h;
   const int k = (int)(blockIdx.x / (unsigned)d.py) - d.h;
-  const bool full = j <= 0 || j >= d.ny || k < 0 || k >= d.nz;
-  if (full) {
-    for (int i = (int)threadIdx.x - d.h; i < d.nx + d.h; i += 64)
-      hydro_halo_point(d, u, v, t, s, i, j, k);
-  } else if ((int)threadIdx.x < 2 * d.h) {
-    const int x = (int)threadIdx.x;
-    const int i = x < d.h ? x - d.h : d.nx + (x - d.h);
-    hydro_halo_point(d, u, v, t, s, i, j, k);
+  const bool zin = k >= 0 && k < d.nz;
+  const bool crow = zin && j >= 0 && j < d.ny, vrow = zin && j > 0 && j < d.ny;   // interior rows
+  const bool vwall = j == 0 || j == d.ny;
+  const int sk = (k < 0) ? -1 - k : (k >= d.nz ? 2 * d.nz - 1 - k : k);
+  const int sj = (j < 0) ? -1 - j : (j >= d.ny ? 2 * d.ny - 1 - j : j);
+  const int sjv = vwall ? 1 : (j < 0) ? -j : (j > d.ny ? 2 * d.ny - j : j);
+  const T sg = vwall ? T(0) : (j < 0 || j > d.ny) ? T(-1) : T(1);
+  const long row = pidx(d, 0, j, k), src = pidx(d, 0, sj, sk), srcv = pidx(d, 0, sjv, sk);
+  auto wrap = [&](int i) { return (i < 0) ? i + d.nx : (i >= d.nx ? i - d.nx : i); };
+  if (crow && vrow) {
+    if ((int)threadIdx.x < 2 * d.h) {
+      const int x = (int)threadIdx.x, i = x < d.h ? x - d.h : d.nx + (x - d.h), si = wrap(i);
+      const T uv = u[src + si], vv = v[srcv + si], tv = t[src + si], sv = s[src + si];
+      u[row + i] = uv;
+      v[row + i] = vv;
+      t[row + i] = tv;
+      s[row + i] = sv;
+    }
+    return;
+  }
+  for (int ib = (int)threadIdx.x - d.h; ib < d.nx + d.h; ib += 64 * HB) {
+    T uv[HB], vv[HB], tv[HB], sv[HB];
+#pragma unroll
+    for (int q = 0; q < HB; ++q) {
+      const int si = wrap(min(ib + 64 * q, d.nx + d.h - 1));
+      uv[q] = u[src + si];
+      vv[q] = v[srcv + si];
+      tv[q] = t[src + si];
+      sv[q] = s[src + si];
+    }
+#pragma unroll
+    for (int q = 0; q < HB; ++q) {
+      const int i = ib + 64 * q;
+      if (i < d.nx + d.h) {
+        const bool xin = i >= 0 && i < d.nx;
+        if (!(crow && xin)) {
+          u[row + i] = uv[q];
+          t[row + i] = tv[q];
+          s[row + i] = sv[q];
+        }
+        if (!(vrow && xin)) v[row + i] = vwall ? T(0) : sg * vv[q];
+      }
+    }
   }
 }
 
@@ -622,7 +653,7 @@ template <class T>
 hipError_t launch_hydro_diag(const HydroBufs<T>& a, hipStream_t s) {
   const unsigned nb =
       (unsigned)(((a.d.nx + 5 + HTX - 1) / HTX) * ((a.d.ny + 5 + HTY - 1) / HTY));
-  hipLaunchKernelGGL(hydro_diag_kernel<T>, dim3(nb), dim3(HTX, HTY), 0, s, a);
+  hipLaunchKernelGGL(hydro_diag_kernel<T>, dim3(nb, 2), dim3(HTX, HTY), 0, s, a);
   return hipGetLastError();
 }
 
@@ -633,7 +664,7 @@ hipError_t launch_hydro_tendency(const HydroBufs<T>& a, const HydroStep<T>& st, 
   // twice the workgroups of one march, so its last round of resident
   // workgroups is fuller
   HydroStep<T> sc = st;
-  const int nchunks = a.d.nz >= 16 ? OC_HYDRO_CHUNKS : 1;
+  const int nchunks = a.d.nz >= 16 ? 2 : 1;
   sc.kc = (a.d.nz + nchunks - 1) / nchunks;
   const dim3 grid((unsigned)(((a.d.nx + TTX - 1) / TTX) * ((a.d.ny + TTY - 1) / TTY) * nchunks));
   const dim3 block(TTX, TTY);

@@ -117,6 +117,14 @@ def test_ragged_small_grid(gpu_lib, n):
     _check_run(gpu_lib, _phys(nx=n[0], ny=n[1], nz=n[2]), "fp64", 2, seed=3)
 
 
+@pytest.mark.parametrize("n,precision", [((8, 8, 8), "fp64"), ((504, 8, 8), "fp64"),
+                                         ((512, 8, 9), "fp32"), ((1016, 8, 16), "fp64")])
+def test_row_lengths_of_the_halo_fill(gpu_lib, n, precision):
+    # rows outside the interior are filled 512 columns at a time: padded rows
+    # of 14, 510, 518 (a second batch of 6 columns) and 1022 points
+    _check_run(gpu_lib, _phys(nx=n[0], ny=n[1], nz=n[2]), precision, 2, seed=4)
+
+
 def test_rest_state_stays_at_rest(gpu_lib):
     ph = _phys(nx=64, ny=16, nz=8)
     s = inputs.hydrostatic_initial(ph, seed=4, t_noise=0.0, stress_scale=0.0)
