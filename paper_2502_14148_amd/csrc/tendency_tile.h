@@ -118,10 +118,10 @@ __device__ inline T interp_lds(const T* q, int L, int s) {
   return interpc<T, R>(a);
 }
 
-// Fluxes of one x or y face slot at LDS position L.  All LDS planes are
-// offsets into one shared array S (so every access stays an LDS access).
-// sd/se are the strides along and across the flux direction (compile-time
-// constants in the main rounds, per lane in the edge round).
+// Fluxes of the own cell's x or y face at LDS position L, into LDS for the
+// neighbour and into own for the cell itself.  All LDS planes are offsets into
+// one shared array S (so every access stays an LDS access).  sd/se are the
+// strides along and across the flux direction.
 struct SlotOff {
   int vd, ve;             // normal and tangential velocity planes (level k)
   int az;                 // normal velocity interpolated in z to face k, per slot
@@ -129,35 +129,36 @@ struct SlotOff {
   int c0;                 // first tracer plane (level k); tracers are PL apart
   int Fself, Fcross, Fw;  // flux arrays (already for this direction)
   int Fc0, Fstride;       // first tracer flux array and the array pitch
+  int fself;              // field of the normal velocity (0 u, 1 v)
 };
 
 // IMM: no diffusive tracer flux through a face next to an immersed cell (the
 // mask plane at S + om).
 template <class T, int SCHEME, int NTR, int PL, int R, bool IMM = false>
 __device__ inline void slot_fluxes(T* S, const SlotOff& o, int L, int sd, int se, int fi, T rd,
-                                   T nu, T kappa, T eps, int om = 0) {
+                                   T nu, T kappa, T eps, int om, T* own) {
   {
     const T* vd = S + o.vd;
     const T adv = interp_lds<T, R>(vd, L, sd);
-    S[o.Fself + fi] = flux_lds<T, SCHEME, R>(vd, L, sd, adv, eps) - nu * (vd[L] - vd[L - sd]) * rd;
+    S[o.Fself + fi] = own[o.fself] = flux_lds<T, SCHEME, R>(vd, L, sd, adv, eps) - nu * (vd[L] - vd[L - sd]) * rd;
   }
   {
     const T* vd = S + o.vd;
     const T* ve = S + o.ve;
     const T adv = interp_lds<T, R>(vd, L, se);
-    S[o.Fcross + fi] = flux_lds<T, SCHEME, R>(ve, L, sd, adv, eps) - nu * (ve[L] - ve[L - sd]) * rd;
+    S[o.Fcross + fi] = own[1 - o.fself] = flux_lds<T, SCHEME, R>(ve, L, sd, adv, eps) - nu * (ve[L] - ve[L - sd]) * rd;
   }
   {
     const T adv = S[o.az + fi];
     const T* wk = S + o.wk;
-    S[o.Fw + fi] = flux_lds<T, SCHEME, R>(wk, L, sd, adv, eps) - nu * (wk[L] - wk[L - sd]) * rd;
+    S[o.Fw + fi] = own[2] = flux_lds<T, SCHEME, R>(wk, L, sd, adv, eps) - nu * (wk[L] - wk[L - sd]) * rd;
   }
   const T un = S[o.vd + L];
   const T kap = IMM ? kappa * (S[om + L] * S[om + L - sd]) : kappa;
 #pragma unroll
   for (int q = 0; q < NTR; ++q) {
     const T* c = S + o.c0 + q * PL;
-    S[o.Fc0 + q * o.Fstride + fi] =
+    S[o.Fc0 + q * o.Fstride + fi] = own[3 + q] =
         flux_lds<T, SCHEME, R>(c, L, sd, un, eps) - kap * (c[L] - c[L - sd]) * rd;
   }
 }
@@ -423,6 +424,9 @@ __device__ __attribute__((always_inline)) inline void tendency_tile(
     // ---- x and y face fluxes (the face velocities of level k were written
     // before the barrier that ended the previous level)
     SlotOff ox, oy;
+    T fx[NF], fy[NF];   // the own cell's, for its tendencies
+    ox.fself = 0;
+    oy.fself = 1;
     ox.vd = OU; ox.ve = OV; ox.az = OAX;
     ox.wk = OWk; ox.c0 = OC;
     ox.Fself = OFX + 0 * NXS; ox.Fcross = OFX + 1 * NXS; ox.Fw = OFX + 2 * NXS;
@@ -433,24 +437,37 @@ __device__ __attribute__((always_inline)) inline void tendency_tile(
     oy.Fc0 = OFY + 3 * NYS; oy.Fstride = NYS;
     // main rounds: the left x face and the bottom y face of the own cell
     slot_fluxes<T, SCHEME, NTR, PLP, R, IMM>(S, ox, Lc, 1, PX, ty * (TX + 1) + tx, P.rdx, P.nu,
-                                             P.kappa, eps, OM);
+                                             P.kappa, eps, OM, fx);
     __builtin_amdgcn_sched_barrier(0);
     slot_fluxes<T, SCHEME, NTR, PLP, R, IMM>(S, oy, Lc, PX, 1, ty * TX + tx, P.rdy, P.nu,
-                                             P.kappa, eps, OM);
+                                             P.kappa, eps, OM, fy);
     __builtin_amdgcn_sched_barrier(0);
-    // edge round: right x faces of the last column, top y faces of the last row
-    if (edge) {
-      const bool xs = tid < TY;
-      const int L = xs ? (tid + R) * PX + (TX + R) : (TY + R) * PX + (tid - TY + R);
-      const int fi = xs ? tid * (TX + 1) + TX : TY * TX + (tid - TY);
-      SlotOff oe;
-      oe.vd = xs ? ox.vd : oy.vd; oe.ve = xs ? ox.ve : oy.ve; oe.az = xs ? ox.az : oy.az;
-      oe.wk = ox.wk; oe.c0 = OC;
-      oe.Fself = xs ? ox.Fself : oy.Fself; oe.Fcross = xs ? ox.Fcross : oy.Fcross;
-      oe.Fw = xs ? ox.Fw : oy.Fw; oe.Fc0 = xs ? ox.Fc0 : oy.Fc0;
-      oe.Fstride = xs ? NXS : NYS;
-      slot_fluxes<T, SCHEME, NTR, PLP, R, IMM>(S, oe, L, xs ? 1 : PX, xs ? PX : 1, fi,
-                                               xs ? P.rdx : P.rdy, P.nu, P.kappa, eps, OM);
+    // edge round: right x faces of the last column, top y faces of the last
+    // row, one field's flux per thread.  (With one face per thread the first
+    // wavefronts computed NF reconstructions more than the others, which waited
+    // for them at the barrier: tendencies at 128^3 FP64 137 -> 126 us, 128^3
+    // FP32 WENO9 165 -> 155, 256^3 FP32 445 -> 436.  Each cell keeping its own
+    // faces' fluxes in registers: 126 -> 123, 155 -> 155, 436 -> 430.)
+#pragma unroll
+    for (int r = 0; r < (NE * NF + NT - 1) / NT; ++r) {
+      const int unit = r * NT + tid;
+      if (unit < NE * NF) {
+        const int f = unit / NE, e = unit - f * NE;
+        const bool xs = e < TY;
+        const int L = xs ? (e + R) * PX + (TX + R) : (TY + R) * PX + (e - TY + R);
+        const int fi = xs ? e * (TX + 1) + TX : TY * TX + (e - TY);
+        const int sd = xs ? 1 : PX;
+        const T* vd = S + (xs ? OU : OV);
+        const T* q = S + (f == 2 ? OWk : lb + (f < 2 ? f : f - 1) * PLP);
+        const T vi = interp_lds<T, R>(vd, L, f == 0 ? 1 : PX);
+        const T vw = S[f == 2 ? (xs ? OAX : OAY) + fi : (xs ? OU : OV) + L];
+        const T vel = f < 2 ? vi : vw;
+        T coef = f < 3 ? P.nu : P.kappa;
+        if (IMM && f >= 3) coef = coef * (S[OM + L] * S[OM + L - sd]);
+        S[(xs ? OFX + f * NXS : OFY + f * NYS) + fi] =
+            flux_lds<T, SCHEME, R>(q, L, sd, vel, eps) -
+            coef * (q[L] - q[L - sd]) * (xs ? P.rdx : P.rdy);
+      }
     }
 
     // ---- z fluxes through the top face of level k (w: at centre k)
@@ -485,8 +502,8 @@ __device__ __attribute__((always_inline)) inline void tendency_tile(
       T G[NF];
 #pragma unroll
       for (int f = 0; f < NF; ++f)
-        G[f] = -(S[OFX + f * NXS + ix + 1] - S[OFX + f * NXS + ix]) * P.rdx -
-               (S[OFY + f * NYS + iy + TX] - S[OFY + f * NYS + iy]) * P.rdy;
+        G[f] = -(S[OFX + f * NXS + ix + 1] - fx[f]) * P.rdx -
+               (S[OFY + f * NYS + iy + TX] - fy[f]) * P.rdy;
       const T* uk = S + OU;
       const T* vk = S + OV;
       G[0] += -(fzt_u - fzb_u) * rzc +

@@ -311,3 +311,26 @@ def test_projection_row_blocks(gpu_lib, n, advection, precision):
     for name in ("u", "v", "w", "T"):
         err = rel_l2(m.get_tendency(name), G[name])
         assert err <= TOL[precision] * (10 if precision == "fp32" else 1), (n, name, err)
+
+
+@pytest.mark.parametrize("n,tracers,advection,precision", [
+    ((8, 8, 8), ("c",), "weno9z", "fp64"), ((16, 8, 8), ("T", "S", "c", "e"), "weno5z", "fp64"),
+    ((32, 8, 16), ("T", "S", "c", "e"), "weno5z", "fp32"), ((96, 16, 8), ("T", "S"), "weno7z", "fp64"),
+    ((64, 8, 16), ("T", "S", "c"), "weno5z", "fp32"), ((64, 16, 8), ("c",), "weno5z", "fp32")])
+def test_tendency_edge_faces(gpu_lib, n, tracers, advection, precision):
+    """The faces at the upper edges of a tile, whose fluxes are dealt over the
+    threads field by field: every tile, one to four tracers."""
+    ph = small_convection(*n, nu=1e-3, kappa=2e-3)
+    ph.advection, ph.tracers, ph.buoyancy = advection, tracers, tracers[0] == "T"
+    if not ph.buoyancy:
+        ph.top_flux = {}
+    s = _prep(inputs.random_state(ph, seed=51, vel=0.1,
+                                  tracer_means=(ph.t_ref, ph.s_ref, 1.0, 2.0)[:len(tracers)]),
+              ph, precision)
+    m = gpu_lib.Model(ph, precision)
+    m.set_states(s)
+    m.tendencies()
+    G = td.tendencies(timestep.make_state(s, ph), ph)
+    for name in m.fields:
+        err = rel_l2(m.get_tendency(name), G[name])
+        assert err <= TOL[precision], (n, name, err)
