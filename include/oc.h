@@ -241,10 +241,11 @@ int oc_get_tendency(oc_model* m, int32_t field, void* buf, int32_t dtype,
  * at interior faces, halos refilled.  Errors: OC_ERR_ARG if dt_eff <= 0.
  * oc_get_pressure copies the p of the model's last solve (this call, or the
  * last substage of oc_rk3_step / oc_ensemble_step) to buf: FP64, shape
- * (nz, ny, nx).  Without an immersed boundary the solve keeps p only as its
- * x-spectrum (the projection transforms it on the fly), and the first
- * oc_get_pressure after a solve enqueues the inverse x transform on
- * `stream` before the copy; with on_device = 0 it waits for the copy. */
+ * (nz, ny, nx).  The solve keeps p only as its x-spectrum (the projection
+ * transforms it on the fly), and the first oc_get_pressure after a solve
+ * enqueues the inverse x transform (with an immersed boundary also the shift
+ * to zero mean over the fluid) on `stream` before the copy; with
+ * on_device = 0 it waits for the copy. */
 int oc_pressure_solve(oc_model* m, double dt_eff, void* stream);
 int oc_get_pressure(oc_model* m, double* buf, int32_t on_device, void* stream);
 

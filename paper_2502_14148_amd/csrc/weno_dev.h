@@ -37,20 +37,22 @@ __device__ inline T interp4(T a0, T a1, T a2, T a3) {
 // q_{-3..2}; `vel` selects the upwind side.
 //
 // WENO-Z form used here (equal to the textbook form in exact arithmetic):
-// with the upwind-ordered stencil (a, b, c, d, e) and its differences
-// d1 = b - a, ..., d4 = e - d,
-//   * candidates as deviations from the upwind neighbour c:
-//       r0 - c = (5 d2 - 2 d1)/6, r1 - c = (d2 + 2 d3)/6, r2 - c = (4 d3 - d4)/6;
-//   * four times the Jiang-Shu indicators plus eps:
-//       s_k = 13/3 t_k^2 + u_k^2 + 4 eps, t = (d2 - d1, d3 - d2, d4 - d3),
-//       u = (3 d2 - d1, d2 + d3, d4 - 3 d3)
-//     (the weights only see ratios, so the common factor 4 drops out);
-//   * WENO-Z weights d_k (1 + (tau / s_k)^2), tau = |s_0 - s_2|, multiplied
-//     through by s_1^2:  a_k = s_1^2 + (tau s_1 / s_k)^2, a_1 = s_1^2 + tau^2,
-//     so two reciprocals (of s_0 and s_2) replace three;
-//   * W = c + sum d_k a_k (r_k - c) / sum d_k a_k.
-// FP32 range: tau s_1 / s_k stays below 1.8e19 for indicators up to ~1e2 in
-// the field's units squared next to an exactly flat stencil.
+// with the upwind-ordered stencil (a, b, c, d, e), its differences
+// d1 = b - a, ..., d4 = e - d and t = (d2 - d1, d3 - d2, d4 - d3),
+//   * candidates as deviations from the upwind neighbour c, twice over:
+//       2 (r0 - c) = d2 + 2/3 t0, 2 (r1 - c) = d2 + 2/3 t1, 2 (r2 - c) = d3 - 1/3 t2;
+//   * the Jiang-Shu indicators plus eps, as t (4/3 t +- d) + d^2 + eps:
+//       s0 with (t0, +d2), s1 with (t1, +d2), s2 with (t2, -d3);
+//   * WENO-Z weights d_k (1 + (tau / s_k)^2), tau = |s0 - s2|, multiplied
+//     through by 10 s1^2:  a0 = s1^2 + (tau s1 / s0)^2, a1 = 6 (s1^2 + tau^2),
+//     a2 = 3 (s1^2 + (tau s1 / s2)^2), both quotients from the one reciprocal
+//     of s0 s2;
+//   * W = c + sum a_k (r_k - c) / sum a_k.
+// Two reciprocals in 45 operations (51 and three reciprocals with one each for
+// s0 and s2, which cost 2 to 4 % of a whole step).
+// FP32 range: s0 s2 and s1^2 need eps above about 1.1e-19 to stay normal next
+// to flat stencils, and tau s1 / s_k stays below 1.8e19 for indicators up to
+// ~1e2 in the field's units squared next to an exactly flat stencil.
 template <class T, int SCHEME>
 __device__ inline T rec6(T m3, T m2, T m1, T p0, T p1, T p2, T vel, T eps) {
   const bool pos = vel > T(0);
