@@ -486,15 +486,6 @@ def run_weno_high(steps, warmup, n):
     return out
 
 
-# Algorithmic HBM bytes per cell of one conjugate-gradient iteration of the
-# immersed-boundary pressure solve (FP64 vectors, a geometry byte per cell,
-# counted as 4 B): A q reads q and the geometry, writes A q (20 B); the
-# residual update reads r and A q and writes r (24 B); the direction update
-# reads x, q, z and writes x, q (40 B).  The preconditioner's five FFT passes
-# (r . z is summed in the last one) come on top.
-CG_BYTES_PER_CELL_ITER = 20 + 24 + 40
-
-
 def run_immersed(steps, warmup, n):
     """The 256^3 free-convection step over a Gaussian seamount (grid-fitted
     immersed bottom, 40 % of the depth high): masked tendencies and the
@@ -536,7 +527,6 @@ def run_immersed(steps, warmup, n):
     n_fft = prof["fft_x_fwd"][1]           # preconditioner applications
     iters_per_solve = n_fft / solves - 1   # one application before the first iteration
     cg_ms = prof["cg"][0]
-    gbs = CG_BYTES_PER_CELL_ITER * ncells * (n_fft - solves) / (cg_ms / 1e3) / 1e9
     return {"value": ncells * steps / (ms / 1e3), "unit": "cell-steps/s", "steps": steps,
             "warmup": warmup, "ms_per_step": ms / steps, "dtype": "f32",
             "config": {"workload": f"free-convection LES {n}^3 over a Gaussian seamount "
@@ -547,10 +537,7 @@ def run_immersed(steps, warmup, n):
             "kernels_ms_per_step": {k: v[0] / steps for k, v in prof.items() if v[1]},
             "cg": {"iterations_per_solve": iters_per_solve, "last_solve": {"iterations": it,
                                                                            "rel_residual": res},
-                   "ms_per_solve": (cg_ms + t_fft) / solves,
-                   "vector_kernels_hbm": {"achieved_gbs": round(gbs, 1),
-                                          "frac": round(gbs / HBM_PEAK_GBS, 4),
-                                          "bytes_per_cell_iteration": CG_BYTES_PER_CELL_ITER}},
+                   "ms_per_solve": (cg_ms + t_fft) / solves},
             "final_max_w": diag["max_w"]}
 
 

@@ -36,7 +36,7 @@ namespace {
 //   u += dtau^2 GU - g H dtau^2 / dx (eta_i - eta_{i-1}),  v likewise,
 // 14 FP64 operations per cell with the running averages and no division (the
 // row factors and their inverses are formed once).  Bound by the
-// state's 140 bytes per cell and launch and by the 2.1 cells computed per
+// state's 140 bytes per cell and launch and by the 2.6 cells computed per
 // own cell.  On the 1440 x 560 sector a substep took 9.6 us with the tile in LDS
 // (three divisions per cell, six substeps per launch), 3.8 us now.  Rows per
 // wave x waves, substeps per launch, us for the 59 substeps and a correction
