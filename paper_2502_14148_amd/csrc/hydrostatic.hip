@@ -154,14 +154,14 @@ __device__ inline T rec(T m3, T m2, T m1, T p0, T p1, T p2, T vel, T eps) {
 // with three halo cells, zeta, u, v and w on face k + 1) in LDS (two
 // buffers: the next level's planes are copied in by the buffer unit while
 // this level computes), computes every tracer face flux of the tile once (the
-// east and north edge faces in a second round by the first wavefront) and
+// east and north edge faces in a second round, one tracer's per thread) and
 // then the cell, u-point and v-point tendencies.  Vertical reconstructions
 // use per-thread register windows along z, and the fluxes through the lower
 // face are carried up from the level below.
 //
 // Bound by vector issue (711 instructions per cell and wave, 0.73 ms at
 // 1440x560x50 FP32) and memory (3.2 GB read with the halos, 1.5 GB written, 0.9 ms
-// at 5.2 TB/s) together: 1.13 ms.  Everything a level reads from memory itself is
+// at 5.2 TB/s) together: 1.05 ms.  Everything a level reads from memory itself is
 // therefore requested at its start, and its stores are not waited for.  With the
 // loads where their values are used and five wavefronts per SIMD to hide them (now
 // four) it took 1.21 ms; whole steps FP64 720x280x50 1269 -> 1014 us.  Dealing the
@@ -283,6 +283,7 @@ __global__ void __launch_bounds__(TTX * TTY)
   const T fc = (T)m.fc[jm], ff = (T)m.ff[jm];
   const T Ax = dy * dz;
   const T Ay0 = (T)m.dxf[jm] * dz;
+  const T Ayn = (T)m.dxf[min(j0 + TTY, d.ny) + d.h] * dz;   // the y faces above the tile
   const T Az = (T)m.areac[jm];
   const T rvol = T(1) / (Az * dz);
   const T nu = a.nu, kappa = a.kappa;
@@ -394,7 +395,9 @@ __global__ void __launch_bounds__(TTX * TTY)
 
     // ---- tracer fluxes through the x faces (west of each column) and the
     // y faces (south of each row) of the tile; then the east and north edge
-    // faces by the first wavefront
+    // faces, one tracer's flux per thread (both tracers by one thread kept the
+    // other wavefronts waiting: a step at 1440x560x50 FP32 1.89 -> 1.86 ms, at
+    // 360x160x50 239 -> 226 us, at 720x280x50 FP64 1012 -> 962 us)
     {
       const T* St = S + SC::L_T;
       const T* Ss = S + SC::L_S;
@@ -420,37 +423,20 @@ __global__ void __launch_bounds__(TTX * TTY)
                    : T(0);
         }
       }
-      if (tid < TTY + TTX) {
-        if (tid < TTY) {           // x face i0 + TTX of row j0 + tid
-          const int ey = tid;
-          if (i0 + TTX <= d.nx && j0 + ey < d.ny) {
-            const T uf = S[SC::L_U + (ey + 1) * P_UX + TTX + 1];
-            const int le = (ey + 3) * P_TX + TTX + 3;
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-              const T* f = q ? Ss : St;
-              FX[q][ey * (TTX + 1) + TTX] =
-                  uf * rec<T, SCHEME>(f[le - 3], f[le - 2], f[le - 1], f[le], f[le + 1], f[le + 2],
-                                      uf, eps) * Ax;
-            }
-          }
-        } else {                   // y face j0 + TTY of column i0 + ex
-          const int ex = tid - TTY;
-          const int jf = j0 + TTY;
-          if (jf <= d.ny && i0 + ex < d.nx) {
-            const T vf = S[SC::L_V + (TTY + 1) * P_VX + ex + 1];
-            const int le = (TTY + 3) * P_TX + ex + 3;
-            const bool open = jf < d.ny;
-            const T Ay = (T)m.dxf[jf + d.h] * dz;
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-              const T* f = q ? Ss : St;
-              FY[q][TTY * TTX + ex] =
-                  open ? vf * rec<T, SCHEME>(f[le - 3 * P_TX], f[le - 2 * P_TX], f[le - P_TX],
-                                             f[le], f[le + P_TX], f[le + 2 * P_TX], vf, eps) * Ay
-                       : T(0);
-            }
-          }
+      if (tid < 2 * (TTY + TTX)) {
+        const int q = tid >= TTY + TTX, e = tid - q * (TTY + TTX);
+        const bool xf = e < TTY;   // x face i0 + TTX of row j0 + e, or
+        const int ex = e - TTY;    // y face j0 + TTY of column i0 + ex
+        if (xf ? i0 + TTX <= d.nx && j0 + e < d.ny : j0 + TTY <= d.ny && i0 + ex < d.nx) {
+          const T vel = S[xf ? SC::L_U + (e + 1) * P_UX + TTX + 1
+                             : SC::L_V + (TTY + 1) * P_VX + ex + 1];
+          const T* f = (q ? Ss : St) + (xf ? (e + 3) * P_TX + TTX + 3 : (TTY + 3) * P_TX + ex + 3);
+          const int sd = xf ? 1 : P_TX;
+          const bool open = xf || j0 + TTY < d.ny;
+          const T A = xf ? Ax : Ayn;
+          const T F = vel * rec<T, SCHEME>(f[-3 * sd], f[-2 * sd], f[-sd], f[0], f[sd], f[2 * sd],
+                                           vel, eps) * A;
+          (xf ? FX[q] : FY[q])[xf ? e * (TTX + 1) + TTX : TTY * TTX + ex] = open ? F : T(0);
         }
       }
     }
