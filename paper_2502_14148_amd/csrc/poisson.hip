@@ -82,9 +82,9 @@ __device__ inline void dft(double2* v) {
 
 // One Stockham pass of radix R over L lines of length N held in LDS at
 // buf[line * ls + n * es].  NS is the length of the sub-transforms already
-// done.  LINE_FAST maps consecutive threads to consecutive lines (used when
-// lines are interleaved, es = L) to avoid LDS bank conflicts.
-template <int N, int R, int NS, int L, int NT, int DIR, bool LINE_FAST>
+// done.  Consecutive threads take consecutive lines (the lines are
+// interleaved, es = L), which avoids LDS bank conflicts.
+template <int N, int R, int NS, int L, int NT, int DIR>
 __device__ inline void stockham_pass(double2* buf, int ls, int es, const double2* __restrict__ tw) {
   constexpr int M = N / R;
   constexpr int NB = L * M;
@@ -94,8 +94,8 @@ __device__ inline void stockham_pass(double2* buf, int ls, int es, const double2
 #pragma unroll
   for (int q = 0; q < BPT; ++q) {
     const int b = threadIdx.x + q * NT;
-    line_[q] = LINE_FAST ? (b % L) : (b / M);
-    jj_[q] = LINE_FAST ? (b / L) : (b % M);
+    line_[q] = b % L;
+    jj_[q] = b / L;
     if (NB % NT == 0 || b < NB) {
       const int k = jj_[q] % NS;
 #pragma unroll
@@ -134,12 +134,12 @@ constexpr int pass_radix() {
   return (MAXR >= 8 && REM % 8 == 0) ? 8 : ((REM % 4 == 0) ? 4 : ((REM % 2 == 0) ? 2 : 3));
 }
 
-template <int N, int NS, int L, int NT, int DIR, bool LINE_FAST, int MAXR = 4>
+template <int N, int NS, int L, int NT, int DIR, int MAXR>
 __device__ inline void fft_lines(double2* buf, int ls, int es, const double2* __restrict__ tw) {
   if constexpr (NS < N) {
     constexpr int R = pass_radix<N / NS, MAXR>();
-    stockham_pass<N, R, NS, L, NT, DIR, LINE_FAST>(buf, ls, es, tw);
-    fft_lines<N, NS * R, L, NT, DIR, LINE_FAST, MAXR>(buf, ls, es, tw);
+    stockham_pass<N, R, NS, L, NT, DIR>(buf, ls, es, tw);
+    fft_lines<N, NS * R, L, NT, DIR, MAXR>(buf, ls, es, tw);
   }
 }
 
@@ -176,7 +176,7 @@ template <int N, int L, int NT, int DIR, int MAXR, class Load>
 __device__ inline void fft_lines_from(double2* buf, const double2* __restrict__ tw,
                                       const Load& load) {
   first_pass_from<N, L, NT, DIR, MAXR>(buf, load);
-  fft_lines<N, pass_radix<N, MAXR>(), L, NT, DIR, true, MAXR>(buf, 1, L, tw);
+  fft_lines<N, pass_radix<N, MAXR>(), L, NT, DIR, MAXR>(buf, 1, L, tw);
 }
 
 // The same lines whose last pass hands its outputs to store(line, n, value)
@@ -186,7 +186,7 @@ __device__ inline void fft_lines_to(double2* buf, const double2* __restrict__ tw
                                     const Store& store) {
   constexpr int R = pass_radix<N / NS, MAXR>();
   if constexpr (NS * R < N) {
-    stockham_pass<N, R, NS, L, NT, DIR, true>(buf, 1, L, tw);
+    stockham_pass<N, R, NS, L, NT, DIR>(buf, 1, L, tw);
     fft_lines_to<N, NS * R, L, NT, DIR, MAXR>(buf, tw, store);
   } else {
     constexpr int M = N / R, NB = L * M, BPT = (NB + NT - 1) / NT;
@@ -240,6 +240,60 @@ __device__ inline void fft_lines_io(double2* buf, const double2* __restrict__ tw
   }
 }
 
+// What one lane wrote to LDS is seen by the other lanes of its wavefront past
+// this point (LDS serves a wavefront's accesses in order; this keeps the
+// compiler from reordering them).
+__device__ inline void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// The Stockham passes from sub-transform length NS on of one line of length N
+// by TPL lanes of one wavefront (t: the lane's index among them).  The passes
+// need no barrier: two in the forward and stand-alone inverse x passes instead
+// of ten at length 256 (memory bound at 256^3 either way, 63 us a pass; a solve
+// at 96x64x128 FP64 46.2 -> 45.1 us, a two-step call there 678 -> 674).
+template <int N, int NS, int TPL, int DIR>
+__device__ inline void fft_wave_line(double2* line, int t, const double2* tw) {
+  if constexpr (NS < N) {
+    constexpr int R = pass_radix<N / NS, 4>(), M = N / R, BPT = (M + TPL - 1) / TPL;
+    double2 v[BPT][R];
+    wave_sync();
+#pragma unroll
+    for (int q = 0; q < BPT; ++q) {
+      const int jj = t + q * TPL;
+      if (M % TPL == 0 || jj < M) {
+        const int k = jj % NS;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          double2 x = line[jj + r * M];
+          if (r > 0 && NS > 1) {
+            double2 w = tw[(r * k) * (N / (NS * R))];
+            if (DIR > 0) w = cconj(w);
+            x = cmul(x, w);
+          }
+          v[q][r] = x;
+        }
+        dft<R, DIR>(v[q]);
+      }
+    }
+    wave_sync();
+#pragma unroll
+    for (int q = 0; q < BPT; ++q) {
+      const int jj = t + q * TPL;
+      if (M % TPL == 0 || jj < M) {
+        const int e = (jj / NS) * NS * R + jj % NS;
+#pragma unroll
+        for (int r = 0; r < R; ++r) line[e + r * NS] = v[q][r];
+      }
+    }
+    fft_wave_line<N, NS * R, TPL, DIR>(line, t, tw);
+  }
+}
+
+// Lanes of an x line.
+template <int N> struct XLanes { static constexpr int TPL = N == 96 ? 32 : N / 4; };
+
 constexpr int NT = 256;
 // Twiddle table staged in LDS by the whole workgroup (made visible by the
 // barrier that follows the tile load), so that the Stockham passes read
@@ -252,7 +306,8 @@ __device__ inline void stage_twiddles(double2* tws, const double2* __restrict__ 
     if (N % NT == 0 || t < N) tws[t] = ld2(tw, t);
   }
 }
-template <int N> struct XCfg { static constexpr int LP = (N >= 1024) ? 1 : 1024 / N; };
+// Line pairs per workgroup of the x passes, each the lanes of one wavefront
+template <int N> struct XCfg { static constexpr int TPL = XLanes<N>::TPL, LP = NT / TPL; };
 template <int N> struct YZCfg { static constexpr int W = (N >= 512) ? 4 : (N >= 256 ? 8 : 16); };
 
 // ---------------------------------------------------------------------------
@@ -336,7 +391,11 @@ __global__ void __launch_bounds__(NT) fwd_x_kernel(Dims d, const T* __restrict__
     for (int m = 0; m < 4; ++m) buf[l * N + i + m] = make_double2(de[m], dod[m]);
   }
   __syncthreads();
-  fft_lines<N, 1, LP, NT, -1, false>(buf, N, 1, tws);
+  {
+    constexpr int TPL = XCfg<N>::TPL;
+    fft_wave_line<N, 1, TPL, -1>(buf + (int)threadIdx.x / TPL * N, (int)threadIdx.x % TPL, tws);
+  }
+  __syncthreads();
   // unpack the two real spectra: X1 = (Z_k + conj Z_{N-k})/2, X2 = -i (Z_k - conj Z_{N-k})/2
   const int nxh = sb.nxh;
   for (int t = threadIdx.x; t < LP * nxh; t += NT) {
@@ -678,7 +737,11 @@ __global__ void __launch_bounds__(NT) inv_x_kernel(Dims d, SpecBufs sb) {
     buf[t] = z;
   }
   __syncthreads();
-  fft_lines<N, 1, LP, NT, 1, false>(buf, N, 1, tws);
+  {
+    constexpr int TPL = XCfg<N>::TPL;
+    fft_wave_line<N, 1, TPL, 1>(buf + (int)threadIdx.x / TPL * N, (int)threadIdx.x % TPL, tws);
+  }
+  __syncthreads();
   for (int t = threadIdx.x; t < LP * N; t += NT) {
     const int l = t / N, i = t % N;
     const int pr = pair0 + l;
@@ -726,62 +789,13 @@ __global__ void __launch_bounds__(NT) inv_x_kernel(Dims d, SpecBufs sb) {
 template <int N> struct PXCfg {
   static constexpr int L = N >= 256 || N == 96 ? 4 : 512 / N;
   static constexpr int LV = N == 96 ? 2 : 1;
-  // threads of a line, all of one wavefront
-  static constexpr int TPL = N == 96 ? 32 : N / 4;
+  static constexpr int TPL = XLanes<N>::TPL;
 };
 
 // ld2 from a uniform address and a 32-bit index.
 __device__ inline double2 ld2u(const double2* p, uint32_t i) {
   const oc_dbl2 v = ((const __attribute__((address_space(1))) oc_dbl2*)p)[i];
   return make_double2(v.x, v.y);
-}
-
-// What one lane wrote to LDS is seen by the other lanes of its wavefront past
-// this point (LDS serves a wavefront's accesses in order; this keeps the
-// compiler from reordering them).
-__device__ inline void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
-
-// The Stockham passes from sub-transform length NS on of one line of length N
-// by TPL lanes of one wavefront (t: the lane's index among them).
-template <int N, int NS, int TPL, int DIR>
-__device__ inline void fft_wave_line(double2* line, int t, const double2* tw) {
-  if constexpr (NS < N) {
-    constexpr int R = pass_radix<N / NS, 4>(), M = N / R, BPT = (M + TPL - 1) / TPL;
-    double2 v[BPT][R];
-    wave_sync();
-#pragma unroll
-    for (int q = 0; q < BPT; ++q) {
-      const int jj = t + q * TPL;
-      if (M % TPL == 0 || jj < M) {
-        const int k = jj % NS;
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          double2 x = line[jj + r * M];
-          if (r > 0) {
-            double2 w = tw[(r * k) * (N / (NS * R))];
-            if (DIR > 0) w = cconj(w);
-            x = cmul(x, w);
-          }
-          v[q][r] = x;
-        }
-        dft<R, DIR>(v[q]);
-      }
-    }
-    wave_sync();
-#pragma unroll
-    for (int q = 0; q < BPT; ++q) {
-      const int jj = t + q * TPL;
-      if (M % TPL == 0 || jj < M) {
-        const int e = (jj / NS) * NS * R + jj % NS;
-#pragma unroll
-        for (int r = 0; r < R; ++r) line[e + r * NS] = v[q][r];
-      }
-    }
-    fft_wave_line<N, NS * R, TPL, DIR>(line, t, tw);
-  }
 }
 
 // MASK (immersed boundary): velocities on closed faces are set to 0.
