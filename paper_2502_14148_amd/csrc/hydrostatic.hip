@@ -160,7 +160,7 @@ __device__ inline T rec(T m3, T m2, T m1, T p0, T p1, T p2, T vel, T eps) {
 // face are carried up from the level below.
 //
 // Bound by vector issue (711 instructions per cell and wave, 0.73 ms at
-// 1440x560x50 FP32) and memory (3.2 GB read with the halos, 1.5 GB written, 0.9 ms
+// 1440x560x50 FP32) and memory (3.5 GB read with the halos, 1.6 GB written, 0.97 ms
 // at 5.2 TB/s) together: 1.05 ms.  Everything a level reads from memory itself is
 // therefore requested at its start, and its stores are not waited for.  With the
 // loads where their values are used and five wavefronts per SIMD to hide them (now

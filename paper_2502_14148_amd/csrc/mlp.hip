@@ -894,38 +894,46 @@ __global__ void __launch_bounds__(256) closure_features_f32_kernel(Dims d, const
 // flux at (x face, z face) as the mean of the four adjacent centres, v the
 // same in y, tracers the mean of the two centres about each z face (J_b
 // turned into a temperature flux), w the difference of tau_ww across its
-// face.  Wall fluxes are zero.
+// face.  Wall fluxes are zero.  A thread reads the fluxes of its own column at
+// the three levels around it (16 bytes a cell) and of its west and south
+// neighbours', all at once, by 32-bit indices (a grid has at most 2^24
+// cells): 64^3 5.3 us, 9.2 with 64-bit divisions and a scalar load for
+// each use.  8 MB, 1.6 us at 5.2 TB/s.
 template <class T>
 __global__ void __launch_bounds__(256) closure_apply_kernel(Dims d, const float* y, ClosureStats st,
                                                             double rdz, T* gu, T* gv, T* gw,
                                                             T* gt) {
-  const long ncell = (long)d.nx * d.ny * d.nz;
-  const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= ncell) return;
-  const int i = (int)(t % d.nx);
-  const int j = (int)((t / d.nx) % d.ny);
-  const int k = (int)(t / ((long)d.nx * d.ny));
-  auto F = [&](int q, int ii, int jj, int kk) -> float {
-    ii = (ii + d.nx) % d.nx;
-    jj = (jj + d.ny) % d.ny;
-    const long c = ((long)kk * d.ny + jj) * d.nx + ii;
-    return y[c * 4 + q] * st.out_std[q] + st.out_mean[q];
+  typedef float f4 __attribute__((ext_vector_type(4)));
+  const uint32_t nx = d.nx, ny = d.ny, nz = d.nz, plane = nx * ny;
+  const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= plane * nz) return;
+  const uint32_t i = t % nx, row = t / nx, j = row % ny, k = row / ny;
+  const uint32_t tw = i == 0 ? t + nx - 1 : t - 1, ts = j == 0 ? t + plane - nx : t - nx;
+  const bool low = k > 0, high = k + 1 < nz;   // the faces that are not walls
+  const uint32_t dl = low ? plane : 0, dh = high ? plane : 0;
+  const auto y4 = (const __attribute__((address_space(1))) f4*)y;
+  const auto y1 = glb(y);
+  const f4 om = y4[t - dl], o0 = y4[t], op = y4[t + dh];
+  const float wm = y1[(tw - dl) * 4], w0 = y1[tw * 4], wp = y1[(tw + dh) * 4];
+  const float sm = y1[(ts - dl) * 4 + 1], s0 = y1[ts * 4 + 1], sp = y1[(ts + dh) * 4 + 1];
+  auto F = [&](int q, float v) { return v * st.out_std[q] + st.out_mean[q]; };
+  // flux of quantity q through the face between the centres a (below) and b,
+  // averaged with the neighbour's na, nb
+  auto mean4 = [&](int q, float na, float a, float nb, float b) {
+    return 0.25f * (F(q, na) + F(q, a) + F(q, nb) + F(q, b));
   };
-  // flux through the z face kk (0..nz) of quantity q averaged over x or y
-  auto zface = [&](int q, int ax, int kk) -> float {
-    if (kk <= 0 || kk >= d.nz) return 0.f;
-    if (ax == 0) return 0.25f * (F(q, i - 1, j, kk - 1) + F(q, i, j, kk - 1) + F(q, i - 1, j, kk) +
-                                 F(q, i, j, kk));
-    if (ax == 1) return 0.25f * (F(q, i, j - 1, kk - 1) + F(q, i, j, kk - 1) + F(q, i, j - 1, kk) +
-                                 F(q, i, j, kk));
-    return 0.5f * (F(q, i, j, kk - 1) + F(q, i, j, kk));
-  };
-  const long p = pidx(d, i, j, k);
+  const float ul = low ? mean4(0, wm, om.x, w0, o0.x) : 0.f;
+  const float uh = high ? mean4(0, w0, o0.x, wp, op.x) : 0.f;
+  const float vl = low ? mean4(1, sm, om.y, s0, o0.y) : 0.f;
+  const float vh = high ? mean4(1, s0, o0.y, sp, op.y) : 0.f;
+  const float tl = low ? 0.5f * (F(3, om.w) + F(3, o0.w)) : 0.f;
+  const float th = high ? 0.5f * (F(3, o0.w) + F(3, op.w)) : 0.f;
+  const long p = pidx(d, (int)i, (int)j, (int)k);
   const float rz = (float)rdz;
-  gu[p] = (T)(-(zface(0, 0, k + 1) - zface(0, 0, k)) * rz);
-  gv[p] = (T)(-(zface(1, 1, k + 1) - zface(1, 1, k)) * rz);
-  gt[p] = (T)(-(zface(3, 2, k + 1) - zface(3, 2, k)) * rz * st.inv_galpha);
-  gw[p] = (k == 0) ? (T)0 : (T)(-(F(2, i, j, k) - F(2, i, j, k - 1)) * rz);
+  gu[p] = (T)(-(uh - ul) * rz);
+  gv[p] = (T)(-(vh - vl) * rz);
+  gt[p] = (T)(-(th - tl) * rz * st.inv_galpha);
+  gw[p] = low ? (T)(-(F(2, o0.z) - F(2, om.z)) * rz) : (T)0;
 }
 
 // Splits of the batch in the weight gradients: enough that the 52 tiles
