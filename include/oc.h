@@ -129,7 +129,10 @@ typedef struct {
                                8).  Orders 7 and 9 widen the halo to 4 and 5
                                cells and are nonhydrostatic-only; ensembles
                                take WENO5-Z */
-  double weno_eps;          /* WENO-Z regulariser (> 0) */
+  double weno_eps;          /* WENO-Z regulariser (> 0).  WENO5-Z squares it:
+                               16 eps^2 has to be a normal number of the
+                               state's type (OC_FP32_MIXED: eps >= 2.8e-20),
+                               else flat stencils give NaN */
   int32_t weno_q;           /* WENO-Z exponent; only 2 is supported */
   int32_t ntracers;         /* 1..OC_MAX_TRACERS */
   int32_t buoyancy;         /* 1: tracers 0, 1 are T, S and b = g(alpha(T-T0) - beta(S-S0)) */

@@ -334,3 +334,32 @@ def test_tendency_edge_faces(gpu_lib, n, tracers, advection, precision):
     for name in m.fields:
         err = rel_l2(m.get_tendency(name), G[name])
         assert err <= TOL[precision], (n, name, err)
+
+
+@pytest.mark.parametrize("precision,eps", [("fp32", 3e-20), ("fp32", 1e-15), ("fp64", 5e-155)])
+@pytest.mark.parametrize("moving", [False, True])
+def test_weno_regulariser_range(gpu_lib, precision, eps, moving):
+    """Stencils that are exactly flat, fully or in part, at regularisers down
+    to the smallest whose weights the type can hold (16 eps^2 a normal
+    number); at rest every momentum stencil is flat.  (Amplitudes of 0.02:
+    next to a flat stencil the square of an indicator over eps has to stay
+    in range too.  Tracers without a mean: the divergence that rounding the
+    velocities leaves, times a mean of 20, is 4e-5 of the tendency in FP32.)"""
+    ph = small_convection(32, 16, 16)
+    ph.weno_eps, ph.t_ref, ph.s_ref = eps, 0.0, 0.0
+    s = inputs.random_state(ph, seed=61, vel=0.02, tracer_means=(0.0, 0.0), tracer_scale=0.02)
+    rng = np.random.default_rng(62)
+    for name in ("T", "S"):
+        patches = np.repeat(rng.random((ph.nz, ph.ny, ph.nx // 8)) < 0.6, 8, axis=2)
+        s[name] = np.where(patches, 0.0, s[name])
+    if not moving:
+        for name in ("u", "v", "w"):
+            s[name] = np.zeros_like(s[name])
+    s = _prep(s, ph, precision)
+    m = gpu_lib.Model(ph, precision)
+    m.set_states(s)
+    m.tendencies()
+    G = td.tendencies(timestep.make_state(s, ph), ph)
+    for name in m.fields:
+        err = rel_l2(m.get_tendency(name), G[name])
+        assert err <= TOL[precision], (eps, moving, name, err)
