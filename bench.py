@@ -524,8 +524,9 @@ def run_immersed(steps, warmup, n):
     ncells = n ** 3
     solves = 3 * steps
     t_fft = sum(prof[k][0] for k in ("fft_x_fwd", "fft_y_fwd", "z_solve", "fft_y_inv", "fft_x_inv"))
-    n_fft = prof["fft_x_fwd"][1]           # preconditioner applications
-    iters_per_solve = n_fft / solves - 1   # one application before the first iteration
+    # box solves: the starting iterate, one per iteration, and the one for p
+    n_fft = prof["fft_x_fwd"][1]
+    iters_per_solve = n_fft / solves - 2
     cg_ms = prof["cg"][0]
     return {"value": ncells * steps / (ms / 1e3), "unit": "cell-steps/s", "steps": steps,
             "warmup": warmup, "ms_per_step": ms / steps, "dtype": "f32",

@@ -191,7 +191,10 @@ typedef struct {
                                with implicit_z, les or closure */
   double cg_tol;            /* immersed: relative residual at which the
                                iteration stops (> 0, e.g. 1e-13 in FP64) */
-  int32_t cg_maxiter;       /* immersed: at most this many iterations (1..10000) */
+  int32_t cg_maxiter;       /* immersed: at most this many iterations (1..10000);
+                               the iteration starts from the FFT solve of the
+                               right-hand side, which is not counted unless it
+                               meets cg_tol by itself (then it is the one) */
 } oc_model_desc;
 
 typedef struct oc_grid oc_grid;
@@ -282,8 +285,10 @@ int oc_implicit_vertical_diffusion(oc_model* m, double dt_eff, void* stream);
 int oc_set_immersed(oc_model* m, const uint8_t* solid, void* stream);
 
 /* Conjugate-gradient statistics of the last pressure solve of an immersed
- * model: iterations taken and the final relative residual |r| / |b| (host
- * outputs; synchronises the stream).  Errors: OC_ERR_ARG, OC_ERR_UNSUPPORTED
+ * model: iterations taken (counted as for cg_maxiter) and the final relative
+ * residual |r| / |b|, r as the iteration carries it: on the fluid cells next
+ * to immersed ones (elsewhere it is zero but for rounding).  Host outputs;
+ * synchronises the stream.  Errors: OC_ERR_ARG, OC_ERR_UNSUPPORTED
  * (immersed = 0). */
 int oc_pressure_stats(oc_model* m, int32_t* iterations, double* rel_residual, void* stream);
 

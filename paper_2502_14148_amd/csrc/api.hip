@@ -585,7 +585,7 @@ int box_solve(oc_model* m, const double* src, const SpecBufs& sb, int npass, hip
 // Pressure correction with an immersed boundary: conjugate gradients on the
 // masked Poisson equation, preconditioned by the FFT solve of the whole box,
 // until |r| <= cg_tol |b| or cg_maxiter iterations (immersed.hip describes the
-// iteration; the first one is the iterate P L^-1 b).  The scalars of an
+// iteration; it starts from the iterate P L^-1 b).  The scalars of an
 // iteration stay on the device, and every kernel of an iteration does
 // nothing once the stop flag is set, so the host need not look at the flag
 // after every iteration: it first looks after one iteration fewer than the
@@ -621,10 +621,10 @@ int pressure_call_immersed(oc_model* m, int which, double dt_eff, hipStream_t s)
   if (rc) return rc;
   {
     ProfScope pc(m, OC_PROF_CG, s);
-    OC_CHECK_HIP(launch_ib_start(d, m->ibits, rdx2, rdy2, rdz2, cg, z, tol2, maxit, s));
+    OC_CHECK_HIP(launch_ib_start(d, m->ibits, rdx2, rdy2, rdz2, cg, z, tol2, s));
   }
-  const int first_look = std::max(1, m->cg_iterations - 1);
-  for (int it = 1;; ++it) {
+  const int first_look = m->cg_iterations - 1;
+  for (int it = 0;; ++it) {                  // it iterations are queued
     if (it >= first_look || it >= maxit) {   // the last iteration always looks
       OC_CHECK_HIP(hipMemcpyAsync(m->cg_host, cg.scal, CG_NSCAL * sizeof(double),
                                   hipMemcpyDeviceToHost, s));

@@ -174,17 +174,21 @@ __device__ inline double apply_at(const ListGeom& g, const double* __restrict__ 
          (dif(IB_ZM, zm) + dif(IB_ZP, zp)) * g.rdz2;
 }
 
-// Stopping test after an iteration with squared residual r2.
+// Stopping test after an iteration (an update of the iterate) with squared
+// residual r2.
 __device__ inline void stop_test(double* sc, double r2, double tol2, int maxiter) {
   sc[CG_RNORM2] = r2;
   sc[CG_IT] += 1.0;
   if (r2 <= tol2 * sc[CG_BNORM2] || sc[CG_IT] >= (double)maxiter) sc[CG_DONE] = 1.0;
 }
 
-// After z = L^-1 b: r = b - A P z, |b|^2 and |r|^2.
+// After z = L^-1 b: r = b - A P z, |b|^2 and |r|^2.  The iterate P z precedes the
+// iterations that are counted and limited (k of them from here leave a smaller
+// residual than k from p = 0); only where it meets the tolerance by itself is
+// it one.
 __global__ void __launch_bounds__(IB_NT) ib_start_kernel(ListGeom g, CgBufs cg,
                                                          const double* __restrict__ z,
-                                                         double tol2, int maxiter) {
+                                                         double tol2) {
   __shared__ double sh[1][IB_NT];
   double v[1] = {0.0};
   for (int e = blockIdx.x * IB_NT + threadIdx.x; e < cg.n; e += gridDim.x * IB_NT) {
@@ -205,11 +209,12 @@ __global__ void __launch_bounds__(IB_NT) ib_start_kernel(ListGeom g, CgBufs cg,
   sc[CG_BNORM2] = b2[0];
   sc[CG_RZ] = 0.0;
   sc[CG_QAQ] = 0.0;
+  sc[CG_RNORM2] = b2[0] == 0.0 ? 0.0 : v[0];
   if (b2[0] == 0.0) {   // nothing to solve: no iteration
-    sc[CG_RNORM2] = 0.0;
     sc[CG_DONE] = 1.0;
-  } else {
-    stop_test(sc, v[0], tol2, maxiter);
+  } else if (v[0] <= tol2 * b2[0]) {
+    sc[CG_IT] = 1.0;
+    sc[CG_DONE] = 1.0;
   }
 }
 
@@ -389,11 +394,10 @@ static int list_grid(const CgBufs& cg) {
 }
 
 hipError_t launch_ib_start(const Dims& d, const uint8_t* bits, double rdx2, double rdy2,
-                           double rdz2, const CgBufs& cg, const double* z, double tol2, int maxiter,
+                           double rdz2, const CgBufs& cg, const double* z, double tol2,
                            hipStream_t s) {
   const ListGeom g{d, bits, rdx2, rdy2, rdz2};
-  hipLaunchKernelGGL(ib_start_kernel, dim3(list_grid(cg)), dim3(IB_NT), 0, s, g, cg, z, tol2,
-                     maxiter);
+  hipLaunchKernelGGL(ib_start_kernel, dim3(list_grid(cg)), dim3(IB_NT), 0, s, g, cg, z, tol2);
   return hipGetLastError();
 }
 

@@ -501,7 +501,7 @@ hipError_t launch_ib_rhs(const Dims& d, const T* u, const T* v, const T* w,
 // After z = L^-1 b: the first iterate P z; r = b - A P z on the list, |r|^2
 // and the stopping test.
 hipError_t launch_ib_start(const Dims& d, const uint8_t* bits, double rdx2, double rdy2,
-                           double rdz2, const CgBufs& cg, const double* z, double tol2, int maxiter,
+                           double rdz2, const CgBufs& cg, const double* z, double tol2,
                            hipStream_t s);
 // One iteration after z = L^-1 r: A z, the scalars, and the updates.
 hipError_t launch_ib_iterate(const Dims& d, const uint8_t* bits, double rdx2, double rdy2,

@@ -265,3 +265,36 @@ def test_full_size_seamount(gpu_lib):
     want = -jt * dx * dy * np.sum(~ph.solid[-1]) * 1.0
     got = d["tracer_integrals"][0] - before
     assert abs(got - want) < 1e-3 * abs(want), (got, want)
+
+
+@pytest.mark.parametrize("maxiter", [1, 2, 4])
+@pytest.mark.parametrize("case", ["seamount_32x32x16", "ridge_16x16x16"])
+def test_stopped_by_the_iteration_limit(gpu_lib, case, maxiter):
+    """A solve that cg_maxiter stops reports that many iterations, and is no
+    further from the solution than as many of the textbook iteration from
+    p = 0 with the same preconditioner."""
+    ph, _ = make_case(case)
+    ph = dataclasses.replace(ph, cg_maxiter=maxiter)
+    s = inputs.random_state(ph, seed=21, divergence_free=False)
+    m = gpu_lib.Model(ph, "fp64")
+    m.set_states(s)
+    m.pressure_solve(0.37)
+    it, res = m.pressure_stats()
+    assert it == maxiter
+
+    w = s["w"].copy()
+    w[0] = w[-1] = 0.0
+    fluid = immersed.fluid(ph)
+    b = pressure.divergence(*immersed.mask_velocities(s["u"], s["v"], w, ph), ph) * fluid / 0.37
+    x, r, q, rz0 = np.zeros_like(b), b.copy(), 0.0, 1.0
+    for n in range(maxiter):
+        z = pressure.solve_poisson(r, ph) * fluid
+        rz = np.sum(r * z)
+        q = z + (rz / rz0 if n else 0.0) * q
+        aq = immersed.laplacian(q, ph)
+        alpha, rz0 = rz / np.sum(q * aq), rz
+        x, r = x + alpha * q, r - alpha * aq
+    x = (x - np.mean(x[fluid > 0])) * fluid
+    exact = immersed.solve_poisson_immersed(b, ph)
+    assert rel_l2(m.get_pressure(), exact) <= rel_l2(x, exact)
+    assert res <= np.linalg.norm(r) / np.linalg.norm(b)
