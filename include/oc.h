@@ -436,7 +436,7 @@ int oc_mlp_destroy(oc_mlp* m);
 int oc_mlp_set_params(oc_mlp* m, const float* params, void* stream);
 int oc_mlp_get_params(oc_mlp* m, float* params, void* stream);
 /* y (device, batch x 4 FP32) = MLP(x) for x (device, batch x 500 FP32);
- * batch a multiple of 32 up to max_batch. */
+ * batch a multiple of 32 up to max_batch.  y may lie within x. */
 int oc_mlp_forward(oc_mlp* m, const float* x, int32_t batch, float* y, void* stream);
 /* Gradients of the mean squared error mean((y - target)^2) over the batch
  * (target: device, batch x 4) into grad (device, OC_MLP_NPARAM FP32, packed

@@ -202,7 +202,15 @@ int oc_mlp_forward(oc_mlp* m, const float* x, int32_t batch, float* y, void* str
   int rc = check_batch(m, batch);
   if (rc) return rc;
   if (!x || !y) { set_error("NULL argument"); return OC_ERR_ARG; }
-  OC_CHECK_HIP(launch_mlp_forward(m->p, x, batch, y, (hipStream_t)stream));
+  hipStream_t s = (hipStream_t)stream;
+  // outputs that lie in the rows: the kernel's workgroups store theirs while
+  // others still read, so they go through the handle's own
+  const uintptr_t x0 = (uintptr_t)x, y0 = (uintptr_t)y;
+  const size_t nx = (size_t)batch * MLP_NIN * 4, ny = (size_t)batch * MLP_NOUT * 4;
+  const bool overlap = y0 < x0 + nx && x0 < y0 + ny;
+  float* out = overlap ? m->y : y;
+  OC_CHECK_HIP(launch_mlp_forward(m->p, x, batch, out, s));
+  if (overlap) OC_CHECK_HIP(hipMemcpyAsync(y, out, ny, hipMemcpyDeviceToDevice, s));
   return OC_OK;
 }
 

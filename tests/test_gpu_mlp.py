@@ -210,3 +210,25 @@ def test_gradient_block_counts(gpu_lib, B):
     for k in go:
         step = -1e-3 * g[k] / (np.abs(g[k]) + 1e-8)
         assert np.max(np.abs((q[k] - p[k]) - step)) < 1e-6, k
+
+
+@pytest.mark.parametrize("B,at", [(32, 0), (4096, 0), (4096, 4 * 37 + 1), (32800, 500 * 32799)])
+def test_forward_into_its_own_rows(gpu_lib, B, at):
+    """Outputs stored over the rows they come from, at the start of the
+    buffer, at an odd element of it, and across its end: the values of a call
+    with a buffer of its own, and nothing beside them touched."""
+    import ctypes
+    import torch
+    p, X, _ = _data(10, B)
+    net = gpu_lib.Mlp(B)
+    net.set_params(p)
+    x = _dev(X)
+    y = net.forward(x)
+    buf = torch.full((B * 500 + B * 4,), 7.0, device="cuda")
+    buf[:B * 500] = x.reshape(-1)
+    before = buf.clone()
+    out = buf[at:at + 4 * B]
+    gpu_lib._check(gpu_lib._lib.oc_mlp_forward(net._h, ctypes.c_void_p(buf.data_ptr()), B,
+                                               ctypes.c_void_p(out.data_ptr()), gpu_lib._stream()))
+    assert torch.equal(out.reshape(B, 4), y)
+    assert torch.equal(buf[:at], before[:at]) and torch.equal(buf[at + 4 * B:], before[at + 4 * B:])
