@@ -256,6 +256,24 @@ struct StageCopy {
 // load-to-LDS copies among them).
 __device__ inline void wait_vm() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
+// Stores that every wave with an active lane issues in a level, past the barrier
+// that follows the copies of the next level: the tendency and the stepped value
+// of u, v, T and S.  wait_copies waits for all memory operations but this many
+// of the newest, so for the copies without the stores: memory operations retire
+// in the order they were issued.  It would return early, with planes still being
+// copied, if a wave issued fewer; more (the level's loads, both branches of a
+// wave that holds a wall row) are waited for without need but do no harm.
+// So each of the eight stands on every path of an active lane (level_store).
+constexpr int LEVEL_STORES = 2 * 4;
+__device__ inline void wait_copies() {
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LEVEL_STORES) : "memory");
+}
+// One of the LEVEL_STORES.
+template <class T>
+__device__ inline void level_store(T* level, unsigned off, T value) {
+  at(uniform_ptr(level), off) = value;
+}
+
 template <class T, int SCHEME>
 __global__ void __launch_bounds__(TTX * TTY)
     hydro_tend_kernel(HydroBufs<T> a, HydroStep<T> st) {
@@ -488,8 +506,8 @@ __global__ void __launch_bounds__(TTX * TTY)
         G += (Nu1 - Nu) * rdz;
         T comb = a1 * G;
         if (!first) comb -= a0 * gu0;
-        at(uniform_ptr(a.Gu + kz), cb) = G;
-        at(uniform_ptr(a.uo + kz), cb) = u_c + dt * comb;
+        level_store(a.Gu + kz, cb, G);
+        level_store(a.uo + kz, cb, u_c + dt * comb);
         gu += (double)comb;
       }
       // ---- v point (x centre i, y face j)
@@ -507,12 +525,12 @@ __global__ void __launch_bounds__(TTX * TTY)
         G += (Nv1 - Nv) * rdz;
         T comb = a1 * G;
         if (!first) comb -= a0 * gv0;
-        at(uniform_ptr(a.Gv + kz), cb) = G;
-        at(uniform_ptr(a.vo + kz), cb) = v_c + dt * comb;
+        level_store(a.Gv + kz, cb, G);
+        level_store(a.vo + kz, cb, v_c + dt * comb);
         gv += (double)comb;
-      } else {
-        at(uniform_ptr(a.Gv + kz), cb) = T(0);
-        at(uniform_ptr(a.vo + kz), cb) = T(0);
+      } else {   // the wall face; stored also because wait_copies counts it
+        level_store(a.Gv + kz, cb, T(0));
+        level_store(a.vo + kz, cb, T(0));
       }
       // ---- tracers at centre (i, j)
 #pragma unroll
@@ -522,11 +540,10 @@ __global__ void __launch_bounds__(TTX * TTY)
         const T fy0 = FY[q][ty * TTX + tx], fy1 = FY[q][(ty + 1) * TTX + tx];
         const T Fz0 = q ? Fs : Ft, Fz1 = q ? Fs1 : Ft1;
         const T G = -((fx1 - fx0) + (fy1 - fy0) + (Fz1 - Fz0)) * rvol;
-        global_ptr<T> Gq = uniform_ptr((q ? a.Gs : a.Gt) + kz);
         T comb = a1 * G;
         if (!first) comb -= a0 * gt0[q];
-        at(Gq, cb) = G;
-        at(uniform_ptr((q ? a.so : a.to) + kz), cb) = cc + dt * comb;
+        level_store((q ? a.Gs : a.Gt) + kz, cb, G);
+        level_store((q ? a.so : a.to) + kz, cb, cc + dt * comb);
       }
 
       // ---- carry face k + 1 up; shift the windows
@@ -541,10 +558,9 @@ __global__ void __launch_bounds__(TTX * TTY)
       uw[5] = u4; vw[5] = v4; tw[5] = t4; sw[5] = s4;
     }
     // the copies of level k + 1 have landed (this wave's), and every wave is
-    // done with this level's planes and flux arrays.  Memory operations retire
-    // in the order they were issued, and a wave with an active lane has issued
-    // its eight stores after the copies: they need not be waited for.
-    if (__any(active)) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+    // done with this level's planes and flux arrays; the stores of a wave that
+    // has an active lane need not be waited for
+    if (__any(active)) wait_copies();
     else wait_vm();
     __syncthreads();
   }
