@@ -206,37 +206,6 @@ __global__ void baro_fill_kernel(double* a, double v, long n) {
   if (t < n) a[t] = v;
 }
 
-// u <- u + (Ubar - dz sum_k u) / H on every column of a 3D field stored in
-// the padded layout; `nyf` rows (v: the interior faces 1..ny-1 only).
-template <class T>
-__global__ void baro_correct_kernel(Dims d, T* __restrict__ f, const double* __restrict__ bar,
-                                    int j_lo, int j_hi, double dz, double inv_h) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  const int j = j_lo + blockIdx.y;
-  if (i >= d.nx || j >= j_hi) return;
-  const long c0 = pidx(d, i, j, 0);
-  // levels fetched CKB at a time so that their loads are in flight together
-  constexpr int CKB = 10;
-  double sum = 0.0;
-  for (int k0 = 0; k0 < d.nz; k0 += CKB) {
-    T x[CKB];
-#pragma unroll
-    for (int q = 0; q < CKB; ++q) x[q] = f[c0 + (long)min(k0 + q, d.nz - 1) * d.sz];
-#pragma unroll
-    for (int q = 0; q < CKB; ++q)
-      if (k0 + q < d.nz) sum += (double)x[q];
-  }
-  const double corr = (bar[(long)j * d.nx + i] - dz * sum) * inv_h;
-  for (int k0 = 0; k0 < d.nz; k0 += CKB) {
-    T x[CKB];
-#pragma unroll
-    for (int q = 0; q < CKB; ++q) x[q] = f[c0 + (long)min(k0 + q, d.nz - 1) * d.sz];
-#pragma unroll
-    for (int q = 0; q < CKB; ++q)
-      if (k0 + q < d.nz) f[c0 + (long)(k0 + q) * d.sz] = (T)((double)x[q] + corr);
-  }
-}
-
 }  // namespace
 
 hipError_t launch_baro_fill(double* a, double v, long n, hipStream_t s) {

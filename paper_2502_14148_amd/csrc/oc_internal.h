@@ -299,7 +299,7 @@ template <class T>
 hipError_t launch_hydro_halo(const Dims& d, T* u, T* v, T* t, T* sf, hipStream_t s);
 
 // ---- MLP closure (500 -> 256 -> 256 -> 4; device widths 512 and 32)
-constexpr int MLP_NIN = 500, MLP_NH = 256, MLP_NOUT = 4, MLP_KIN = 512, MLP_NOUTP = 32;
+constexpr int MLP_NIN = 500, MLP_NH = 256, MLP_NOUT = 4, MLP_KIN = 512;
 constexpr int MLP_OFF_W1 = 0;
 constexpr int MLP_OFF_B1 = MLP_OFF_W1 + MLP_NH * MLP_NIN;
 constexpr int MLP_OFF_W2 = MLP_OFF_B1 + MLP_NH;
