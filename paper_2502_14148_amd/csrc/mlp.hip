@@ -48,8 +48,8 @@ __device__ void mlp_write_bf16(const MlpParams& p, int t, float w) {
 namespace {
 
 // erf(z / sqrt 2) and exp(-z^2 / 2) by Abramowitz & Stegun, formula 7.1.26
-// (absolute error of erf at most 1.5e-7, far below the BF16 rounding the
-// activations get next): for x >= 0, erf x = 1 - t P(t) exp(-x^2),
+// (absolute error of erf at most 1.5e-7; evaluated in FP32 5.1e-7, and 2.9e-7 in
+// the GELU derivative it serves): for x >= 0, erf x = 1 - t P(t) exp(-x^2),
 // t = 1 / (1 + p x), P a quartic; erf is odd.  About a dozen full-rate
 // instructions, a reciprocal and an exponential: the activation epilogues
 // are the bulk of the fused kernel's vector instructions.
@@ -68,7 +68,11 @@ __device__ inline ErfGauss erf_gauss(float z) {
 // erf(z / sqrt 2) alone by Abramowitz & Stegun, formula 7.1.28 (absolute
 // error at most 3e-7): for x >= 0, erf x = 1 - (1 + a1 x + ... + a6 x^6)^-16,
 // here with the 1/sqrt 2 folded into the coefficients.  One reciprocal and
-// no exponential.
+// no exponential.  Evaluated in FP32 the error is 1.9e-6 (the sixteenth power
+// multiplies the rounding of the reciprocal, near z = 0), that of the GELU
+// 7.7e-7.  Relative to the GELU it is below the rounding to BF16 (2e-3) for
+// z > -3.5; in the tail beyond, where the GELU is under 8.2e-4, it reaches 2 %
+// at z = -4.5 and 10 % at -5.
 __device__ inline float erf_sqrt2(float z) {
   const float az = fabsf(z);
   float q = fmaf(0.0000430638f / 8.0f, az, 0.0002765672f / 5.65685424949238f);
