@@ -105,7 +105,10 @@ __device__ inline P opaque(P p) {
 // 5 fields, with every chunk of 32 levels at most and the images tested at
 // each level, and now: 256x256x128 FP32 149 -> 91 us, 256x256x200 FP32
 // 199 -> 168, 128x128x64 FP64 37.5 -> 24, 128x128x256 FP64 95 -> 87, 64x64x32
-// FP32 15 -> 9.6.  (16 chunks instead of 8: 123 us for the first.)
+// FP32 15 -> 9.6.  (16 chunks instead of 8: 123 us for the first.)  Long columns
+// of short rows, by events around the launch: 64x64x256 FP32 36.3 -> 33.4, FP64
+// 44.4 -> 39.9, 32x64x256 FP32 27.3 -> 25.8 (39.7, 48.9 and 30.1 with a pass of
+// images for each side).
 template <class T, int CM>
 __global__ void __launch_bounds__(64 * VCH) vimplicit_kernel(Dims d, VImplicitArgs<T> a) {
   __shared__ T endv[VCH][64];
@@ -199,19 +202,23 @@ __global__ void __launch_bounds__(64 * VCH) vimplicit_kernel(Dims d, VImplicitAr
 #pragma unroll
   for (int r = 0; r < CM; ++r) x[r] += Q[min(q0 + r, n - 1)] * xin;
   // The column, then its periodic x / y images (of the h columns next to each
-  // side; one at both ends of an axis shorter than 2H): image m is shifted by
-  // a length of x (m % 3 = 1 up, 2 down) and of y (m / 3).  A combination that
-  // no lane has is passed over whole, so the interior pays for it once per
-  // column and not once per level.
+  // side): image m is shifted by a length of x (m % 3) and of y (m / 3): 1 is the
+  // image past the other end, up for a column next to the start and down for one
+  // next to the end (one pass for both: a wave of a row of 64 holds both); 2 the
+  // second image, down, of a column within reach of both ends of an axis shorter
+  // than 2H.  A combination that no lane has is passed over whole, so the
+  // interior pays for it once per column and not once per level.
   const bool edge = k0 + q0 <= H || k0 + q1 >= d.nz - H;   // levels with mirror images
 #pragma unroll 1
   for (int m = 0; m < 9; ++m) {
     const int mx = m % 3, my = m / 3;
-    const bool has = (mx == 0 || (mx == 1 ? i < H : i >= d.nx - H)) &&
-                     (my == 0 || (my == 1 ? j < H : j >= d.ny - H));
+    const bool xl = i < H, xh = i >= d.nx - H, yl = j < H, yh = j >= d.ny - H;
+    const bool has = (mx == 0 || (mx == 1 ? xl || xh : xl && xh)) &&
+                     (my == 0 || (my == 1 ? yl || yh : yl && yh));
     if (!has) continue;
-    const uint32_t at = own + (uint32_t)((mx == 1 ? d.nx : mx == 2 ? -d.nx : 0) +
-                                         (my == 1 ? d.ny : my == 2 ? -d.ny : 0) * (int)d.sy);
+    const int ox = mx == 0 ? 0 : mx == 1 && xl ? d.nx : -d.nx;
+    const int oy = my == 0 ? 0 : my == 1 && yl ? d.ny : -d.ny;
+    const uint32_t at = own + (uint32_t)(ox + oy * (int)d.sy);
     // (opaque: the level addresses and signed values are formed here instead
     // of being kept for all levels across the combinations, which spills)
     const int kb = opaque(k0 + q0), nl = opaque(q1 - q0), odd = opaque(wface);
