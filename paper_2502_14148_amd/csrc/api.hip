@@ -47,7 +47,7 @@ struct Layout {
   uint64_t baro[15], metric, hzeta, hpx, hpy, hmet;
   uint64_t gc[MAXF];
   uint64_t les_nu, les_kap[OC_MAX_TRACERS], les_d2;
-  uint64_t mask, ibits, cg_b, cg_r, cg_idx, cg_s, cg_q, cg_aq, cg_az, cg_part, cg_scal;
+  uint64_t mask, ibits, cg_b, cg_r, cg_idx, cg_s, cg_aq, cg_part, cg_scal;
   uint64_t zt64, ztT, vfac;
   uint64_t total;
 };
@@ -110,9 +110,7 @@ Layout make_layout(const oc_grid_desc& g, const oc_model_desc& m) {
     // list vectors: the list may hold almost every cell
     L.cg_idx = off; off += align256((uint64_t)g.nx * g.ny * g.nz * 4);
     L.cg_s = off; off += nv;
-    L.cg_q = off; off += nv;
     L.cg_aq = off; off += nv;
-    L.cg_az = off; off += nv;
     L.cg_part = off; off += align256((uint64_t)(IB_PART_CAP + IB_NPART) * 8);
     L.cg_scal = off; off += align256((uint64_t)CG_NSCAL * 8 + 8);   // and the ticket
   }
@@ -1407,9 +1405,8 @@ int oc_model_create(const oc_grid* g, const oc_model_desc* md, void* workspace,
   m->cg.r = (double*)(m->ws + L.cg_r);
   m->cg.idx = (const int*)(m->ws + L.cg_idx);
   m->cg.s = (double*)(m->ws + L.cg_s);
-  m->cg.q = (double*)(m->ws + L.cg_q);
   m->cg.aq = (double*)(m->ws + L.cg_aq);
-  m->cg.az = (double*)(m->ws + L.cg_az);
+  m->cg.az = (double*)m->sb.spec;   // at least nx numbers a row
   m->cg.part = (double*)(m->ws + L.cg_part);
   m->cg.bpart = m->cg.part + IB_PART_CAP;
   m->cg.scal = (double*)(m->ws + L.cg_scal);

@@ -14,9 +14,10 @@
 // all fluid cells but those next to immersed ones (the list): starting from
 // the iterate P L^-1 b, every residual, and every A q of a direction q = P
 // L^-1 s, is zero off the list.  The iteration therefore keeps the vectors r,
-// s, q, A q on the list alone (1 to 2 % of the cells of a seamount) and A q by
-// its recurrence A q = A z + beta A q; it needs z = L^-1 r only on the list and
-// its neighbours, and the FFT passes skip the levels and rows where the
+// s and A q on the list alone (1 to 2 % of the cells of a seamount), A q by its
+// recurrence A q = A z + beta A q; q itself is not formed (its products are
+// taken with A q, which A's symmetry allows).  It needs z = L^-1 r only on the
+// list and its neighbours, and the FFT passes skip the levels and rows where the
 // residual is zero or the result unused.  The steps are summed as
 // sum alpha s, and the solution is p = L^-1 (b + sum alpha s), one more solve
 // whose last pass is the projection's.  Against the iteration on dense
@@ -196,7 +197,6 @@ __global__ void __launch_bounds__(IB_NT) ib_start_kernel(ListGeom g, CgBufs cg,
     const double r = cg.b[n] - apply_at(g, z, n, z[n]);
     cg.r[n] = r;
     cg.s[e] = 0.0;
-    cg.q[e] = 0.0;
     cg.aq[e] = 0.0;
     v[0] += r * r;
   }
@@ -218,26 +218,24 @@ __global__ void __launch_bounds__(IB_NT) ib_start_kernel(ListGeom g, CgBufs cg,
   }
 }
 
-// The scalars of an iteration from r.z, z.Az and q_old.Az: beta = (r.z) / (r.z)_old
-// (0 at first), and with q = z + beta q_old the q.Aq = z.Az + 2 beta q_old.Az +
-// beta^2 q_old.Aq_old (A is symmetric), so alpha is known before q is formed.
-__device__ inline void scalars(double* sc, double rz, double zaz, double qaz) {
+// The scalars of an iteration from r.z, z.Az and z.Aq_old: beta = (r.z) / (r.z)_old
+// (0 at first), and with q = z + beta q_old the q.Aq = z.Az + 2 beta z.Aq_old +
+// beta^2 q_old.Aq_old (A is symmetric), so alpha is known before A q is updated.
+__device__ inline void scalars(double* sc, double rz, double zaz, double zaq) {
   const double beta = sc[CG_RZ] == 0.0 ? 0.0 : rz / sc[CG_RZ];
-  const double qaq = zaz + beta * (2.0 * qaz + beta * sc[CG_QAQ]);
+  const double qaq = zaz + beta * (2.0 * zaq + beta * sc[CG_QAQ]);
   sc[CG_RZ] = rz;
   sc[CG_BETA] = beta;
   sc[CG_QAQ] = qaq;
   sc[CG_ALPHA] = rz / qaq;
 }
 
-// The updates of list entry e (cell n): s = r + beta s, q = z + beta q, A q =
-// A z + beta A q; the step alpha s into b; r -= alpha A q.  Returns the new r.
-__device__ inline double take_step(const CgBufs& cg, int e, int n, double z0, double az,
-                                   double alpha, double beta) {
+// The updates of list entry e (cell n): s = r + beta s, A q = A z + beta A q; the
+// step alpha s into b; r -= alpha A q.  Returns the new r.
+__device__ inline double take_step(const CgBufs& cg, int e, int n, double alpha, double beta) {
   const double r0 = cg.r[n];
-  const double s = r0 + beta * cg.s[e], aq = az + beta * cg.aq[e];
+  const double s = r0 + beta * cg.s[e], aq = cg.az[e] + beta * cg.aq[e];
   cg.s[e] = s;
-  cg.q[e] = z0 + beta * cg.q[e];
   cg.aq[e] = aq;
   cg.b[n] += alpha * s;
   const double r = r0 - alpha * aq;
@@ -258,21 +256,20 @@ __global__ void __launch_bounds__(IB_NT) ib_az_kernel(ListGeom g, CgBufs cg,
     cg.az[e] = az;
     v[0] += cg.r[n] * z0;
     v[1] += z0 * az;
-    v[2] += cg.q[e] * az;
+    v[2] += z0 * cg.aq[e];
   }
   if (grid_sums<3>(v, cg.part, cg.ticket, sh) && threadIdx.x == 0)
     scalars(cg.scal, v[0], v[1], v[2]);
 }
 
-__global__ void __launch_bounds__(IB_NT) ib_step_kernel(CgBufs cg, const double* __restrict__ z,
-                                                        double tol2, int maxiter) {
+__global__ void __launch_bounds__(IB_NT) ib_step_kernel(CgBufs cg, double tol2, int maxiter) {
   __shared__ double sh[1][IB_NT];
   if (cg.scal[CG_DONE] != 0.0) return;
   const double alpha = cg.scal[CG_ALPHA], beta = cg.scal[CG_BETA];
   double v[1] = {0.0};
   for (int e = blockIdx.x * IB_NT + threadIdx.x; e < cg.n; e += gridDim.x * IB_NT) {
     const int n = cg.idx[e];
-    const double r = take_step(cg, e, n, z[n], cg.az[e], alpha, beta);
+    const double r = take_step(cg, e, n, alpha, beta);
     v[0] += r * r;
   }
   if (grid_sums<1>(v, cg.part, cg.ticket, sh) && threadIdx.x == 0)
@@ -317,7 +314,7 @@ __global__ void __launch_bounds__(IB_ONE) ib_iterate_kernel(ListGeom g, CgBufs c
     cg.az[e] = az;
     v[0] += cg.r[n] * z0;
     v[1] += z0 * az;
-    v[2] += cg.q[e] * az;
+    v[2] += z0 * cg.aq[e];
   }
   one_block_sums<3>(v, sh);
   if (threadIdx.x == 0) scalars(sc, v[0], v[1], v[2]);
@@ -327,7 +324,7 @@ __global__ void __launch_bounds__(IB_ONE) ib_iterate_kernel(ListGeom g, CgBufs c
 #pragma unroll 4
   for (int e = threadIdx.x; e < cg.n; e += IB_ONE) {
     const int n = cg.idx[e];
-    const double r = take_step(cg, e, n, z[n], cg.az[e], alpha, beta);
+    const double r = take_step(cg, e, n, alpha, beta);
     r2[0] += r * r;
   }
   one_block_sums<1>(r2, sh);
@@ -410,7 +407,7 @@ hipError_t launch_ib_iterate(const Dims& d, const uint8_t* bits, double rdx2, do
     return hipGetLastError();
   }
   hipLaunchKernelGGL(ib_az_kernel, dim3(list_grid(cg)), dim3(IB_NT), 0, s, g, cg, z);
-  hipLaunchKernelGGL(ib_step_kernel, dim3(list_grid(cg)), dim3(IB_NT), 0, s, cg, z, tol2, maxiter);
+  hipLaunchKernelGGL(ib_step_kernel, dim3(list_grid(cg)), dim3(IB_NT), 0, s, cg, tol2, maxiter);
   return hipGetLastError();
 }
 

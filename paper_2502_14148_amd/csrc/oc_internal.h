@@ -480,10 +480,10 @@ struct CgBufs {
   double* b;         // dense: right-hand side; on the list, the steps taken
   double* r;         // dense: residual, zero off the list
   const int* idx;    // the list: dense indices, ascending
-  double* s;         // compact, per list entry: q = P L^-1 s (search direction)
-  double* q;
+  double* s;         // compact, per list entry: q = P L^-1 s is the search direction
   double* aq;        // A q
-  double* az;        // A z of this iteration
+  double* az;        // A z of this iteration; in the spectral buffer, whose
+                     // contents the box solve that gave z has used up
   double* part;      // IB_PART_CAP
   double* bpart;     // IB_NPART partial sums of b^2
   double* scal;      // CG_NSCAL scalars

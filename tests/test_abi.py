@@ -279,3 +279,25 @@ def test_new_calls_reject_null_arguments():
     assert lib.oc_autotune(None, None) == -1
     assert lib.oc_ensemble_set_tuning(None, None) == -1
     assert lib.oc_diagnostics(None, None, None) == -1
+
+
+@pytest.mark.parametrize("n,precision", [((8, 8, 8), 0), ((96, 32, 64), 1), ((256, 256, 256), 1)])
+def test_immersed_workspace(n, precision):
+    """What an immersed boundary adds to a model's workspace: the mask and the
+    cells' geometry bytes, four FP64 vectors and the list's indices, and
+    partial sums."""
+    lib = oc.load_library()
+    g = ctypes.c_void_p()
+    gd = oc.GridDesc(*n, oc.OC_BOUNDED, 0, 1, 0, 1, 0, 1, oc.OC_RECTILINEAR, 0.0)
+    assert lib.oc_grid_create(ctypes.byref(gd), ctypes.byref(g)) == 0
+    md = oc.ModelDesc()
+    md.precision, md.advection, md.weno_eps, md.weno_q = precision, 1, 1e-15, 2
+    md.ntracers, md.buoyancy = 2, 1
+    plain, imm = ctypes.c_uint64(), ctypes.c_uint64()
+    assert lib.oc_model_workspace_size(g, ctypes.byref(md), ctypes.byref(plain)) == 0
+    md.immersed, md.cg_tol, md.cg_maxiter = 1, 1e-13, 200
+    assert lib.oc_model_workspace_size(g, ctypes.byref(md), ctypes.byref(imm)) == 0
+    cells = n[0] * n[1] * n[2]
+    mask = (n[0] + 6) * (n[1] + 6) * (n[2] + 6) * (8 if precision == 0 else 4)
+    assert imm.value - plain.value <= mask + cells * (1 + 4 * 8 + 4) + (1 << 17)
+    assert lib.oc_grid_destroy(g) == 0
