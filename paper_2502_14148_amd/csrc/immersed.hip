@@ -170,9 +170,17 @@ __device__ inline double apply_at(const ListGeom& g, const double* __restrict__ 
   const int xm = (i == 0) ? n + g.d.nx - 1 : n - 1, xp = (i + 1 == g.d.nx) ? n - i : n + 1;
   const int ym = (j == 0) ? n + sz - sy : n - sy, yp = (j + 1 == g.d.ny) ? n - j * sy : n + sy;
   const int zm = (k == 0) ? n + (g.d.nz - 1) * sz : n - sz, zp = (k + 1 == g.d.nz) ? n - k * sz : n + sz;
-  auto dif = [&](unsigned bit, int m) { return (fb & bit) ? z[m] - z0 : 0.0; };
-  return (dif(IB_XM, xm) + dif(IB_XP, xp)) * g.rdx2 + (dif(IB_YM, ym) + dif(IB_YP, yp)) * g.rdy2 +
-         (dif(IB_ZM, zm) + dif(IB_ZP, zp)) * g.rdz2;
+  // all six loads before the first difference (with a load in each difference
+  // they wait for each other: 128^3 with 15 % of the cells immersed, a list of
+  // 1 million, 19.9 ms a step instead of 14.2; loading also across closed faces
+  // costs a 256^3 seamount 1 %)
+  auto at = [&](unsigned bit, int m) { return (fb & bit) ? z[m] : 0.0; };
+  const double vxm = at(IB_XM, xm), vxp = at(IB_XP, xp), vym = at(IB_YM, ym),
+               vyp = at(IB_YP, yp), vzm = at(IB_ZM, zm), vzp = at(IB_ZP, zp);
+  auto dif = [&](unsigned bit, double v) { return (fb & bit) ? v - z0 : 0.0; };
+  return (dif(IB_XM, vxm) + dif(IB_XP, vxp)) * g.rdx2 +
+         (dif(IB_YM, vym) + dif(IB_YP, vyp)) * g.rdy2 +
+         (dif(IB_ZM, vzm) + dif(IB_ZP, vzp)) * g.rdz2;
 }
 
 // Stopping test after an iteration (an update of the iterate) with squared
@@ -187,19 +195,22 @@ __device__ inline void stop_test(double* sc, double r2, double tol2, int maxiter
 // iterations that are counted and limited (k of them from here leave a smaller
 // residual than k from p = 0); only where it meets the tolerance by itself is
 // it one.
+template <int U>
 __global__ void __launch_bounds__(IB_NT) ib_start_kernel(ListGeom g, CgBufs cg,
                                                          const double* __restrict__ z,
                                                          double tol2) {
   __shared__ double sh[1][IB_NT];
   double v[1] = {0.0};
-  for (int e = blockIdx.x * IB_NT + threadIdx.x; e < cg.n; e += gridDim.x * IB_NT) {
-    const int n = cg.idx[e];
-    const double r = cg.b[n] - apply_at(g, z, n, z[n]);
-    cg.r[n] = r;
-    cg.s[e] = 0.0;
-    cg.aq[e] = 0.0;
-    v[0] += r * r;
-  }
+  double r[U];
+  list_entries<U>(
+      cg, blockIdx.x * IB_NT + threadIdx.x, gridDim.x * IB_NT,
+      [&](int q, int, int n) { r[q] = cg.b[n] - apply_at(g, z, n, z[n]); },
+      [&](int q, int e, int n) {
+        cg.r[n] = r[q];
+        cg.s[e] = 0.0;
+        cg.aq[e] = 0.0;
+        v[0] += r[q] * r[q];
+      });
   if (!grid_sums<1>(v, cg.part, cg.ticket, sh)) return;
   double b2[1] = {0.0};
   for (int b = threadIdx.x; b < IB_NPART; b += IB_NT) b2[0] += cg.bpart[b];
@@ -230,48 +241,96 @@ __device__ inline void scalars(double* sc, double rz, double zaz, double zaq) {
   sc[CG_ALPHA] = rz / qaq;
 }
 
-// The updates of list entry e (cell n): s = r + beta s, A q = A z + beta A q; the
-// step alpha s into b; r -= alpha A q.  Returns the new r.
-__device__ inline double take_step(const CgBufs& cg, int e, int n, double alpha, double beta) {
-  const double r0 = cg.r[n];
-  const double s = r0 + beta * cg.s[e], aq = cg.az[e] + beta * cg.aq[e];
-  cg.s[e] = s;
-  cg.aq[e] = aq;
-  cg.b[n] += alpha * s;
-  const double r = r0 - alpha * aq;
-  cg.r[n] = r;
-  return r;
+// Every `stride`-th list entry from e0 on, U at a time: load(q, e, n) takes what
+// entry e (cell n) needs into element q, use(q, e, n) computes and stores.  The
+// loads of U entries travel together; the compiler could not move an entry's
+// before the stores of the one ahead.  (Entries past the list's end load its last
+// one and are not used.)
+template <int U, class Load, class Use>
+__device__ inline void list_entries(const CgBufs& cg, int e0, int stride, Load load, Use use) {
+  for (int e = e0; e < cg.n; e += U * stride) {
+    int ee[U], n[U];
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+      ee[q] = min(e + q * stride, cg.n - 1);
+      n[q] = cg.idx[ee[q]];
+    }
+#pragma unroll
+    for (int q = 0; q < U; ++q) load(q, ee[q], n[q]);
+#pragma unroll
+    for (int q = 0; q < U; ++q)
+      if (e + q * stride < cg.n) use(q, ee[q], n[q]);
+  }
+}
+
+// A z on the list, and this thread's parts of r.z, z.Az and z.Aq_old.
+template <int U>
+__device__ inline void list_az(const ListGeom& g, const CgBufs& cg, const double* __restrict__ z,
+                               int e0, int stride, double (&v)[3]) {
+  double z0[U], az[U], r[U], aq[U];
+  list_entries<U>(
+      cg, e0, stride,
+      [&](int q, int e, int n) {
+        z0[q] = z[n];
+        az[q] = apply_at(g, z, n, z0[q]);
+        r[q] = cg.r[n];
+        aq[q] = cg.aq[e];
+      },
+      [&](int q, int e, int) {
+        cg.az[e] = az[q];
+        v[0] += r[q] * z0[q];
+        v[1] += z0[q] * az[q];
+        v[2] += z0[q] * aq[q];
+      });
+}
+
+// The updates: s = r + beta s, A q = A z + beta A q; the step alpha s into b;
+// r -= alpha A q, and this thread's part of |r|^2.
+template <int U>
+__device__ inline double list_step(const CgBufs& cg, int e0, int stride, double alpha,
+                                   double beta) {
+  double r0[U], s0[U], az[U], aq0[U], b0[U], r2 = 0.0;
+  list_entries<U>(
+      cg, e0, stride,
+      [&](int q, int e, int n) {
+        r0[q] = cg.r[n];
+        s0[q] = cg.s[e];
+        az[q] = cg.az[e];
+        aq0[q] = cg.aq[e];
+        b0[q] = cg.b[n];
+      },
+      [&](int q, int e, int n) {
+        const double s = r0[q] + beta * s0[q], aq = az[q] + beta * aq0[q];
+        const double r = r0[q] - alpha * aq;
+        cg.s[e] = s;
+        cg.aq[e] = aq;
+        cg.b[n] = b0[q] + alpha * s;
+        cg.r[n] = r;
+        r2 += r * r;
+      });
+  return r2;
 }
 
 // An iteration after z = L^-1 r in two launches: A z and the scalars, then the
 // updates, |r|^2 and the stopping test.
+template <int U>
 __global__ void __launch_bounds__(IB_NT) ib_az_kernel(ListGeom g, CgBufs cg,
                                                       const double* __restrict__ z) {
   __shared__ double sh[3][IB_NT];
   if (cg.scal[CG_DONE] != 0.0) return;
   double v[3] = {0.0, 0.0, 0.0};
-  for (int e = blockIdx.x * IB_NT + threadIdx.x; e < cg.n; e += gridDim.x * IB_NT) {
-    const int n = cg.idx[e];
-    const double z0 = z[n], az = apply_at(g, z, n, z0);
-    cg.az[e] = az;
-    v[0] += cg.r[n] * z0;
-    v[1] += z0 * az;
-    v[2] += z0 * cg.aq[e];
-  }
+  list_az<U>(g, cg, z, blockIdx.x * IB_NT + threadIdx.x, gridDim.x * IB_NT, v);
   if (grid_sums<3>(v, cg.part, cg.ticket, sh) && threadIdx.x == 0)
     scalars(cg.scal, v[0], v[1], v[2]);
 }
 
+template <int U>
 __global__ void __launch_bounds__(IB_NT) ib_step_kernel(CgBufs cg, double tol2, int maxiter) {
   __shared__ double sh[1][IB_NT];
   if (cg.scal[CG_DONE] != 0.0) return;
   const double alpha = cg.scal[CG_ALPHA], beta = cg.scal[CG_BETA];
-  double v[1] = {0.0};
-  for (int e = blockIdx.x * IB_NT + threadIdx.x; e < cg.n; e += gridDim.x * IB_NT) {
-    const int n = cg.idx[e];
-    const double r = take_step(cg, e, n, alpha, beta);
-    v[0] += r * r;
-  }
+  double v[1] = {
+      list_step<U>(cg, blockIdx.x * IB_NT + threadIdx.x, gridDim.x * IB_NT, alpha, beta)};
   if (grid_sums<1>(v, cg.part, cg.ticket, sh) && threadIdx.x == 0)
     stop_test(cg.scal, v[0], tol2, maxiter);
 }
@@ -280,7 +339,7 @@ __global__ void __launch_bounds__(IB_NT) ib_step_kernel(CgBufs cg, double tol2, 
 // where the two launches and their tickets cost more than the work: a solve's
 // iteration takes 2.9 us less with it at 596 entries and 2.2 us less at 2656;
 // at 11916 one CU's gathers take 91 us against the launches' 16.
-constexpr int IB_ONE = 1024, IB_ONE_MAX = 3 * IB_ONE;
+constexpr int IB_ONE = 1024, IB_ONE_U = 3, IB_ONE_MAX = IB_ONE_U * IB_ONE;
 
 template <int K>
 __device__ inline void one_block_sums(double (&v)[K], double (*sh)[IB_ONE / 64]) {
@@ -307,26 +366,12 @@ __global__ void __launch_bounds__(IB_ONE) ib_iterate_kernel(ListGeom g, CgBufs c
   if (cg.scal[CG_DONE] != 0.0) return;
   if (threadIdx.x < CG_NSCAL) sc[threadIdx.x] = cg.scal[threadIdx.x];
   double v[3] = {0.0, 0.0, 0.0};
-#pragma unroll 4
-  for (int e = threadIdx.x; e < cg.n; e += IB_ONE) {
-    const int n = cg.idx[e];
-    const double z0 = z[n], az = apply_at(g, z, n, z0);
-    cg.az[e] = az;
-    v[0] += cg.r[n] * z0;
-    v[1] += z0 * az;
-    v[2] += z0 * cg.aq[e];
-  }
+  list_az<IB_ONE_U>(g, cg, z, threadIdx.x, IB_ONE, v);
   one_block_sums<3>(v, sh);
   if (threadIdx.x == 0) scalars(sc, v[0], v[1], v[2]);
   __syncthreads();
   const double alpha = sc[CG_ALPHA], beta = sc[CG_BETA];
-  double r2[1] = {0.0};
-#pragma unroll 4
-  for (int e = threadIdx.x; e < cg.n; e += IB_ONE) {
-    const int n = cg.idx[e];
-    const double r = take_step(cg, e, n, alpha, beta);
-    r2[0] += r * r;
-  }
+  double r2[1] = {list_step<IB_ONE_U>(cg, threadIdx.x, IB_ONE, alpha, beta)};
   one_block_sums<1>(r2, sh);
   if (threadIdx.x == 0) stop_test(sc, r2[0], tol2, maxiter);
   __syncthreads();
@@ -386,15 +431,26 @@ hipError_t launch_ib_rhs(const Dims& d, const T* u, const T* v, const T* w,
   return hipGetLastError();
 }
 
+// One entry per thread up to IB_LISTWG workgroups, beyond that IB_LISTU entries at a
+// time.  Every workgroup of a reducing kernel releases its sums device-wide at
+// the ticket, which is what more workgroups cost: 128^3 steps over scattered cells
+// with 1024, 512, 256 and 128 workgroups: 5 % of the cells immersed (a list of
+// 0.5 million) 12.0, 9.3, 8.0, 7.9 ms, 15 % (1 million) 20.0, 15.3, 13.7, 14.2 ms;
+// a 256^3 seamount (105 thousand) 9.18, -, 9.14, 9.10 ms.  With 128 and one entry
+// at a time 15 % took 16.2 ms, with two 14.4.
+constexpr int IB_LISTWG = 128, IB_LISTU = 4;
+static_assert(IB_LISTWG <= IB_LPART, "room for the partial sums");
 static int list_grid(const CgBufs& cg) {
-  return std::max(1, std::min((cg.n + IB_NT - 1) / IB_NT, IB_LPART));
+  return std::max(1, std::min((cg.n + IB_NT - 1) / IB_NT, IB_LISTWG));
 }
+static bool batched(const CgBufs& cg) { return cg.n > IB_LISTWG * IB_NT; }
 
 hipError_t launch_ib_start(const Dims& d, const uint8_t* bits, double rdx2, double rdy2,
                            double rdz2, const CgBufs& cg, const double* z, double tol2,
                            hipStream_t s) {
   const ListGeom g{d, bits, rdx2, rdy2, rdz2};
-  hipLaunchKernelGGL(ib_start_kernel, dim3(list_grid(cg)), dim3(IB_NT), 0, s, g, cg, z, tol2);
+  hipLaunchKernelGGL(batched(cg) ? ib_start_kernel<IB_LISTU> : ib_start_kernel<1>, dim3(list_grid(cg)),
+                     dim3(IB_NT), 0, s, g, cg, z, tol2);
   return hipGetLastError();
 }
 
@@ -406,8 +462,10 @@ hipError_t launch_ib_iterate(const Dims& d, const uint8_t* bits, double rdx2, do
     hipLaunchKernelGGL(ib_iterate_kernel, dim3(1), dim3(IB_ONE), 0, s, g, cg, z, tol2, maxiter);
     return hipGetLastError();
   }
-  hipLaunchKernelGGL(ib_az_kernel, dim3(list_grid(cg)), dim3(IB_NT), 0, s, g, cg, z);
-  hipLaunchKernelGGL(ib_step_kernel, dim3(list_grid(cg)), dim3(IB_NT), 0, s, cg, tol2, maxiter);
+  hipLaunchKernelGGL(batched(cg) ? ib_az_kernel<IB_LISTU> : ib_az_kernel<1>, dim3(list_grid(cg)),
+                     dim3(IB_NT), 0, s, g, cg, z);
+  hipLaunchKernelGGL(batched(cg) ? ib_step_kernel<IB_LISTU> : ib_step_kernel<1>, dim3(list_grid(cg)),
+                     dim3(IB_NT), 0, s, cg, tol2, maxiter);
   return hipGetLastError();
 }
 

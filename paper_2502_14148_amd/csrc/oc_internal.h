@@ -473,7 +473,7 @@ hipError_t launch_poisson_x_inverse_project(const Dims& d, const SpecBufs& sb, T
 // workgroup in part; the last workgroup to finish adds them in a fixed order
 // and updates the scalars in scal (indices CG_*).
 constexpr int IB_NPART = 4096;       // workgroups of the right-hand side's kernel
-constexpr int IB_LPART = 1024;       // most workgroups of the list kernels
+constexpr int IB_LPART = 1024;       // most workgroups of the others that reduce
 constexpr int IB_PART_CAP = 3 * IB_LPART;   // partial sums (at most three per workgroup)
 enum { CG_RZ = 0, CG_ALPHA, CG_BETA, CG_BNORM2, CG_RNORM2, CG_IT, CG_DONE, CG_MEAN, CG_QAQ, CG_NSCAL };
 struct CgBufs {

@@ -298,3 +298,36 @@ def test_stopped_by_the_iteration_limit(gpu_lib, case, maxiter):
     exact = immersed.solve_poisson_immersed(b, ph)
     assert rel_l2(m.get_pressure(), exact) <= rel_l2(x, exact)
     assert res <= np.linalg.norm(r) / np.linalg.norm(b)
+
+
+@pytest.mark.parametrize("frac", [0.04, 0.3])
+def test_immersed_pressure_long_lists(gpu_lib, frac):
+    """Lists of more entries than the list kernels have threads (32768), whose
+    entries are taken four at a time: 54 and 162 thousand of 64 x 64 x 64 cells,
+    neither a multiple of a batch.  The bar of the equation: the residual of
+    1e-13 and rounding, 2e-16 times |A| |p| / |b| of about (64 / 2 pi)^2 12."""
+    ph = _conv((64, 64, 64))
+    ph = dataclasses.replace(ph, solid=_scatter(ph, frac, 7))
+    c = immersed.fluid(ph) > 0
+    closed = sum(np.roll(~c, d, axis=a) for a in (1, 2) for d in (1, -1))
+    closed[1:] += ~c[:-1]
+    closed[:-1] += ~c[1:]
+    entries = int(np.sum(c & (closed > 0)))
+    assert entries > 32768 and entries % 1024, entries
+    s = inputs.random_state(ph, seed=29, divergence_free=False)
+    m = gpu_lib.Model(ph, "fp64")
+    m.set_states(s)
+    m.pressure_solve(0.37)
+    it, res = m.pressure_stats()
+    assert 1 <= it < ph.cg_maxiter and res <= ph.cg_tol, (it, res)
+    w = s["w"].copy()
+    w[0] = w[-1] = 0.0
+    u, v, w = immersed.mask_velocities(s["u"], s["v"], w, ph)
+    b = pressure.divergence(u, v, w, ph) * c / 0.37
+    p = m.get_pressure()
+    # the equation itself, on every fluid cell (at 30 % some cells are cut off
+    # from the rest, and p there is determined up to a constant)
+    assert rel_l2(immersed.laplacian(p, ph), b) <= 1e-11
+    for name, ref in zip("uvw", immersed.mask_velocities(
+            *pressure.apply_gradient(u, v, w, p, 0.37, ph), ph)):
+        assert rel_l2(m.get_state(name), ref) <= TOL["fp64"], name
