@@ -427,30 +427,30 @@ std::vector<char> padded_mask(const oc_model* m, const uint8_t* solid) {
 }
 
 // The per-cell geometry bytes of the conjugate-gradient kernels (IB_*):
-// fluid, and which faces are open (both neighbours fluid; walls closed).
+// fluid, and which faces are open (both neighbours fluid; walls closed).  Row
+// by row: the neighbours of a row's cells are four other rows and the row itself.
 std::vector<uint8_t> geometry_bits(const oc_model* m, const uint8_t* solid) {
   const Dims& d = m->dims;
-  const long n = (long)d.nx * d.ny * d.nz;
-  std::vector<uint8_t> out(n, 0);
-  auto fluid = [&](int i, int j, int k) {
-    i = (i + d.nx) % d.nx;
-    j = (j + d.ny) % d.ny;
-    k = (k + d.nz) % d.nz;
-    return !solid || solid[((size_t)k * d.ny + j) * d.nx + i] == 0;
-  };
+  const size_t n = (size_t)d.nx * d.ny * d.nz;
+  std::vector<uint8_t> fluid(n, 1), out(n, 0);
+  if (solid)
+    for (size_t c = 0; c < n; ++c) fluid[c] = solid[c] == 0;
+  const std::vector<uint8_t> closed(d.nx, 0);
+  auto row = [&](int j, int k) { return fluid.data() + ((size_t)k * d.ny + j) * d.nx; };
   for (int k = 0; k < d.nz; ++k)
-    for (int j = 0; j < d.ny; ++j)
+    for (int j = 0; j < d.ny; ++j) {
+      const uint8_t* c = row(j, k);
+      const uint8_t* ym = row((j + d.ny - 1) % d.ny, k);
+      const uint8_t* yp = row((j + 1) % d.ny, k);
+      const uint8_t* zm = d.zb && k == 0 ? closed.data() : row(j, (k + d.nz - 1) % d.nz);
+      const uint8_t* zp = d.zb && k + 1 == d.nz ? closed.data() : row(j, (k + 1) % d.nz);
+      uint8_t* o = out.data() + (c - fluid.data());
       for (int i = 0; i < d.nx; ++i) {
-        if (!fluid(i, j, k)) continue;
-        uint8_t b = IB_FLUID;
-        if (fluid(i - 1, j, k)) b |= IB_XM;
-        if (fluid(i + 1, j, k)) b |= IB_XP;
-        if (fluid(i, j - 1, k)) b |= IB_YM;
-        if (fluid(i, j + 1, k)) b |= IB_YP;
-        if ((!d.zb || k > 0) && fluid(i, j, k - 1)) b |= IB_ZM;
-        if ((!d.zb || k + 1 < d.nz) && fluid(i, j, k + 1)) b |= IB_ZP;
-        out[((size_t)k * d.ny + j) * d.nx + i] = b;
+        const int xm = c[i == 0 ? d.nx - 1 : i - 1], xp = c[i + 1 == d.nx ? 0 : i + 1];
+        o[i] = (uint8_t)(c[i] * (IB_FLUID + IB_XM * xm + IB_XP * xp + IB_YM * ym[i] +
+                                 IB_YP * yp[i] + IB_ZM * zm[i] + IB_ZP * zp[i]));
       }
+    }
   return out;
 }
 
@@ -459,7 +459,7 @@ std::vector<uint8_t> geometry_bits(const oc_model* m, const uint8_t* solid) {
 // that hold it and its neighbours across open faces (out).
 std::vector<int> boundary_list(oc_model* m, const std::vector<uint8_t>& bits) {
   const Dims& d = m->dims;
-  std::vector<int> list;
+  std::vector<int> list, line(d.nx);
   int in[4] = {d.nz, -1, d.ny, -1}, out[4] = {d.nz, -1, d.ny, -1};   // k, j: first, last
   auto see = [](int* r, int j, int k) {
     r[0] = std::min(r[0], k);
@@ -467,24 +467,32 @@ std::vector<int> boundary_list(oc_model* m, const std::vector<uint8_t>& bits) {
     r[2] = std::min(r[2], j);
     r[3] = std::max(r[3], j);
   };
-  long n = 0;
-  for (int k = 0; k < d.nz; ++k)
-    for (int j = 0; j < d.ny; ++j)
-      for (int i = 0; i < d.nx; ++i, ++n) {
-        const unsigned b = bits[n];
-        if (!(b & IB_FLUID)) continue;
-        unsigned want = IB_XM | IB_XP | IB_YM | IB_YP;
-        if (!d.zb || k > 0) want |= IB_ZM;
-        if (!d.zb || k + 1 < d.nz) want |= IB_ZP;
-        if ((b & want) == want) continue;
-        list.push_back((int)n);
-        see(in, j, k);
-        see(out, j, k);
-        if (b & IB_YM) see(out, (j + d.ny - 1) % d.ny, k);
-        if (b & IB_YP) see(out, (j + 1) % d.ny, k);
-        if (b & IB_ZM) see(out, j, (k + d.nz - 1) % d.nz);
-        if (b & IB_ZP) see(out, j, (k + 1) % d.nz);
+  for (int k = 0; k < d.nz; ++k) {
+    unsigned want = IB_FLUID | IB_XM | IB_XP | IB_YM | IB_YP;
+    if (!d.zb || k > 0) want |= IB_ZM;
+    if (!d.zb || k + 1 < d.nz) want |= IB_ZP;
+    for (int j = 0; j < d.ny; ++j) {
+      const int c0 = (k * d.ny + j) * d.nx;
+      const uint8_t* c = bits.data() + c0;
+      int found = 0;
+      unsigned open = 0;   // faces that some cell of this row's list has open
+      for (int i = 0; i < d.nx; ++i) {
+        const unsigned b = c[i];
+        const bool take = (b & IB_FLUID) && (b & want) != want;
+        line[found] = c0 + i;
+        found += take;
+        open |= take ? b : 0;
       }
+      if (!found) continue;
+      list.insert(list.end(), line.begin(), line.begin() + found);
+      see(in, j, k);
+      see(out, j, k);
+      if (open & IB_YM) see(out, (j + d.ny - 1) % d.ny, k);
+      if (open & IB_YP) see(out, (j + 1) % d.ny, k);
+      if (open & IB_ZM) see(out, j, (k + d.nz - 1) % d.nz);
+      if (open & IB_ZP) see(out, j, (k + 1) % d.nz);
+    }
+  }
   if (list.empty()) in[0] = in[1] = in[2] = in[3] = out[0] = out[1] = out[2] = out[3] = 0;
   SpecBufs& sb = m->cgbox;
   sb = m->sb;
