@@ -41,7 +41,8 @@ __device__ inline T interp4(T a0, T a1, T a2, T a3) {
 // c2 = 2 (c - b), n3 = 2 (c - d), and their differences t0 = c2 + 2 (a - b),
 // t1 = -n3 - c2, t2 = 2 (e - d) + n3 (each rounded as its half would be),
 //   * candidates as deviations from the upwind neighbour c:
-//       4 (r0 - c) = c2 + 2/3 t0, 12 (r1 - c) = 2 (c2 - 2 n3), 12 (r2 - c) = -(3 n3 + t2);
+//       4 (r0 - c) = c2 + 2/3 t0, 4 (r1 - c) = c2 + 2/3 t1 = 1/3 (c2 - 2 n3),
+//       4 (r2 - c) = -(n3 + 1/3 t2);
 //   * four times the Jiang-Shu indicators plus eps, as t (4/3 t + n) + n^2 +
 //     4 eps: s0 with (t0, c2), s1 with (t1, c2), s2 with (t2, n3)
 //     (the weights only see ratios, so the common factor drops out);
@@ -53,10 +54,14 @@ __device__ inline T interp4(T a0, T a1, T a2, T a3) {
 // Two reciprocals in 45 operations (51 and three reciprocals with one each for
 // s0 and s2, which cost 2 to 4 % of a whole step).
 // FP32 range: next to flat stencils s0 s2 and s1^2 are 16 eps^2, normal for
-// eps above 2.72e-20 (undoubled differences took the same number of
-// operations, 0.1 to 0.4 % of a step less time for their encodings, and needed
-// eps above 1.1e-19); tau s1 / s_k stays below 1.8e19 for indicators up to ~1e2
-// in the field's units squared next to an exactly flat stencil at eps = 1e-15.
+// eps above 2.72e-20 (with undoubled differences, in as many operations, eps had
+// to be above 1.1e-19); tau s1 / s_k stays below 1.8e19 for indicators up to
+// ~1e2 in the field's units squared next to an exactly flat stencil at eps =
+// 1e-15.
+// Four steps at 256^3 FP32, two at 96x64x128 FP64: 10.04 ms and 671 us; undoubled
+// differences 10.07 and 671; both factors in the candidates 10.13 and 669, both
+// on the weights 10.04 and 680; indicators scaled by two multiplications 10.15
+// and 677.
 template <class T, int SCHEME>
 __device__ inline T rec6(T m3, T m2, T m1, T p0, T p1, T p2, T vel, T eps) {
   const bool pos = vel > T(0);
@@ -78,12 +83,22 @@ __device__ inline T rec6(T m3, T m2, T m1, T p0, T p1, T p2, T vel, T eps) {
   const T s1s = s1 * s1;
   const T g = tau * s1 * rcp(s0 * s2);
   const T g0 = g * s2, g2 = g * s0;
-  const T a0 = fmad(g0, g0, s1s);
-  const T a1 = T(2) * fmad(tau, tau, s1s);   // twice a1
-  const T a2 = fmad(g2, g2, s1s);
-  const T num = fmad(a0, fmad(T(2.0 / 3.0), t0, c2),
-                     fmad(a1, fmad(T(-2), n3, c2), -(a2 * fmad(T(3), n3, t2))));
-  const T den = fmad(T(3), a1 + a2, a0);
+  const T a0 = fmad(g0, g0, s1s), a1 = fmad(tau, tau, s1s), a2 = fmad(g2, g2, s1s);
+  // 4 (W - c); the weights' factors 6 and 3 where the type encodes them best:
+  // FP32 multiply-adds carry a literal, FP64 constants take registers
+  const T e0 = fmad(T(2.0 / 3.0), t0, c2);
+  T num, den;
+  if constexpr (sizeof(T) == 4) {
+    const T b1 = T(6) * a1, b2 = T(3) * a2;
+    const T e1 = fmad(T(2.0 / 3.0), t1, c2), e2 = fmad(T(1.0 / 3.0), t2, n3);
+    num = fmad(a0, e0, fmad(b1, e1, -(b2 * e2)));
+    den = a0 + b1 + b2;
+  } else {
+    const T b1 = T(2) * a1;
+    const T e1 = fmad(T(-2), n3, c2), e2 = fmad(T(3), n3, t2);
+    num = fmad(a0, e0, fmad(-a2, e2, b1 * e1));
+    den = fmad(T(3), b1 + a2, a0);
+  }
   return fmad(T(0.25), num * rcp(den), c);
 }
 
