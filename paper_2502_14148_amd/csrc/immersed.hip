@@ -23,7 +23,7 @@
 // whose last pass is the projection's.  Against the iteration on dense
 // vectors (operator, direction and residual passes of 83 bytes per cell and
 // an unrestricted solve each time) a 128^3 step over a seamount went from
-// 6.9 to 3.2 ms, a 256^3 one from 30.2 to 10.6 ms, with the same residuals.
+// 6.9 to 3.1 ms, a 256^3 one from 29.8 to 10.0 ms, with the same residuals.
 //
 // Vectors are FP64; the geometry comes as one byte per cell (IB_* bits: the
 // cell is fluid, and which of its six faces are open).  Reductions are

@@ -51,11 +51,11 @@ __device__ inline T interp4(T a0, T a1, T a2, T a3) {
 //     tau^2, 3 a2 with a2 = s1^2 + (tau s1 / s2)^2, both quotients from the one
 //     reciprocal of s0 s2;
 //   * W = c + (a0 (r0 - c) + 6 a1 (r1 - c) + 3 a2 (r2 - c)) / (a0 + 6 a1 + 3 a2).
-// Two reciprocals in 45 operations (51 and three reciprocals with one each for
-// s0 and s2, which cost 2 to 4 % of a whole step).
+// Two reciprocals in 45 operations (46 in FP32, of shorter encodings; 51 and three
+// reciprocals with one each for s0 and s2, which cost 2 to 4 % of a whole step).
 // FP32 range: next to flat stencils s0 s2 and s1^2 are 16 eps^2, normal for
-// eps above 2.72e-20 (with undoubled differences, in as many operations, eps had
-// to be above 1.1e-19); tau s1 / s_k stays below 1.8e19 for indicators up to
+// eps above 2.72e-20 (with undoubled differences, in 45 operations, eps had to be
+// above 1.1e-19); tau s1 / s_k stays below 1.8e19 for indicators up to
 // ~1e2 in the field's units squared next to an exactly flat stencil at eps =
 // 1e-15.
 // Four steps at 256^3 FP32, two at 96x64x128 FP64: 10.04 ms and 671 us; undoubled
