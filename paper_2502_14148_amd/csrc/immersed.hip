@@ -244,15 +244,15 @@ __device__ inline void scalars(double* sc, double rz, double zaz, double zaq) {
 // Every `stride`-th list entry from e0 on, U at a time: load(q, e, n) takes what
 // entry e (cell n) needs into element q, use(q, e, n) computes and stores.  The
 // loads of U entries travel together; the compiler could not move an entry's
-// before the stores of the one ahead.  (Entries past the list's end load its last
-// one and are not used.)
+// before the stores of the one ahead.  (Past the list's end the thread's own entry
+// e is loaded again and not used: no other thread stores to it.)
 template <int U, class Load, class Use>
 __device__ inline void list_entries(const CgBufs& cg, int e0, int stride, Load load, Use use) {
   for (int e = e0; e < cg.n; e += U * stride) {
     int ee[U], n[U];
 #pragma unroll
     for (int q = 0; q < U; ++q) {
-      ee[q] = min(e + q * stride, cg.n - 1);
+      ee[q] = e + q * stride < cg.n ? e + q * stride : e;
       n[q] = cg.idx[ee[q]];
     }
 #pragma unroll
